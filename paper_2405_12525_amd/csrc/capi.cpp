@@ -12,6 +12,7 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -165,6 +166,13 @@ struct mpk_plan_s {
     DevBuf d_rowptr, d_col, d_val, d_outrow, d_perm;
     DevBuf d_soff, d_rlen, d_scol, d_sval;   // sliced layout (empty if not built)
     DevBuf d_sdel;                           // its 16-bit column offsets (if they fit)
+    DevBuf d_dcount, d_dia;                  // diagonal slices (empty if not built)
+    const DiaSlice *dsl = nullptr;           // parts of d_dia
+    const DiaGroup *dgroup = nullptr;
+    const DiaRowMask *dmask = nullptr;
+    const void *dvals = nullptr;
+    const int32_t *drow = nullptr;
+    int32_t dgroups = 0;
     int64_t sell_entries = 0;
     std::map<int, std::unique_ptr<SliceSet>> spmv_slices;  // p x SpMV, by slice size
     // schedules and workspaces
@@ -174,6 +182,7 @@ struct mpk_plan_s {
     std::vector<std::unique_ptr<SchedEntry>> retired;
     std::vector<std::unique_ptr<Workspace>> pool;
     std::map<long long, int> wg_cache;
+    std::set<std::pair<int, int>> shapes;         // (powers, slice size) run or prepared unscheduled
     std::map<hipStream_t, hipEvent_t> stream_ev;  // last run issued per stream
     DevBuf status_words;                          // kStatusSlots failure words
     std::map<hipStream_t, int> status_slot;       // stream -> its word
@@ -183,7 +192,8 @@ struct mpk_plan_s {
         return DevMatrix{d_rowptr.as<int32_t>(), d_col.as<int32_t>(), d_val.ptr,
                          d_outrow.as<int32_t>(), (int32_t)n, value_bits,
                          d_soff.as<const int64_t>(), d_rlen.as<int32_t>(), d_scol.as<int32_t>(),
-                         d_sdel.as<int16_t>(), d_sval.ptr};
+                         d_sdel.as<int16_t>(), d_sval.ptr,
+                         dsl, dgroup, dmask, dvals, drow, dgroups};
     }
     ~mpk_plan_s() {
         if (!host_only) {
@@ -413,6 +423,105 @@ mpk_status_t build_sell(mpk_plan_t plan) {
     return MPK_OK;
 }
 
+// The diagonal slices of the plan's matrix, where at least half of its slices
+// have one.  Slices with equal lists share one: a box stencil has a few dozen
+// lists however many rows it has.
+mpk_status_t build_dia(mpk_plan_t plan) {
+    if (!plan->d_scol.ptr) return MPK_OK;
+    mpk_status_t st;
+    const size_t n = (size_t)plan->n, n_sl = (n + kDiaRows - 1) / kDiaRows;
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    // device buffers: the rows' places in the sliced layout (permuted plans,
+    // whose vectors stay in the caller's order) and the counts; then one block
+    // for all that the kernels read (each hipMalloc and hipFree costs ~0.3 ms)
+    const bool permuted = plan->d_outrow.ptr != nullptr;
+    const size_t row_b = permuted ? up(n * 4) : 0;
+    if ((st = plan->d_dcount.alloc(row_b + n_sl * sizeof(DiaCount)))) return st;
+    char *c0 = plan->d_dcount.as<char>();
+    const int32_t *drow = permuted ? reinterpret_cast<const int32_t *>(c0) : nullptr;
+    if (permuted) {
+        hipError_t e = hipMemcpy(c0, plan->lv.iperm.data(), n * 4, hipMemcpyHostToDevice);
+        if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
+    }
+    const int64_t *soff = plan->d_soff.as<const int64_t>();
+    const int32_t *rlen = plan->d_rlen.as<int32_t>(), *scol = plan->d_scol.as<int32_t>();
+    std::vector<DiaCount> cnt;
+    int rc = gpu_dia_count(plan->n, drow, soff, rlen, scol, plan->d_sval.ptr, plan->value_bits,
+                           plan->d_sdel.ptr ? 16 : 32, reinterpret_cast<DiaCount *>(c0 + row_b), cnt);
+    if (rc) return hip_fail((hipError_t)rc, "diagonal slices");
+    size_t taken = 0;
+    for (const DiaCount &c : cnt) taken += c.count >= 0;
+    if (2 * taken < n_sl) {
+        plan->d_dcount.release();
+        return MPK_OK;
+    }
+    std::vector<DiaSlice> sl(n_sl);
+    std::vector<uint8_t> emit(n_sl);
+    for (int share = 1; share >= 0; --share) {   // equal lists shared; else a list per slice
+        std::map<std::pair<uint64_t, int32_t>, int32_t> seen;
+        uint64_t last_hash = 0;
+        int32_t last_first = -1, last_count = -1;
+        int64_t groups = 0, blocks = 0;
+        for (size_t s = 0; s < n_sl; ++s) {
+            const DiaCount &c = cnt[s];
+            emit[s] = 0;
+            const int64_t r0 = (int64_t)s * kDiaRows, r1 = r0 + kDiaRows - 1;
+            const bool edge = r1 >= plan->n ||
+                              (c.count > 0 && (r0 + c.lo < 0 || r1 + c.hi >= plan->n));
+            const int kind = c.vblocks == 0 ? kDiaShared
+                             : c.vblocks == c.count ? kDiaPerRow : kDiaMixed;
+            sl[s] = DiaSlice{0, c.count, (int32_t)blocks, kind | (edge ? kDiaEdge : 0),
+                             {c.whole[0], c.whole[1]}};
+            if (c.count < 0) continue;
+            blocks += c.vblocks;
+            if (share && last_first >= 0 && c.hash == last_hash && c.count == last_count) {
+                sl[s].first = last_first;
+                continue;
+            }
+            auto it = share ? seen.find({c.hash, c.count}) : seen.end();
+            if (it != seen.end()) {
+                sl[s].first = it->second;
+            } else {
+                sl[s].first = (int32_t)groups;
+                emit[s] = 1;
+                if (share) seen.emplace(std::make_pair(c.hash, c.count), sl[s].first);
+                groups += (c.count + 3) / 4;
+            }
+            last_hash = c.hash;
+            last_count = c.count;
+            last_first = sl[s].first;
+        }
+        if (groups > INT32_MAX || blocks > INT32_MAX) return MPK_OK;
+        const size_t g_b = up((size_t)groups * sizeof(DiaGroup)),
+                     m_b = up((size_t)groups * sizeof(DiaRowMask)),
+                     s_b = up(n_sl * sizeof(DiaSlice)), e_b = up(n_sl + 256);
+        if ((st = plan->d_dia.alloc(g_b + m_b + s_b + e_b +
+                                    (size_t)blocks * kDiaRows * (plan->value_bits / 8))))
+            return st;
+        char *b = plan->d_dia.as<char>();
+        DiaGroup *dgroup = reinterpret_cast<DiaGroup *>(b);
+        DiaRowMask *dmask = reinterpret_cast<DiaRowMask *>(b + g_b);
+        DiaSlice *dsl = reinterpret_cast<DiaSlice *>(b + g_b + m_b);
+        uint8_t *demit = reinterpret_cast<uint8_t *>(b + g_b + m_b + s_b);
+        void *dvals = b + g_b + m_b + s_b + e_b;
+        int differ = 0;
+        rc = gpu_dia_fill(plan->n, drow, soff, rlen, scol, plan->d_sval.ptr, plan->value_bits, sl,
+                          emit, groups, dsl, demit, dgroup, dmask, dvals, &differ);
+        if (rc) return hip_fail((hipError_t)rc, "diagonal slices");
+        if (!differ) {
+            plan->dsl = dsl;
+            plan->dgroup = dgroup;
+            plan->dmask = dmask;
+            plan->dvals = dvals;
+            plan->drow = drow;
+            for (const DiaCount &c : cnt)
+                plan->dgroups = std::max(plan->dgroups, (c.count + 3) / 4);
+            return MPK_OK;
+        }
+    }
+    return MPK_OK;   // not reached: a list of its own always matches
+}
+
 // Device-side state every device plan holds from the start (allocated
 // outside any capture): the zeroed failure words.
 mpk_status_t init_device_state(mpk_plan_t plan) {
@@ -453,6 +562,11 @@ int default_workgroups(mpk_plan_t plan, int R) {
     if (wg <= 0) wg = 1024;
     plan->wg_cache[key] = wg;
     return wg;
+}
+
+int default_workgroups_locked(mpk_plan_t plan, int R) {
+    std::lock_guard<std::mutex> g(plan->mu);
+    return default_workgroups(plan, R);
 }
 
 mpk_status_t check_run_args(mpk_plan_t plan, const double *x, int p, int nrhs, double *Y) {
@@ -533,12 +647,117 @@ void acc_flushes(const double *w, int p, std::vector<uint8_t> &f) {
     if (!started) f[(size_t)p] = kAccZero;
 }
 
+// Slice table of the p x SpMV kernel for R right-hand sides, built once
+// (plan->mu held).
+mpk_status_t spmv_slices(mpk_plan_t plan, int R, SliceSet **out) {
+    const int key = slice_nnz(kSpmvKP, R);
+    auto it = plan->spmv_slices.find(key);
+    if (it == plan->spmv_slices.end()) {
+        auto ss = std::make_unique<SliceSet>();
+        if (!plan->d_scol.ptr) {   // the sliced layout's kernels need no table
+            const std::vector<int32_t> whole{0, (int32_t)plan->n};
+            mpk_status_t st = make_slices(plan->rowptr, whole, key, false, *ss);
+            if (st) return st;
+        }
+        it = plan->spmv_slices.emplace(key, std::move(ss)).first;
+    }
+    *out = it->second.get();
+    return MPK_OK;
+}
+
+// The powers one after the other, one launch each (Y the p outputs, or with
+// poly the two-slot ring).
+mpk_status_t launch_powers(mpk_plan_t plan, const SliceSet *sl, const double *x, int p, int nrhs,
+                           const double *alpha, const double *beta, const double *gamma, double *Y,
+                           const Poly *poly, void *stream_v) {
+    const bool recur = alpha != nullptr;
+    const size_t stride = (size_t)plan->n * nrhs;
+    const DevMatrix m = plan->matrix();
+    for (int k = 1; k <= p; ++k) {
+        // with poly, Y is a ring of two: power k in slot (k-1) mod 2
+        const size_t o_in = poly ? (size_t)((k - 2) & 1) : (size_t)(k - 2);
+        const size_t o_prev = poly ? (size_t)((k - 3) & 1) : (size_t)(k - 3);
+        const size_t o_out = poly ? (size_t)((k - 1) & 1) : (size_t)(k - 1);
+        const double *in = k == 1 ? x : Y + o_in * stride;
+        const double *prev = k == 1 ? nullptr : (k == 2 ? x : Y + o_prev * stride);
+        double *out = Y + o_out * stride;
+        AccStep as{};
+        if (poly) {
+            as.acc_a = poly->acc_a;
+            as.acc_b = poly->acc_b;
+            for (int i = 0; i < 3; ++i) {  // powers k-2, k-1, k
+                as.wa[i] = poly->w(poly->wa, k - 2 + i);
+                as.wb[i] = poly->w(poly->wb, k - 2 + i);
+            }
+            as.fa = poly->fa[(size_t)k];
+            as.fb = poly->fb[(size_t)k];
+        }
+        int rc = launch_spmv_power(m, sl->view(), sl->n_slices, kSpmvSlicesPerWG, in, prev, out,
+                                   nrhs, recur ? 1 : 0, recur ? alpha[k - 1] : 1.0,
+                                   recur ? beta[k - 1] : 0.0, recur ? gamma[k - 1] : 0.0,
+                                   poly ? &as : nullptr, stream_v);
+        if (rc) return hip_fail((hipError_t)rc, "spmv kernel launch");
+    }
+    return MPK_OK;
+}
+
+// Tunings that leave the order of the work to the library (the default
+// schedule with no slack or workgroup count asked for): the powers then run
+// one launch each.  The persistent kernel pays a dependency check, a barrier
+// and write-through stores per task, and where rows are permuted an L2
+// invalidation too; with the slack that this tuning would give it, it was
+// slower wherever the plan has diagonal slices (5-point 64^2, p = 4: 33
+// against 18 us; 27-point 128^3, p = 8: 1067 against 156 us; Anderson 160^3
+// with 8 right-hand sides, p = 16: 7568 against 3023 us), its runs need that
+// invalidation (random band of 2^22 rows in BFS order, p = 6: 4245 against
+// 2405 us) or the rows are staged from CSR (the same band in its own order:
+// 3450 against 2230 us).  Elsewhere it stays (27-point 96^3 in plan order, p =
+// 8: 340 against 444 us).
+bool library_order(const mpk_tune_t &t) {
+    return t.schedule == MPK_SCHED_WAVE && t.lag == 0 && t.workgroups == 0 && t.skip_ahead == 0 &&
+           !t.acquire_always;
+}
+
+// Whether such a run can do without a schedule: whatever the right-hand sides
+// and pointers, it takes one launch per power.
+bool never_scheduled(mpk_plan_t plan) {
+    return library_order(plan->tune) && plan->dsl &&
+           plan->n / kChunkRows + 1 + kMaxQueues + 2 <= kScratchWords;
+}
+
 // The run of mpk_run_noalloc: the device's scratch workspace and the
 // caller's status word instead of a pooled workspace and the stream's word.
 struct NoAlloc {
     int32_t *scratch;
     int32_t *status;
 };
+
+mpk_status_t check_scratch(int32_t n_chunks) {
+    if ((int64_t)n_chunks + kMaxQueues + 2 <= kScratchWords) return MPK_OK;
+    return fail(MPK_EUNSUPPORTED, "the schedule has " + std::to_string(n_chunks) +
+                                      " chunks; the no-allocation run holds at most " +
+                                      std::to_string(kScratchWords - kMaxQueues - 2) +
+                                      " (raise tune.chunk_nnz)");
+}
+
+// What a run of a segment of ps powers fetches first (plan->mu held): the
+// schedule, the slice table and a workspace (fresh: a never-used one, which a
+// capture on `stream` can take without an event query).
+mpk_status_t prepare_segment(mpk_plan_t plan, int ps, int nrhs, int wg_default, hipStream_t stream,
+                             bool fresh) {
+    if (never_scheduled(plan)) {
+        plan->shapes.insert({ps, slice_nnz(kTaskKP, nrhs)});
+        return MPK_OK;
+    }
+    SchedEntry *se = nullptr;
+    mpk_status_t st = get_schedule(plan, ps, &se, wg_default);
+    if (st) return st;
+    SliceSet *ss = nullptr;
+    if ((st = task_slices(plan, se, nrhs, &ss))) return st;
+    if (!se->host.step_ptr.empty()) return MPK_OK;
+    Workspace *ws = nullptr;
+    return get_workspace(plan, se->host.n_chunks(), stream, false, &ws, fresh);
+}
 
 // Y is the output (p vectors), or with poly the two-slot ring.  With `na`
 // nothing is built, allocated or recorded: schedules, slice tables and the
@@ -577,9 +796,12 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
     const size_t stride = (size_t)plan->n * nrhs;
     const DevMatrix m = plan->matrix();
     const int seg = plan->tune.seg_powers > 0 ? plan->tune.seg_powers : kMaxSegPowers;
+    const bool unscheduled = never_scheduled(plan);
+    const int key = slice_nnz(kTaskKP, nrhs);
     if (na) {  // the caller's status word reports this run only: 0 until a wait fails
         for (int base = 0; base < p; base += seg)
-            if (!plan->scheds.count(std::min(seg, p - base)))
+            if (!plan->scheds.count(std::min(seg, p - base)) &&
+                !(unscheduled && plan->shapes.count({std::min(seg, p - base), key})))
                 return fail(MPK_EINVAL,
                             "no schedule for this p: call mpk_plan_prepare(plan, p, nrhs) first");
         int32_t *b = na->scratch;
@@ -587,8 +809,25 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
         int rc = launch_reset(w0, 0, stream, true);
         if (rc) return hip_fail((hipError_t)rc, "reset kernel launch");
     }
+    // Without an invalidating acquire per task, an output line must never be
+    // read before it is complete: the chunks must own whole 128-byte lines of
+    // every output vector (line-closed schedule, plan row order, 128-byte
+    // aligned outputs with n*R a multiple of 16) and no address may be
+    // written twice in a run (not so for the ring of the weighted-sum kernels).
+    const bool lines_can = !poly && !plan->d_outrow.ptr &&
+                           ((size_t)plan->n * nrhs) % kLineRows == 0 &&
+                           reinterpret_cast<uintptr_t>(Y) % 128 == 0;
+    const bool per_power = library_order(plan->tune) &&
+                           (m.dsl || !m.scol || !lines_can);
     for (int base = 0; base < p; base += seg) {
         const int ps = std::min(seg, p - base);
+        if (unscheduled) {
+            if ((capturing || na) && !plan->shapes.count({ps, key}))
+                return fail(MPK_EINVAL, "not prepared for this p and RHS count: call "
+                                        "mpk_plan_prepare or run once outside capture first");
+            plan->shapes.insert({ps, key});
+            continue;
+        }
         if (na && !plan->scheds.count(ps))
             return fail(MPK_EINVAL, "no schedule for this p: call mpk_plan_prepare(plan, p, nrhs) first");
         if (capturing && !plan->scheds.count(ps))  // building one would copy synchronously
@@ -635,6 +874,10 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
         if ((capturing || na) && !se->slices.count(slice_nnz(kTaskKP, nrhs)))
             return fail(MPK_EINVAL, "no slice table for this RHS count: call mpk_plan_prepare first");
         if ((st = task_slices(plan, se, nrhs, &ss))) return st;
+        if (per_power) {
+            if (na && (st = check_scratch(se->host.n_chunks()))) return st;
+            continue;   // launched below, once every segment's state is there
+        }
         if (!se->host.step_ptr.empty()) {
             // one launch per diagonal; stream order separates the diagonals
             const auto &sp = se->host.step_ptr;
@@ -651,12 +894,7 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
         Workspace *ws = nullptr;
         DevWorkspace wv;
         if (na) {
-            if ((int64_t)nc + kMaxQueues + 2 > kScratchWords)
-                return fail(MPK_EUNSUPPORTED,
-                            "the schedule has " + std::to_string(nc) +
-                                " chunks; the no-allocation run holds at most " +
-                                std::to_string(kScratchWords - kMaxQueues - 2) +
-                                " (raise tune.chunk_nnz)");
+            if ((st = check_scratch(nc))) return st;
             int32_t *b = na->scratch;
             wv = DevWorkspace{b, b + nc, b + nc + kMaxQueues, b + nc + kMaxQueues + 1, na->status};
         } else {
@@ -669,15 +907,7 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
                        se->host.n_chunks()};
         int rc = launch_reset(wv, nc, stream);
         if (rc) return hip_fail((hipError_t)rc, "reset kernel launch");
-        // Without an invalidating acquire per task, an output line must
-        // never be read before it is complete: the chunks must own whole
-        // 128-byte lines of every output vector (line-closed schedule, plan
-        // row order, 128-byte aligned outputs with n*R a multiple of 16) and
-        // no address may be written twice in a run (not so for the ring of
-        // the weighted-sum kernels).
-        const bool lines_own = se->host.line_closed && !poly && !plan->d_outrow.ptr &&
-                               ((size_t)plan->n * nrhs) % kLineRows == 0 &&
-                               reinterpret_cast<uintptr_t>(Y) % 128 == 0;
+        const bool lines_own = se->host.line_closed && lines_can;
         const int acquire = (plan->tune.acquire_always || !lines_own) ? 1 : 0;
         const bool xcd = !se->host.qptr.empty();
         // static task order: only where the launch can hold the device alone
@@ -730,23 +960,15 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
             ws->last_stream = stream;
         }
     }
-    if (!capturing && !na && (st = note_stream(plan, stream))) return st;
-    return MPK_OK;
-}
-
-// Slice table of the p x SpMV kernel for R right-hand sides, built once
-// (plan->mu held).
-mpk_status_t spmv_slices(mpk_plan_t plan, int R, SliceSet **out) {
-    const int key = slice_nnz(kSpmvKP, R);
-    auto it = plan->spmv_slices.find(key);
-    if (it == plan->spmv_slices.end()) {
-        auto ss = std::make_unique<SliceSet>();
-        const std::vector<int32_t> whole{0, (int32_t)plan->n};
-        mpk_status_t st = make_slices(plan->rowptr, whole, key, false, *ss);
-        if (st) return st;
-        it = plan->spmv_slices.emplace(key, std::move(ss)).first;
+    if (per_power) {
+        SliceSet *sl = nullptr;
+        if ((capturing || na) && !plan->spmv_slices.count(slice_nnz(kSpmvKP, nrhs)))
+            return fail(MPK_EINVAL, "no slice table for this RHS count: call mpk_plan_prepare first");
+        if ((st = spmv_slices(plan, nrhs, &sl))) return st;
+        if ((st = launch_powers(plan, sl, x, p, nrhs, alpha, beta, gamma, Y, poly, stream_v)))
+            return st;
     }
-    *out = it->second.get();
+    if (!capturing && !na && (st = note_stream(plan, stream))) return st;
     return MPK_OK;
 }
 
@@ -771,33 +993,7 @@ mpk_status_t run_baseline(mpk_plan_t plan, const double *x, int p, int nrhs, con
             return fail(MPK_EINVAL, "no slice table for this RHS count: call mpk_plan_prepare or run once outside capture first");
         if ((st = spmv_slices(plan, nrhs, &sl))) return st;
     }
-    const size_t stride = (size_t)plan->n * nrhs;
-    const DevMatrix m = plan->matrix();
-    for (int k = 1; k <= p; ++k) {
-        // with poly, Y is a ring of two: power k in slot (k-1) mod 2
-        const size_t o_in = poly ? (size_t)((k - 2) & 1) : (size_t)(k - 2);
-        const size_t o_prev = poly ? (size_t)((k - 3) & 1) : (size_t)(k - 3);
-        const size_t o_out = poly ? (size_t)((k - 1) & 1) : (size_t)(k - 1);
-        const double *in = k == 1 ? x : Y + o_in * stride;
-        const double *prev = k == 1 ? nullptr : (k == 2 ? x : Y + o_prev * stride);
-        double *out = Y + o_out * stride;
-        AccStep as{};
-        if (poly) {
-            as.acc_a = poly->acc_a;
-            as.acc_b = poly->acc_b;
-            for (int i = 0; i < 3; ++i) {  // powers k-2, k-1, k
-                as.wa[i] = poly->w(poly->wa, k - 2 + i);
-                as.wb[i] = poly->w(poly->wb, k - 2 + i);
-            }
-            as.fa = poly->fa[(size_t)k];
-            as.fb = poly->fb[(size_t)k];
-        }
-        int rc = launch_spmv_power(m, sl->view(), sl->n_slices, kSpmvSlicesPerWG, in, prev, out,
-                                   nrhs, recur ? 1 : 0, recur ? alpha[k - 1] : 1.0,
-                                   recur ? beta[k - 1] : 0.0, recur ? gamma[k - 1] : 0.0,
-                                   poly ? &as : nullptr, stream_v);
-        if (rc) return hip_fail((hipError_t)rc, "spmv kernel launch");
-    }
+    if ((st = launch_powers(plan, sl, x, p, nrhs, alpha, beta, gamma, Y, poly, stream_v))) return st;
     if (cap != hipStreamCaptureStatusActive) {
         std::lock_guard<std::mutex> g(plan->mu);
         if ((st = note_stream(plan, stream))) return st;
@@ -1119,6 +1315,7 @@ mpk_status_t mpk_plan(const mpk_csr_t *A, const mpk_plan_opts_t *opts, mpk_plan_
         plan->fingerprint = fingerprint(A->n, A->nnz, o, A->rowptr, sample);
     }
     if (!host_only && (st = build_sell(plan.get()))) return st;
+    if (!host_only && (st = build_dia(plan.get()))) return st;
     plan->plan_ms = now_ms() - t0;
     *out = plan.release();
     return MPK_OK;
@@ -1254,6 +1451,7 @@ mpk_status_t mpk_plan_device(const mpk_csr_t *A, const mpk_plan_opts_t *opts, mp
         }
         plan->fingerprint = fingerprint(n, nnz, o, rph, sample);
         mpk_status_t st2 = build_sell(plan.get());
+        if (!st2) st2 = build_dia(plan.get());
         if (st2) return st2;
     } catch (const std::bad_alloc &) {
         return fail(MPK_ENOMEM, "host allocation failed");
@@ -1290,6 +1488,7 @@ mpk_status_t mpk_plan_tune(mpk_plan_t plan, const mpk_tune_t *tune) {
     // schedules may still be read by queued kernels: keep them until destroy
     for (auto &kv : plan->scheds) plan->retired.push_back(std::move(kv.second));
     plan->scheds.clear();
+    plan->shapes.clear();
     return MPK_OK;
 }
 
@@ -1448,14 +1647,8 @@ mpk_status_t mpk_plan_prepare(mpk_plan_t plan, int p, int nrhs) {
     const int wg_default = default_workgroups(plan, nrhs);
     const int seg = plan->tune.seg_powers > 0 ? plan->tune.seg_powers : kMaxSegPowers;
     for (int base = 0; base < p; base += seg) {
-        SchedEntry *se = nullptr;
-        if ((st = get_schedule(plan, std::min(seg, p - base), &se, wg_default))) return st;
-        SliceSet *ss = nullptr;
-        if ((st = task_slices(plan, se, nrhs, &ss))) return st;
-        if (se->host.step_ptr.empty()) {
-            Workspace *ws = nullptr;
-            if ((st = get_workspace(plan, se->host.n_chunks(), nullptr, false, &ws))) return st;
-        }
+        if ((st = prepare_segment(plan, std::min(seg, p - base), nrhs, wg_default, nullptr, false)))
+            return st;
     }
     SliceSet *sl = nullptr;
     return spmv_slices(plan, nrhs, &sl);
@@ -1620,7 +1813,7 @@ mpk_status_t mpk_plan_autotune(mpk_plan_t plan, const double *x, int p, int nrhs
     // (chunks are capped so that each running workgroup gets two per power:
     // 65536 means "as large as that allows", e.g. ~54K nonzeros for 2^21 rows
     // of a 27-point stencil)
-    for (int chunk : {8192, 16384, 32768, 65536}) add(MPK_SCHED_WAVE, 64, chunk, 0);
+    add(MPK_SCHED_WAVE, 64, 32768, 0);   // one launch per power
     add(MPK_SCHED_XCD, 64, 16384, 0);
     add(MPK_SCHED_POWERS, 64, 8192, 0);
     int cus = 0;
@@ -1655,7 +1848,10 @@ mpk_status_t mpk_plan_autotune(mpk_plan_t plan, const double *x, int p, int nrhs
         }
         add(MPK_SCHED_POWERS, 64, 4096, 0, 8 * cus, 0, 0, 1);
     }
-    if (p >= 4) add(MPK_SCHED_WAVE, 64, 32768, 0, 0, (p + 1) / 2);  // two segments
+    const int wg0 = default_workgroups_locked(plan, nrhs);
+    const int slack0 = std::max(1, (8 * wg0 + p - 1) / p);   // no waits, a wide window
+    for (int chunk : {16384, 65536}) add(MPK_SCHED_WAVE, 64, chunk, slack0, wg0);
+    if (p >= 4) add(MPK_SCHED_WAVE, 64, 32768, slack0, wg0, (p + 1) / 2);  // two segments
     add(MPK_SCHED_WAVE, 64, 16384, 0, 0, 0, 2);                     // park up to two tasks
     // Chebyshev coefficients for timing the recurrence (values do not change the time)
     std::vector<double> al(p), be(p, 0.0), ga(p, -1.0);
@@ -1787,18 +1983,12 @@ mpk_status_t mpk_graph_capture(mpk_plan_t plan, const double *x, int p, int nrhs
         const int wg_default = default_workgroups(plan, nrhs);
         const int seg = plan->tune.seg_powers > 0 ? plan->tune.seg_powers : kMaxSegPowers;
         for (int base = 0; base < p; base += seg) {
-            const int ps = std::min(seg, p - base);
-            SchedEntry *se = nullptr;
-            if ((st = get_schedule(plan, ps, &se, wg_default))) return st;
-            SliceSet *ss = nullptr;
-            if ((st = task_slices(plan, se, nrhs, &ss))) return st;
-            if (se->host.step_ptr.empty()) {
-                Workspace *ws = nullptr;
-                // a never-used workspace: the capture below can take it without an event query
-                if ((st = get_workspace(plan, se->host.n_chunks(), g->stream, false, &ws, true)))
-                    return st;
-            }
+            if ((st = prepare_segment(plan, std::min(seg, p - base), nrhs, wg_default, g->stream,
+                                      true)))
+                return st;
         }
+        SliceSet *sl = nullptr;
+        if ((st = spmv_slices(plan, nrhs, &sl))) return st;
     }
     g->device = plan->device;
     e = hipStreamBeginCapture(g->stream, hipStreamCaptureModeThreadLocal);
@@ -1850,10 +2040,9 @@ mpk_status_t mpk_graph_capture_time_step(mpk_plan_t plan, const double *psi, int
     if (plan->n > 0) {
         // everything a run allocates or uploads is prepared before the capture
         std::lock_guard<std::mutex> lk(plan->mu);
-        if (baseline) {
-            SliceSet *ss = nullptr;
-            if ((st = spmv_slices(plan, nrhs, &ss))) return st;
-        } else {
+        SliceSet *sl = nullptr;
+        if ((st = spmv_slices(plan, nrhs, &sl))) return st;
+        if (!baseline) {
             const int sym = pattern_symmetric(plan);
             if (sym < 0) return MPK_EHIP;
             if (!sym)
@@ -1863,15 +2052,9 @@ mpk_status_t mpk_graph_capture_time_step(mpk_plan_t plan, const double *psi, int
             const int wg_default = default_workgroups(plan, nrhs);
             const int seg = plan->tune.seg_powers > 0 ? plan->tune.seg_powers : kMaxSegPowers;
             for (int base = 0; base < M; base += seg) {
-                SchedEntry *se = nullptr;
-                if ((st = get_schedule(plan, std::min(seg, M - base), &se, wg_default))) return st;
-                SliceSet *ss = nullptr;
-                if ((st = task_slices(plan, se, nrhs, &ss))) return st;
-                if (se->host.step_ptr.empty()) {
-                    Workspace *ws = nullptr;
-                    if ((st = get_workspace(plan, se->host.n_chunks(), g->stream, false, &ws, true)))
-                        return st;
-                }
+                if ((st = prepare_segment(plan, std::min(seg, M - base), nrhs, wg_default,
+                                          g->stream, true)))
+                    return st;
             }
         }
     }

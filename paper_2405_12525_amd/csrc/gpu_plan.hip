@@ -643,4 +643,286 @@ int gpu_sell_fill(int64_t n, const int32_t *rowptr, const int32_t *col, const vo
     return 0;
 }
 
+// ------------------------------------------------------------------ diagonal slices
+
+namespace {
+
+constexpr uint64_t kHashBasis = 1469598103934665603ull, kHashPrime = 1099511628211ull;
+
+// Smallest value over the wave's 64 lanes.
+__device__ __forceinline__ int32_t wave_min(int32_t v) {
+    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
+    return v;
+}
+
+template <typename V>
+__device__ __forceinline__ uint64_t value_bits_of(V v) {
+    if constexpr (sizeof(V) == 8)
+        return (uint64_t)__double_as_longlong(v);
+    else
+        return (uint64_t)__float_as_uint(v);
+}
+
+// Bit i of v to bit 2i.
+__device__ __forceinline__ uint64_t spread_bits(uint32_t v) {
+    uint64_t x = v;
+    x = (x | x << 16) & 0x0000ffff0000ffffull;
+    x = (x | x << 8) & 0x00ff00ff00ff00ffull;
+    x = (x | x << 4) & 0x0f0f0f0f0f0f0f0full;
+    x = (x | x << 2) & 0x3333333333333333ull;
+    x = (x | x << 1) & 0x5555555555555555ull;
+    return x;
+}
+
+// One step of a slice's walk.
+template <typename V>
+struct DiaStep {
+    int32_t step, off;
+    uint64_t even, odd;    // its rows
+    bool same;             // they store one value
+    uint64_t lead_bits;    // that value
+    V v[2];                // this lane's values (0 where the row lacks it)
+};
+
+// Walks slice s (one wave, lane l = rows 2l and 2l + 1 of it): the rows'
+// entries are merged by ascending column offset, one diagonal per step, and
+// fn is called for each.  Returns the number of diagonals, or -1 where a row's
+// columns do not ascend strictly or there are more than max_slots.
+template <typename V, typename F>
+__device__ int32_t walk_slice(int64_t n, const int32_t *drow, const int64_t *soff,
+                              const int32_t *rlen, const int32_t *scol, const V *sval, int64_t s,
+                              int32_t max_slots, F &&fn) {
+    const int lane = (int)(threadIdx.x & 63);
+    const int64_t r0 = s * kDiaRows + 2 * lane;
+    int32_t L[2], e[2] = {0, 0}, d[2];   // length, cursor, offset of the next entry
+    int64_t q[2];
+    for (int i = 0; i < 2; ++i) {
+        L[i] = 0;
+        q[i] = 0;
+        if (r0 + i < n) {
+            const int64_t pr = drow ? drow[r0 + i] : r0 + i;
+            L[i] = rlen[pr];
+            q[i] = soff[pr / kSellRows] + pr % kSellRows;
+        }
+        d[i] = L[i] > 0 ? scol[q[i]] - (int32_t)(r0 + i) : INT32_MAX;   // |offset| < INT32_MAX
+    }
+    bool ok = true;
+    int32_t step = 0;
+    for (;;) {
+        DiaStep<V> t;
+        t.off = wave_min(min(d[0], d[1]));
+        if (t.off == INT32_MAX) break;
+        if (__ballot(!ok) || step >= max_slots) return -1;
+        t.step = step;
+        t.even = __ballot(d[0] == t.off);
+        t.odd = __ballot(d[1] == t.off);
+        for (int i = 0; i < 2; ++i)
+            t.v[i] = d[i] == t.off ? sval[q[i] + (int64_t)e[i] * kSellRows] : V(0);
+        const int lead = __ffsll((long long)(t.even | t.odd)) - 1;
+        const uint64_t b0 = value_bits_of(t.v[0]), b1 = value_bits_of(t.v[1]);
+        t.lead_bits = (uint64_t)__shfl((long long)(d[0] == t.off ? b0 : b1), lead);
+        t.same = __ballot((d[0] == t.off && b0 != t.lead_bits) ||
+                          (d[1] == t.off && b1 != t.lead_bits)) == 0;
+        fn(t);
+        ++step;
+        for (int i = 0; i < 2; ++i)
+            if (d[i] == t.off) {
+                ++e[i];
+                d[i] = e[i] < L[i] ? scol[q[i] + (int64_t)e[i] * kSellRows] - (int32_t)(r0 + i)
+                                   : INT32_MAX;
+                if (d[i] <= t.off) ok = false;
+            }
+    }
+    return __ballot(!ok) ? -1 : step;
+}
+
+// One wave per slice.  A slice is taken where its list is at most twice as
+// long as its longest row and list and values take no more bytes than its
+// entries in the sliced layout (col_bits: the width of the columns there).
+template <typename V>
+__global__ void dia_count_kernel(int64_t n, const int32_t *drow, const int64_t *soff,
+                                 const int32_t *rlen, const int32_t *scol, const V *sval,
+                                 int col_bits, DiaCount *out) {
+    const int64_t n_sl = (n + kDiaRows - 1) / kDiaRows;
+    const int64_t s = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (s >= n_sl) return;
+    const int lane = (int)(threadIdx.x & 63);
+    int32_t width = 0;
+    int64_t entries = 0;
+    for (int i = 0; i < 2; ++i) {
+        const int64_t r = s * kDiaRows + 2 * lane + i;
+        if (r < n) {
+            const int32_t L = rlen[drow ? drow[r] : r];
+            width = max(width, L);
+            entries += L;
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        width = max(width, __shfl_xor(width, o));
+        entries += __shfl_xor((long long)entries, o);
+    }
+    DiaCount c{0, 0, INT32_MAX, -INT32_MAX, {0, 0}, kHashBasis};
+    uint64_t even = ~0ull, odd = ~0ull;
+    c.count = walk_slice<V>(n, drow, soff, rlen, scol, sval, s, 2 * width,
+                            [&](const DiaStep<V> &t) {
+                                uint64_t h = c.hash;
+                                h = (h ^ (uint32_t)t.off) * kHashPrime;
+                                for (uint64_t m : {t.even, t.odd}) {
+                                    h = (h ^ (m & 0xffffffffull)) * kHashPrime;
+                                    h = (h ^ (m >> 32)) * kHashPrime;
+                                }
+                                h = (h ^ (t.same ? t.lead_bits * 2 + 1 : 0)) * kHashPrime;
+                                c.hash = h ^ (h >> 29);
+                                if (!t.same) ++c.vblocks;
+                                c.lo = min(c.lo, t.off);
+                                c.hi = max(c.hi, t.off);
+                                even &= t.even;
+                                odd &= t.odd;
+                            });
+    if (c.count >= 0 && (int64_t)c.count * 56 + (int64_t)c.vblocks * kDiaRows * (int64_t)sizeof(V) >
+                            entries * ((int64_t)sizeof(V) + col_bits / 8) + 256)
+        c.count = -1;
+    c.whole[0] = spread_bits((uint32_t)even) | spread_bits((uint32_t)odd) << 1;
+    c.whole[1] = spread_bits((uint32_t)(even >> 32)) | spread_bits((uint32_t)(odd >> 32)) << 1;
+    if (lane == 0) out[s] = c;
+}
+
+template <typename V>
+__device__ __forceinline__ double value_of_bits(uint64_t bits) {
+    if constexpr (sizeof(V) == 8)
+        return __longlong_as_double((long long)bits);
+    else
+        return static_cast<double>(__uint_as_float((uint32_t)bits));
+}
+
+template <typename V>
+__global__ void dia_fill_kernel(int64_t n, const int32_t *drow, const int64_t *soff,
+                                const int32_t *rlen, const int32_t *scol, const V *sval,
+                                const DiaSlice *slices, const uint8_t *emit, DiaGroup *groups,
+                                DiaRowMask *mask, V *vals) {
+    const int64_t n_sl = (n + kDiaRows - 1) / kDiaRows;
+    const int64_t s = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (s >= n_sl) return;
+    const DiaSlice ds = slices[s];
+    if (ds.count < 0) return;
+    const int lane = (int)(threadIdx.x & 63);
+    const bool list = emit[s] != 0;
+    int32_t vb = 0;
+    walk_slice<V>(n, drow, soff, rlen, scol, sval, s, ds.count, [&](const DiaStep<V> &t) {
+        if (list && lane == 0) {
+            DiaGroup &g = groups[(int64_t)ds.first + t.step / 4];
+            DiaRowMask &k = mask[(int64_t)ds.first + t.step / 4];
+            const int u = t.step & 3;
+            g.off[u] = t.off;
+            if (u == 0) g.vblock = vb;
+            if (!t.same) g.vary |= 1 << u;
+            if ((t.even & t.odd) != ~0ull) g.partial |= 1 << u;
+            g.n = u + 1;
+            g.uval[u] = t.same ? value_of_bits<V>(t.lead_bits) : 0.0;
+            g.even[u] = t.even;
+            g.odd[u] = t.odd;
+            k.lo[u] = spread_bits((uint32_t)t.even) | spread_bits((uint32_t)t.odd) << 1;
+            k.hi[u] = spread_bits((uint32_t)(t.even >> 32)) |
+                      spread_bits((uint32_t)(t.odd >> 32)) << 1;
+        }
+        if (!t.same) {
+            V *v = vals + ((int64_t)ds.vfirst + vb) * kDiaRows + 2 * lane;
+            v[0] = t.v[0];
+            v[1] = t.v[1];
+            ++vb;
+        }
+    });
+}
+
+// Every slice's own list against the pattern it was given.
+template <typename V>
+__global__ void dia_verify_kernel(int64_t n, const int32_t *drow, const int64_t *soff,
+                                  const int32_t *rlen, const int32_t *scol, const V *sval,
+                                  const DiaSlice *slices, const DiaGroup *groups, int32_t *bad) {
+    const int64_t n_sl = (n + kDiaRows - 1) / kDiaRows;
+    const int64_t s = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (s >= n_sl) return;
+    const DiaSlice ds = slices[s];
+    if (ds.count < 0) return;
+    bool differs = false;
+    int32_t vb = 0;
+    const int32_t cnt = walk_slice<V>(
+        n, drow, soff, rlen, scol, sval, s, ds.count, [&](const DiaStep<V> &t) {
+            const DiaGroup &g = groups[(int64_t)ds.first + t.step / 4];
+            const int u = t.step & 3;
+            differs |= g.off[u] != t.off || (g.vary >> u & 1) != (t.same ? 0 : 1) ||
+                       (u == 0 && g.vblock != vb) || g.even[u] != t.even || g.odd[u] != t.odd;
+            if (t.same)
+                differs |= __double_as_longlong(value_of_bits<V>(t.lead_bits)) !=
+                           __double_as_longlong(g.uval[u]);
+            else
+                ++vb;
+        });
+    if ((differs || cnt != ds.count) && (threadIdx.x & 63) == 0) atomicOr(bad, 1);
+}
+
+inline dim3 wave_grid(int64_t n_sl) { return dim3((unsigned)((n_sl * 64 + kThreads - 1) / kThreads)); }
+
+template <typename V>
+int dia_fill(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t *rlen,
+             const int32_t *scol, const V *sval, const std::vector<DiaSlice> &slices,
+             const std::vector<uint8_t> &emit, int64_t n_groups, DiaSlice *d_slices,
+             uint8_t *d_emit, DiaGroup *groups, DiaRowMask *mask, V *vals, int *mismatch) {
+    const int64_t n_sl = (n + kDiaRows - 1) / kDiaRows;
+    int32_t *bad = reinterpret_cast<int32_t *>(d_emit + (n_sl + 3) / 4 * 4);
+    MPK_TRY(hipMemcpy(d_slices, slices.data(), (size_t)n_sl * sizeof(DiaSlice), hipMemcpyHostToDevice));
+    MPK_TRY(hipMemcpy(d_emit, emit.data(), (size_t)n_sl, hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(kThreads), 0, 0, bad, (int64_t)1, 0);
+    const int64_t words = n_groups * (int64_t)(sizeof(DiaGroup) / 4);
+    hipLaunchKernelGGL(fill_kernel, dim3(grid_for(words)), dim3(kThreads), 0, 0,
+                       reinterpret_cast<int32_t *>(groups), words, 0);
+    hipLaunchKernelGGL(fill_kernel, dim3(grid_for(words / 2)), dim3(kThreads), 0, 0,
+                       reinterpret_cast<int32_t *>(mask), words / 2, 0);
+    hipLaunchKernelGGL(dia_fill_kernel<V>, wave_grid(n_sl), dim3(kThreads), 0, 0, n, drow, soff,
+                       rlen, scol, sval, d_slices, d_emit, groups, mask, vals);
+    hipLaunchKernelGGL(dia_verify_kernel<V>, wave_grid(n_sl), dim3(kThreads), 0, 0, n, drow, soff,
+                       rlen, scol, sval, d_slices, groups, bad);
+    MPK_TRY(hipGetLastError());
+    int32_t b = 0;
+    MPK_TRY(hipMemcpy(&b, bad, 4, hipMemcpyDeviceToHost));
+    *mismatch = b;
+    return 0;
+}
+
+}  // namespace
+
+int gpu_dia_count(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t *rlen,
+                  const int32_t *scol, const void *sval, int value_bits, int col_bits,
+                  DiaCount *scratch, std::vector<DiaCount> &out) {
+    const int64_t n_sl = (n + kDiaRows - 1) / kDiaRows;
+    out.resize((size_t)n_sl);
+    if (n_sl == 0) return 0;
+    if (value_bits == 32)
+        hipLaunchKernelGGL(dia_count_kernel<float>, wave_grid(n_sl), dim3(kThreads), 0, 0, n, drow,
+                           soff, rlen, scol, static_cast<const float *>(sval), col_bits, scratch);
+    else
+        hipLaunchKernelGGL(dia_count_kernel<double>, wave_grid(n_sl), dim3(kThreads), 0, 0, n,
+                           drow, soff, rlen, scol, static_cast<const double *>(sval), col_bits,
+                           scratch);
+    MPK_TRY(hipGetLastError());
+    MPK_TRY(hipMemcpy(out.data(), scratch, (size_t)n_sl * sizeof(DiaCount), hipMemcpyDeviceToHost));
+    return 0;
+}
+
+int gpu_dia_fill(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t *rlen,
+                 const int32_t *scol, const void *sval, int value_bits,
+                 const std::vector<DiaSlice> &slices, const std::vector<uint8_t> &emit,
+                 int64_t n_groups, DiaSlice *d_slices, uint8_t *d_emit, DiaGroup *groups,
+                 DiaRowMask *mask, void *vals, int *mismatch) {
+    *mismatch = 0;
+    if (n == 0) return 0;
+    if (value_bits == 32)
+        return dia_fill<float>(n, drow, soff, rlen, scol, static_cast<const float *>(sval), slices,
+                               emit, n_groups, d_slices, d_emit, groups, mask,
+                               static_cast<float *>(vals), mismatch);
+    return dia_fill<double>(n, drow, soff, rlen, scol, static_cast<const double *>(sval), slices,
+                            emit, n_groups, d_slices, d_emit, groups, mask,
+                            static_cast<double *>(vals), mismatch);
+}
+
 }  // namespace mpk

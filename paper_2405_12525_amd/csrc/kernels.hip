@@ -384,6 +384,291 @@ __device__ __forceinline__ void run_sell(const DevMatrix &m, const PowerIO &io, 
         run_sell_cols<V, RC, WT, ACC, U, false, NT>(m, io, R_rt, r0, r1);
 }
 
+// ------------------------------------------------------------------ diagonal slices
+
+// Data written before the launch, read through the scalar cache where the
+// address is the same for the whole wave.
+template <typename T>
+__device__ __forceinline__ T ld_const(const T *p) {
+    return *(const __attribute__((address_space(4))) T *)(uintptr_t)p;
+}
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef double v2d __attribute__((ext_vector_type(2)));
+
+// Two consecutive doubles (8-byte aligned).
+typedef double v2d __attribute__((ext_vector_type(2), aligned(8)));
+typedef float v2f __attribute__((ext_vector_type(2), aligned(4)));
+__device__ __forceinline__ void load_2(double (&v)[2], const double *p) {
+    const v2d t = *reinterpret_cast<const v2d *>(p);
+    v[0] = t.x;
+    v[1] = t.y;
+}
+__device__ __forceinline__ void load_2(double (&v)[2], const float *p) {
+    const v2f t = *reinterpret_cast<const v2f *>(p);
+    v[0] = static_cast<double>(t.x);
+    v[1] = static_cast<double>(t.y);
+}
+template <bool WT>
+__device__ __forceinline__ void store_2(double *p, const double (&v)[2]) {
+    if constexpr (WT) {
+        store_out<true>(p, v[0]);
+        store_out<true>(p + 1, v[1]);
+    } else
+        *reinterpret_cast<v2d *>(p) = v2d{v[0], v[1]};
+}
+
+// accumulate and finish for two consecutive elements.
+template <bool WT>
+__device__ __forceinline__ void accumulate_2(double *acc, int f, double w2, double w1, double w0,
+                                             const double (&y2)[2], const double (&y1)[2],
+                                             const double (&v)[2], size_t idx) {
+    if (!f) return;
+    double r[2] = {0.0, 0.0};
+    if (!(f & kAccZero)) {
+        const bool start = f & kAccStart;
+        if (!start) load_2(r, acc + idx);
+        for (int i = 0; i < 2; ++i) {
+            bool have = !start;
+            if (f & kAccT2) {
+                const double t = w2 * y2[i];
+                r[i] = have ? r[i] + t : t;
+                have = true;
+            }
+            if (f & kAccT1) {
+                const double t = w1 * y1[i];
+                r[i] = have ? r[i] + t : t;
+                have = true;
+            }
+            if (f & kAccT0) {
+                const double t = w0 * v[i];
+                r[i] = have ? r[i] + t : t;
+            }
+        }
+    }
+    store_2<WT>(acc + idx, r);
+}
+template <bool WT, bool ACC>
+__device__ __forceinline__ void finish_2(const PowerIO &io, const double (&s)[2], size_t idx) {
+    const bool b = io.recur && io.beta != 0.0;
+    const bool g = io.recur && io.prev && io.gamma != 0.0;
+    const bool need1 = b || (ACC && ((io.fa | io.fb) & kAccT1));
+    const bool need2 = g || (ACC && ((io.fa | io.fb) & kAccT2));
+    double y1[2] = {0.0, 0.0}, y2[2] = {0.0, 0.0}, v[2];
+    if (need1) load_2(y1, io.in + idx);
+    if (need2) load_2(y2, io.prev + idx);
+    for (int i = 0; i < 2; ++i) {
+        v[i] = s[i];
+        if (io.recur) {
+            v[i] = io.alpha * s[i];
+            if (b) {
+                const double t = io.beta * y1[i];
+                v[i] = v[i] + t;
+            }
+            if (g) {
+                const double t = io.gamma * y2[i];
+                v[i] = v[i] + t;
+            }
+        }
+    }
+    store_2<WT>(io.out + idx, v);
+    if constexpr (ACC) {
+        accumulate_2<WT>(io.acc_a, io.fa, io.wa2, io.wa1, io.wa0, y2, y1, v, idx);
+        accumulate_2<WT>(io.acc_b, io.fb, io.wb2, io.wb1, io.wb0, y2, y1, v, idx);
+    }
+}
+
+// How the lanes of a pass share a slice.  The kDiaRows * R elements of a
+// vector's slice are consecutive; pass q of R takes 128 of them and a lane two
+// neighbours (one 16-byte load per diagonal: the vector cache moves 64
+// bytes a clock that way and 32 with 8-byte loads): two rows (kOneRhs), two
+// right-hand sides of a row (kEven) or either (kOdd).
+enum DiaMode { kOneRhs, kEven, kOdd };
+struct DiaLane {
+    int32_t row[2];   // of the slice
+    int32_t sub0;     // first row of the pass (uniform)
+    uint32_t at;      // byte offset of the first element in a vector
+};
+// Rows sub0 .. sub0 + 63 of a mask (uniform).
+__device__ __forceinline__ uint64_t mask_from(uint64_t lo, uint64_t hi, int32_t sub0) {
+    if (sub0 >= 64) return hi >> (sub0 - 64);
+    return sub0 ? lo >> sub0 | hi << (64 - sub0) : lo;
+}
+
+// The first U diagonals of group g, added to the two sums of this lane.  All
+// loads go out before the products; a row without a diagonal keeps its sum.
+// vals: the group's first block of per-row values.  WHOLE: every row of the
+// pass has every diagonal.  EDGE: every load address is a row's own or one of
+// its columns; else any row plus any of the slice's offsets is inside the
+// vector.  live (EDGE): the lane's rows exist.
+template <typename V, int U, int MODE, int KIND, bool WHOLE, bool EDGE>
+__device__ __forceinline__ void dia_group(const DevMatrix &m, const double *in, int32_t g,
+                                          const V *vals, const DiaLane &l, int32_t rbytes,
+                                          const bool (&live)[2], double (&s)[2]) {
+    typedef int v16i __attribute__((ext_vector_type(16), aligned(64)));
+    typedef uint64_t v8u __attribute__((ext_vector_type(8), aligned(64)));
+    const v16i h = ld_const(reinterpret_cast<const v16i *>(m.dgroup + g));
+    v8u mk = {};
+    if constexpr (MODE == kOneRhs)
+        mk = ld_const(reinterpret_cast<const v8u *>(m.dgroup + g) + 1);
+    else if constexpr (!WHOLE)
+        mk = ld_const(reinterpret_cast<const v8u *>(m.dmask + g));
+    double a[U][2], x[U][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t ub = (uint64_t)(uint32_t)h[8 + 2 * u] | (uint64_t)(uint32_t)h[9 + 2 * u] << 32;
+        a[u][0] = a[u][1] = __longlong_as_double((long long)ub);
+        if (KIND == kDiaPerRow || (KIND == kDiaMixed && (h[5] >> u & 1))) {   // uniform
+            if constexpr (MODE == kOneRhs) {
+                load_2(a[u], vals + (uint32_t)l.row[0]);
+            } else {
+                a[u][0] = a[u][1] = static_cast<double>(vals[(uint32_t)l.row[0]]);
+                if (MODE == kOdd) a[u][1] = static_cast<double>(vals[(uint32_t)l.row[1]]);
+            }
+            vals += kDiaRows;
+        }
+    }
+    const char *p = reinterpret_cast<const char *>(in);
+    if constexpr (!EDGE) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            load_2(x[u], reinterpret_cast<const double *>(
+                             p + (uint32_t)(l.at + (uint32_t)(h[u] * rbytes))));
+        if (WHOLE || h[6] == 0) {   // uniform
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) s[i] = s[i] + a[u][i] * x[u][i];
+            return;
+        }
+    }
+    bool bit[U][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if constexpr (MODE == kOneRhs) {
+            bit[u][0] = __builtin_amdgcn_inverse_ballot_w64(mk[u]);
+            bit[u][1] = __builtin_amdgcn_inverse_ballot_w64(mk[4 + u]);
+        } else {
+            const uint64_t w = mask_from(mk[u], mk[4 + u], l.sub0);
+            bit[u][0] = w >> (l.row[0] - l.sub0) & 1;
+            bit[u][1] = MODE == kEven ? bit[u][0] : w >> (l.row[1] - l.sub0) & 1;
+        }
+        if constexpr (EDGE) {
+            const uint32_t d = (uint32_t)(h[u] * rbytes);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                bit[u][i] = bit[u][i] && live[i];
+                const uint32_t q = (live[i] ? l.at + 8u * i : 0u) + (bit[u][i] ? d : 0u);
+                x[u][i] = *reinterpret_cast<const double *>(p + q);
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const double t = s[i] + a[u][i] * x[u][i];
+            s[i] = bit[u][i] ? t : s[i];
+        }
+}
+// All `count` diagonals from group g on.
+template <typename V, int MODE, int KIND, bool WHOLE, bool EDGE>
+__device__ __forceinline__ void dia_sum(const DevMatrix &m, const double *in, int32_t g,
+                                        int32_t count, const V *vals, const DiaLane &l,
+                                        int32_t rbytes, const bool (&live)[2], double (&s)[2]) {
+    for (; count >= 4; count -= 4, ++g) {
+        dia_group<V, 4, MODE, KIND, WHOLE, EDGE>(m, in, g, vals, l, rbytes, live, s);
+        if (KIND == kDiaPerRow) vals += 4 * kDiaRows;
+        if (KIND == kDiaMixed)
+            vals += (size_t)__popc((unsigned)ld_const(&m.dgroup[g].vary)) * kDiaRows;
+    }
+    switch (count) {   // uniform
+    case 3: dia_group<V, 3, MODE, KIND, WHOLE, EDGE>(m, in, g, vals, l, rbytes, live, s); break;
+    case 2: dia_group<V, 2, MODE, KIND, WHOLE, EDGE>(m, in, g, vals, l, rbytes, live, s); break;
+    case 1: dia_group<V, 1, MODE, KIND, WHOLE, EDGE>(m, in, g, vals, l, rbytes, live, s); break;
+    }
+}
+template <typename V, int MODE, int KIND>
+__device__ __forceinline__ void dia_sum(const DevMatrix &m, const double *in, int32_t g,
+                                        int32_t count, const V *vals, const DiaLane &l,
+                                        int32_t rbytes, bool whole, double (&s)[2]) {
+    const bool live[2] = {true, true};
+    if (MODE != kOneRhs && whole)   // uniform
+        dia_sum<V, MODE, KIND, true, false>(m, in, g, count, vals, l, rbytes, live, s);
+    else
+        dia_sum<V, MODE, KIND, false, false>(m, in, g, count, vals, l, rbytes, live, s);
+}
+
+// Pass q of slice s (both uniform) by one wave.
+template <typename V, int MODE, bool WT, bool ACC>
+__device__ __forceinline__ void dia_pass(const DevMatrix &m, const PowerIO &io, int32_t R,
+                                         int32_t s, int32_t q) {
+    typedef int v8i __attribute__((ext_vector_type(8), aligned(16)));
+    const v8i ds = ld_const(reinterpret_cast<const v8i *>(m.dsl + s));
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const int32_t f = q * 128 + 2 * lane;   // element of the slice
+    const size_t idx = (size_t)s * kDiaRows * R + f;
+    DiaLane l;
+    bool whole = false;
+    if constexpr (MODE == kOneRhs) {
+        l.row[0] = f;
+        l.row[1] = f + 1;
+        l.sub0 = 0;
+    } else {
+        // f / R for f < 128 * 16: by a rounded-up reciprocal, exact there
+        const int32_t inv = (65536 + R - 1) / R;
+        l.row[0] = f * inv >> 16;
+        l.row[1] = MODE == kEven ? l.row[0] : (f + 1) * inv >> 16;
+        l.sub0 = q * 128 * inv >> 16;
+        const int32_t k = ((q * 128 + 127) * inv >> 16) + 1 - l.sub0;   // 8 .. 64 rows
+        const uint64_t sub = ~0ull >> (64 - k);
+        const uint64_t lo = (uint64_t)(uint32_t)ds[4] | (uint64_t)(uint32_t)ds[5] << 32;
+        const uint64_t hi = (uint64_t)(uint32_t)ds[6] | (uint64_t)(uint32_t)ds[7] << 32;
+        whole = (mask_from(lo, hi, l.sub0) & sub) == sub;
+    }
+    l.at = (uint32_t)idx * (uint32_t)sizeof(double);
+    const int32_t rbytes = R * (int32_t)sizeof(double);
+    const V *vals = static_cast<const V *>(m.dvals) + (size_t)ds.z * kDiaRows;
+    double sum[2] = {0.0, 0.0};
+    if (ds.y >= 0 && ds.w < kDiaEdge) {
+        if (ds.w == kDiaShared)
+            dia_sum<V, MODE, kDiaShared>(m, io.in, ds.x, ds.y, vals, l, rbytes, whole, sum);
+        else if (ds.w == kDiaPerRow)
+            dia_sum<V, MODE, kDiaPerRow>(m, io.in, ds.x, ds.y, vals, l, rbytes, whole, sum);
+        else
+            dia_sum<V, MODE, kDiaMixed>(m, io.in, ds.x, ds.y, vals, l, rbytes, whole, sum);
+        finish_2<WT, ACC>(io, sum, idx);
+        return;
+    }
+    const bool live[2] = {s * kDiaRows + l.row[0] < m.n, s * kDiaRows + l.row[1] < m.n};
+    if (ds.y >= 0) {
+        dia_sum<V, MODE, kDiaMixed, false, true>(m, io.in, ds.x, ds.y, vals, l, rbytes, live, sum);
+    } else {   // rows as the sliced layout holds them
+        const V *sval = static_cast<const V *>(m.sval);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (!live[i]) continue;
+            const int32_t row = s * kDiaRows + l.row[i], pr = m.drow ? m.drow[row] : row;
+            const int32_t rr = (f + i) - l.row[i] * R, L = m.rlen[pr];
+            const int64_t base = m.soff[pr / kSellRows] + pr % kSellRows;
+            for (int32_t j = 0; j < L; j += 4) {
+                double a[4], x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int64_t e = base + (int64_t)min(j + u, L - 1) * kSellRows;
+                    a[u] = static_cast<double>(sval[e]);
+                    x[u] = io.in[(size_t)m.scol[e] * R + rr];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (j + u < L) sum[i] = sum[i] + a[u] * x[u];
+            }
+        }
+    }
+    if (live[0]) finish<WT, ACC>(io, sum[0], idx);
+    if (live[1]) finish<WT, ACC>(io, sum[1], idx + 1);
+}
+
 // Products staged per thread and buffer: the slice path for R < 4 (R = 0 is
 // the generic instantiation, which takes either path at run time).
 template <int RC, int KP>
@@ -537,6 +822,21 @@ __global__ __launch_bounds__(kBlock) void spmv_sell_kernel(DevMatrix m, PowerIO 
     for (int32_t r0 = blockIdx.x * step; r0 < m.n; r0 += gridDim.x * step)
         run_sell<V, RC, false, ACC, SpmvSellU<RC>::value, RC == 1>(m, io, R, r0,
                                                                    min(m.n, r0 + step));
+}
+
+// One power from the diagonal slices.  A wave takes one pass of one slice,
+// blocks dealt so that every XCD sweeps a contiguous eighth of the slices
+// (workgroup b runs on XCD b mod 8): a row's neighbours then mostly lie in the
+// same XCD's L2.
+template <typename V, int MODE, bool ACC>
+__global__ __launch_bounds__(kBlock) void spmv_dia_kernel(DevMatrix m, PowerIO io, int32_t R,
+                                                          int32_t units, int32_t per_xcd) {
+    const int32_t b = (int32_t)(blockIdx.x & 7) * per_xcd + (int32_t)(blockIdx.x >> 3);
+    const int32_t u = b * (kBlock / kWave) +
+                      __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x / kWave));
+    if (u >= units) return;
+    const int32_t s = MODE == kOneRhs ? u : u / R;
+    dia_pass<V, MODE, false, ACC>(m, io, R, s, u - s * R);
 }
 
 // ------------------------------------------------------------------ level-blocked
@@ -1094,6 +1394,7 @@ __global__ __launch_bounds__(kBlock) void load_probe_local_kernel(const double2 
 
 using SpmvFn = void (*)(DevMatrix, PowerIO, int32_t, DevSlices, int32_t, int32_t);
 using SpmvSellFn = void (*)(DevMatrix, PowerIO, int32_t);
+using SpmvDiaFn = void (*)(DevMatrix, PowerIO, int32_t, int32_t, int32_t);
 using LbFn = void (*)(LBParams, Coefs);
 using LbAccFn = void (*)(LBParams, Coefs, AccCoefs);
 using StepFn = void (*)(DevMatrix, DevSlices, const int32_t *, const int32_t *, const int32_t *,
@@ -1176,6 +1477,15 @@ SpmvSellFn spmv_sell_fn(int value_bits, int R, bool acc) {
     if (value_bits == 32) return acc ? t32().spmv_sell_acc[i] : t32().spmv_sell[i];
     return acc ? t64().spmv_sell_acc[i] : t64().spmv_sell[i];
 }
+template <typename V>
+SpmvDiaFn spmv_dia_of(int R, bool acc) {
+    if (R == 1) return acc ? spmv_dia_kernel<V, kOneRhs, true> : spmv_dia_kernel<V, kOneRhs, false>;
+    if (R % 2 == 0) return acc ? spmv_dia_kernel<V, kEven, true> : spmv_dia_kernel<V, kEven, false>;
+    return acc ? spmv_dia_kernel<V, kOdd, true> : spmv_dia_kernel<V, kOdd, false>;
+}
+SpmvDiaFn spmv_dia_fn(int value_bits, int R, bool acc) {
+    return value_bits == 32 ? spmv_dia_of<float>(R, acc) : spmv_dia_of<double>(R, acc);
+}
 // skip: the skip-ahead kernel (LDS-staged rows); else sell picks the
 // sliced-layout kernel
 LbFn lb_fn(int value_bits, int R, bool skip, bool sell) {
@@ -1257,7 +1567,7 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
                       double alpha, double beta, double gamma, const AccStep *acc,
                       void *stream) {
     if (R < 1 || R > 16 || per < 1) return (int)hipErrorInvalidValue;
-    if (m.n == 0 || n_slices == 0) return 0;
+    if (m.n == 0) return 0;
     PowerIO io{in, inm1, out, alpha, beta, gamma, recur};
     io.acc_a = io.acc_b = nullptr;
     io.wa2 = io.wa1 = io.wa0 = io.wb2 = io.wb1 = io.wb0 = 0.0;
@@ -1274,6 +1584,14 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
         io.fa = acc->fa;
         io.fb = acc->fb;
     }
+    if (dia_fits(m, R)) {
+        const int32_t units = (m.n + kDiaRows - 1) / kDiaRows * R;   // passes of a wave
+        const int32_t blocks = (units + kBlock / kWave - 1) / (kBlock / kWave);
+        const int32_t per = (blocks + 7) / 8;
+        hipLaunchKernelGGL(spmv_dia_fn(m.value_bits, R, acc != nullptr), dim3((unsigned)per * 8),
+                           dim3(kBlock), 0, (hipStream_t)stream, m, io, R, units, per);
+        return (int)hipGetLastError();
+    }
     if (m.scol) {  // sliced layout: row blocks of 256 / R rows, grid-stride
         const int64_t nblk = ((int64_t)m.n + kBlock / R - 1) / (kBlock / R);
         const int64_t grid = std::min<int64_t>(nblk, kSpmvSellGrid);
@@ -1281,6 +1599,7 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
                            dim3(kBlock), 0, (hipStream_t)stream, m, io, R);
         return (int)hipGetLastError();
     }
+    if (n_slices == 0) return 0;
     const int32_t grid = (n_slices + per - 1) / per;
     hipLaunchKernelGGL(spmv_fn(m.value_bits, R, acc != nullptr), dim3((unsigned)grid), dim3(kBlock), 0,
                        (hipStream_t)stream, m, io, R, sl, n_slices, per);

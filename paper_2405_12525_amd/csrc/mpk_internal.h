@@ -104,6 +104,65 @@ int gpu_sell_widths(int64_t n, const int32_t *rowptr, std::vector<int32_t> &widt
 int gpu_sell_fill(int64_t n, const int32_t *rowptr, const int32_t *col, const void *val,
                   int value_bits, const int64_t *soff, int64_t entries, int32_t *rlen,
                   int32_t *scol, int16_t *sdel, void *sval, int32_t *max_offset);
+// Diagonal slices, a second layout in slices of kDiaRows consecutive rows in
+// the numbering of the vectors (the caller's, or the plan's with
+// MPK_ORDER_PLAN).  Where the rows of a slice store their entries in ascending
+// column order, the slice is a list of diagonals in that order.  A diagonal
+// holds the column offset its entries share (col = row + off), the rows that
+// have it (one bit each) and either the one value they all store or the place
+// of a value per row.  Entries then need no index of their own, and equal
+// values are stored once: a stencil's slice costs nothing per entry, one with
+// general coefficients its values only.  Sums still run over each row's
+// entries in stored order.  Slices with equal lists share one (a pattern).
+constexpr int kDiaRows = 128;
+struct alignas(16) DiaSlice {
+    int32_t first;    // first group of its pattern
+    int32_t count;    // diagonals; -1: the slice is read in the sliced layout
+    int32_t vfirst;   // its first block of kDiaRows per-row values
+    int32_t kind;     // DiaKind
+    uint64_t whole[2];  // rows 0..63 / 64..127 that have every diagonal
+};
+// Which diagonals store a value per row.  kDiaEdge: a row plus one of the
+// slice's offsets may fall outside the matrix, or the slice has rows past n.
+enum DiaKind { kDiaShared = 0, kDiaPerRow = 1, kDiaMixed = 2, kDiaEdge = 4 };
+// Four diagonals of a list (the last group of a list may hold fewer): a
+// group is two 64-byte scalar loads.
+struct alignas(64) DiaGroup {
+    int32_t off[4];      // column - row
+    int32_t vblock;      // block (from vfirst) of the group's first per-row values
+    int32_t vary;        // bit u: diagonal u stores a value per row, in the next block
+    int32_t partial;     // bit u: some row of the slice lacks diagonal u
+    int32_t n;           // diagonals
+    double uval[4];      // the one value of a diagonal that has one
+    uint64_t even[4];    // rows 2i that have the diagonal (bit i)
+    uint64_t odd[4];     // rows 2i + 1
+};
+struct alignas(64) DiaRowMask {
+    uint64_t lo[4], hi[4];   // the same as rows 0..63 / 64..127
+};
+// Counts of one slice: diagonals (-1: not representable, or not smaller than
+// the sliced layout), blocks of per-row values, the smallest and largest
+// offset, the rows that have every diagonal, and a hash of its list.
+struct DiaCount {
+    int32_t count, vblocks, lo, hi;
+    uint64_t whole[2];
+    uint64_t hash;
+};
+// gpu_dia_count: the counts of every slice (scratch: one DiaCount per slice
+// on the device).  gpu_dia_fill: slices and emit to the device (d_emit: 256
+// bytes longer), the values of every slice with count >= 0 into vals, the lists
+// of those with emit[s] != 0 into groups / mask, then *mismatch = 1 if any
+// slice's own list differs from the one slices[s].first names.  The matrix is
+// read from the sliced layout; drow[r] is row r's place there (null: r).
+// hipError_t results.
+int gpu_dia_count(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t *rlen,
+                  const int32_t *scol, const void *sval, int value_bits, int col_bits,
+                  DiaCount *scratch, std::vector<DiaCount> &out);
+int gpu_dia_fill(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t *rlen,
+                 const int32_t *scol, const void *sval, int value_bits,
+                 const std::vector<DiaSlice> &slices, const std::vector<uint8_t> &emit,
+                 int64_t n_groups, DiaSlice *d_slices, uint8_t *d_emit, DiaGroup *groups,
+                 DiaRowMask *mask, void *vals, int *mismatch);
 // Levels from far[] (order_levels' rule): level 0 = row 0, level j+1 ends
 // just past the farthest neighbour of level j.
 Levels levels_from_far(int64_t n, const std::vector<int32_t> &far);
@@ -173,7 +232,27 @@ struct DevMatrix {
                               // [-n/2, n/2)) where they all fit 16 bits (the
                               // kernels then read these), or null
     const void *sval;         // slotted values (double or float)
+    // the diagonal slices (dsl null: none)
+    const DiaSlice *dsl;      // one per slice
+    const DiaGroup *dgroup;   // the patterns' diagonals
+    const DiaRowMask *dmask;  // their rows
+    const void *dvals;        // blocks of kDiaRows per-row values (double or float)
+    const int32_t *drow;      // plan row of a vector's row (null: the same)
+    int32_t dgroups;          // groups of the longest list
 };
+
+// Whether a run of R right-hand sides reads the diagonal slices: their gathers
+// address a vector with 32-bit byte offsets, and with fewer than three waves
+// per compute unit (a wave takes 128 elements) the groups' dependent loads are
+// the time, where the sliced layout has twice the waves: 27-point 24^3 with 4
+// right-hand sides 7.9 against 6.8 us per power, 48^3 10.2 against 17.3 us;
+// lists of two groups are short enough (5-point 100^2 with 4: 3.6 against 4.0).
+// One right-hand side gains at every size, by its 16-byte loads.
+inline bool dia_fits(const DevMatrix &m, int R) {
+    const int64_t elements = (int64_t)m.n * R;
+    return m.dsl && elements * (int64_t)sizeof(double) < ((int64_t)1 << 32) &&
+           (R == 1 || m.dgroups <= 2 || elements >= 3 * 256 * 128);
+}
 
 constexpr int kMaxSegPowers = 64;   // powers per kernel launch
 

@@ -1,0 +1,141 @@
+"""GPU: matrices whose rows share column offsets are read as diagonals, 128
+rows at a time (plans of every kind of slice: one value per diagonal, a value
+per row, both, the matrix's first and last rows, and slices that fall back to
+the sliced layout because a row is unsorted or repeats a column).  One launch
+per power and the persistent kernels give the oracle's bits for every count of
+right-hand sides, for row counts around the slice height, in both row
+orders, with infinities and NaN next to rows that do not read them."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as w
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+mpk = pytest.importorskip("paper_2405_12525_amd")
+
+
+def banded(n, offsets, seed, vary=(), drop=0.0, odd_rows=False):
+    """Row i holds i + d for the offsets d that stay inside, each left out with
+    probability `drop`; diagonals in `vary` have a value per row, the others
+    one value (-0.0 for the first).  odd_rows: a few rows are unsorted, repeat
+    a column or are empty."""
+    g = np.random.default_rng(seed)
+    const = {d: float(v) for d, v in zip(offsets, g.standard_normal(len(offsets)))}
+    const[offsets[0]] = -0.0
+    rp, cols, vals = [0], [], []
+    for i in range(n):
+        c = [i + d for d in offsets if 0 <= i + d < n and g.random() >= drop]
+        v = [float(g.standard_normal()) if k - i in vary else const[k - i] for k in c]
+        if odd_rows and i % 300 == 7:
+            c, v = c[::-1], v[::-1]
+        elif odd_rows and i % 300 == 9 and c:
+            c, v = c + [c[-1]], v + [0.5]
+        elif odd_rows and i % 300 == 11:
+            c, v = [], []
+        cols += c
+        vals += v
+        rp.append(len(cols))
+    return w.CSR(n, np.array(rp, np.int32), np.array(cols, np.int32), np.array(vals, np.float64))
+
+
+def check(A, R, p=3, value_bits=64, x=None, reorder="none", order="original"):
+    x = w.uniform_vectors(A.n, R, 17 * A.n + R) if x is None else x
+    ref = oracle.powers(A, x, p, value_bits=value_bits)
+    P = mpk.Plan(A, value_bits=value_bits, reorder=reorder, order=order)
+    xd = torch.from_numpy(x).cuda()
+    for tune in (None, dict(schedule="powers", chunk_nnz=900), dict(schedule="wave", lag=3, chunk_nnz=900)):
+        if tune:
+            P.tune(**tune)
+        Y, B = P.run(xd, p), P.run_baseline(xd, p)
+        P.sync()
+        assert np.array_equal(Y.cpu().numpy().reshape(ref.shape), ref, equal_nan=True), (A.n, R, tune)
+        assert np.array_equal(B.cpu().numpy().reshape(ref.shape), ref, equal_nan=True), (A.n, R, tune)
+    P.close()
+
+
+OFFS = [-40, -3, -1, 0, 1, 2, 40]
+
+
+@pytest.mark.parametrize("n", [1, 3, 127, 128, 129, 255, 256, 257, 640, 1001])
+@pytest.mark.parametrize("R", [1, 2, 3, 16])
+def test_row_counts_around_the_slice_height(n, R):
+    check(banded(n, OFFS, n), R)
+    check(banded(n, OFFS, n + 1, vary=OFFS), R)
+
+
+@pytest.mark.parametrize("R", list(range(1, 17)))
+@pytest.mark.parametrize("vary", [(), (0,), (-3, 1, 40), tuple(OFFS)])
+def test_every_rhs_count_and_kind_of_diagonal(R, vary):
+    check(banded(900, OFFS, R, vary=vary, drop=0.1), R)
+    check(banded(900, OFFS, R, vary=vary), R, value_bits=32)
+
+
+@pytest.mark.parametrize("m", range(1, 10))
+def test_list_lengths(m):
+    offs = [-5, -4, -2, -1, 0, 1, 3, 4, 7][:m]
+    check(banded(700, offs, m, vary=offs[::2]), 1)
+    check(banded(700, offs, m, vary=offs[1::2]), 4)
+
+
+@pytest.mark.parametrize("reorder,R", [("none", 1), ("none", 5), ("bfs", 1), ("bfs", 4)])
+def test_slices_that_fall_back(reorder, R):
+    check(banded(4000, OFFS, 3, vary=(1,), drop=0.05, odd_rows=True), R, reorder=reorder)
+
+
+@pytest.mark.parametrize("R", [1, 2, 3])
+def test_infinities_and_nan_stay_in_their_columns(R):
+    A = banded(700, OFFS, 5, vary=(2,), drop=0.2)
+    x = w.uniform_vectors(A.n, R, 6)
+    x[0, 0], x[130, R - 1], x[131, 0], x[699, R - 1] = np.inf, np.nan, -np.inf, np.inf
+    x[200] = -0.0
+    A.val[A.rowptr[300]] = np.inf
+    A.val[A.rowptr[301]] = np.nan
+    with np.errstate(invalid="ignore"):
+        check(A, R, p=2, x=x)
+
+
+@pytest.mark.parametrize("R", [1, 2, 5])
+def test_recurrence_and_sums(R):
+    A = w.anderson_3d(9)          # periodic: wrapped rows at both ends of every line
+    x = w.random_sign_unit_vectors(A.n, R, 12)
+    xd = torch.from_numpy(x).cuda()
+    al, be, ga, wa, wb = mpk.cheb_time_coefficients(11, 0.7)
+    be = be + 0.25
+    for bits in (64, 32):
+        P = mpk.Plan(A, value_bits=bits)
+        assert np.array_equal(P.run_recur(xd, al, be, ga).cpu().numpy(),
+                              oracle.recur(A, x, al, be, ga, value_bits=bits))
+        ra, rb = oracle.poly_sums(A, x, al, be, ga, wa, wb, value_bits=bits)
+        for run in (P.run_poly, P.run_baseline_poly):
+            acc = run(xd, wa, wb, al, be, ga)[0].cpu().numpy()
+            assert np.array_equal(acc[0], ra) and np.array_equal(acc[1], rb)
+        P.close()
+
+
+def test_unaligned_vectors_and_captured_run():
+    A = w.stencil_3d27(12)
+    x = w.uniform_vectors(A.n, 1, 4)
+    buf = torch.zeros(A.n + 1, dtype=torch.float64, device="cuda")
+    out = torch.zeros(4 * A.n + 1, dtype=torch.float64, device="cuda")
+    xd, Y = buf[1:], out[1:].view(4, A.n)          # 8-byte aligned only
+    xd.copy_(torch.from_numpy(x[:, 0]))
+    ref = oracle.powers(A, x, 4)[:, :, 0]
+    P = mpk.Plan(A)
+    P.run(xd, 4, Y)
+    assert np.array_equal(Y.cpu().numpy(), ref)
+    G = P.capture(xd, 4, Y)
+    for _ in range(3):
+        Y.fill_(np.nan)
+        torch.cuda.synchronize()
+        G.launch()
+        assert np.array_equal(Y.cpu().numpy(), ref)
+    G.close()
+    status = torch.full((1,), 7, dtype=torch.int32).pin_memory()
+    Y.fill_(np.nan)
+    P.run_noalloc(xd, 4, Y, status=status)         # run before: prepared
+    torch.cuda.synchronize()
+    assert int(status[0]) == 0 and np.array_equal(Y.cpu().numpy(), ref)
+    P.close()
