@@ -172,7 +172,8 @@ struct mpk_plan_s {
     const DiaRowMask *dmask = nullptr;
     const void *dvals = nullptr;
     const int32_t *drow = nullptr;
-    int32_t dgroups = 0;
+    int32_t dgroups = 0, dreach = 0;
+    int64_t dval_bytes = 0;
     int64_t sell_entries = 0;
     std::map<int, std::unique_ptr<SliceSet>> spmv_slices;  // p x SpMV, by slice size
     // schedules and workspaces
@@ -193,7 +194,7 @@ struct mpk_plan_s {
                          d_outrow.as<int32_t>(), (int32_t)n, value_bits,
                          d_soff.as<const int64_t>(), d_rlen.as<int32_t>(), d_scol.as<int32_t>(),
                          d_sdel.as<int16_t>(), d_sval.ptr,
-                         dsl, dgroup, dmask, dvals, drow, dgroups};
+                         dsl, dgroup, dmask, dvals, drow, dgroups, dreach, dval_bytes};
     }
     ~mpk_plan_s() {
         if (!host_only) {
@@ -514,8 +515,16 @@ mpk_status_t build_dia(mpk_plan_t plan) {
             plan->dmask = dmask;
             plan->dvals = dvals;
             plan->drow = drow;
-            for (const DiaCount &c : cnt)
+            plan->dval_bytes = blocks * kDiaRows * (plan->value_bits / 8);
+            std::vector<int32_t> reach;
+            for (const DiaCount &c : cnt) {
                 plan->dgroups = std::max(plan->dgroups, (c.count + 3) / 4);
+                if (c.count > 0) reach.push_back(std::max(c.hi, -c.lo));
+            }
+            if (!reach.empty()) {   // the median
+                std::nth_element(reach.begin(), reach.begin() + reach.size() / 2, reach.end());
+                plan->dreach = reach[reach.size() / 2];
+            }
             return MPK_OK;
         }
     }

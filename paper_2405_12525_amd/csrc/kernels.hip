@@ -321,6 +321,7 @@ template <int RC>
 struct SpmvSellU {
     static constexpr int value = RC == 1 ? 2 : 4;
 };
+constexpr int64_t kMallBytes = (int64_t)256 << 20;   // memory-side cache
 constexpr int64_t kSpmvSellGrid = 4096;   // baseline workgroups per power (sliced layout)
 // DEL: the columns come from the 16-bit offsets (col = row + offset, wrapped
 // into [0, n)).  NT: the matrix is loaded non-temporally: by the one-launch-
@@ -392,9 +393,6 @@ template <typename T>
 __device__ __forceinline__ T ld_const(const T *p) {
     return *(const __attribute__((address_space(4))) T *)(uintptr_t)p;
 }
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef double v2d __attribute__((ext_vector_type(2)));
 
 // Two consecutive doubles (8-byte aligned).
 typedef double v2d __attribute__((ext_vector_type(2), aligned(8)));
@@ -409,17 +407,23 @@ __device__ __forceinline__ void load_2(double (&v)[2], const float *p) {
     v[0] = static_cast<double>(t.x);
     v[1] = static_cast<double>(t.y);
 }
-template <bool WT>
+// NT: past the caches (a vector too large to be read from them again).
+template <bool WT, bool NT>
 __device__ __forceinline__ void store_2(double *p, const double (&v)[2]) {
+    typedef double v2n __attribute__((ext_vector_type(2)));
     if constexpr (WT) {
         store_out<true>(p, v[0]);
         store_out<true>(p + 1, v[1]);
+    } else if constexpr (NT) {
+        typedef v2n v2u __attribute__((aligned(8)));
+        __builtin_nontemporal_store(v2n{v[0], v[1]}, reinterpret_cast<v2u *>(p));
     } else
         *reinterpret_cast<v2d *>(p) = v2d{v[0], v[1]};
 }
 
-// accumulate and finish for two consecutive elements.
-template <bool WT>
+// accumulate and finish for two consecutive elements; y2: y_{k-2} there, where
+// needs_prev says so (loaded ahead of the sum).
+template <bool WT, bool NT>
 __device__ __forceinline__ void accumulate_2(double *acc, int f, double w2, double w1, double w0,
                                              const double (&y2)[2], const double (&y1)[2],
                                              const double (&v)[2], size_t idx) {
@@ -446,17 +450,19 @@ __device__ __forceinline__ void accumulate_2(double *acc, int f, double w2, doub
             }
         }
     }
-    store_2<WT>(acc + idx, r);
+    store_2<WT, NT>(acc + idx, r);
 }
-template <bool WT, bool ACC>
-__device__ __forceinline__ void finish_2(const PowerIO &io, const double (&s)[2], size_t idx) {
+template <bool ACC>
+__device__ __forceinline__ bool needs_prev(const PowerIO &io) {
+    return (io.recur && io.prev && io.gamma != 0.0) || (ACC && ((io.fa | io.fb) & kAccT2));
+}
+template <bool WT, bool ACC, bool NT>
+__device__ __forceinline__ void finish_2(const PowerIO &io, const double (&s)[2],
+                                         const double (&y2)[2], size_t idx) {
     const bool b = io.recur && io.beta != 0.0;
     const bool g = io.recur && io.prev && io.gamma != 0.0;
-    const bool need1 = b || (ACC && ((io.fa | io.fb) & kAccT1));
-    const bool need2 = g || (ACC && ((io.fa | io.fb) & kAccT2));
-    double y1[2] = {0.0, 0.0}, y2[2] = {0.0, 0.0}, v[2];
-    if (need1) load_2(y1, io.in + idx);
-    if (need2) load_2(y2, io.prev + idx);
+    double y1[2] = {0.0, 0.0}, v[2];
+    if (b || (ACC && ((io.fa | io.fb) & kAccT1))) load_2(y1, io.in + idx);
     for (int i = 0; i < 2; ++i) {
         v[i] = s[i];
         if (io.recur) {
@@ -471,23 +477,26 @@ __device__ __forceinline__ void finish_2(const PowerIO &io, const double (&s)[2]
             }
         }
     }
-    store_2<WT>(io.out + idx, v);
+    store_2<WT, NT>(io.out + idx, v);
     if constexpr (ACC) {
-        accumulate_2<WT>(io.acc_a, io.fa, io.wa2, io.wa1, io.wa0, y2, y1, v, idx);
-        accumulate_2<WT>(io.acc_b, io.fb, io.wb2, io.wb1, io.wb0, y2, y1, v, idx);
+        accumulate_2<WT, NT>(io.acc_a, io.fa, io.wa2, io.wa1, io.wa0, y2, y1, v, idx);
+        accumulate_2<WT, NT>(io.acc_b, io.fb, io.wb2, io.wb1, io.wb0, y2, y1, v, idx);
     }
 }
 
-// How the lanes of a pass share a slice.  The kDiaRows * R elements of a
-// vector's slice are consecutive; pass q of R takes 128 of them and a lane two
+// How the lanes of a wave share a slice.  The kDiaRows * R elements of a
+// vector's slice are consecutive; a pass takes 128 of them and a lane two
 // neighbours (one 16-byte load per diagonal: the vector cache moves 64
 // bytes a clock that way and 32 with 8-byte loads): two rows (kOneRhs), two
-// right-hand sides of a row (kEven) or either (kOdd).
+// right-hand sides of a row (kEven) or either (kOdd).  (Two passes at once per
+// wave, to share the records, took 102 registers instead of 48 and was 5%
+// slower on 27-point 64^3 with 16 right-hand sides.)
 enum DiaMode { kOneRhs, kEven, kOdd };
 struct DiaLane {
     int32_t row[2];   // of the slice
     int32_t sub0;     // first row of the pass (uniform)
     uint32_t at;      // byte offset of the first element in a vector
+    bool live[2];     // the rows exist (slices with kDiaEdge)
 };
 // Rows sub0 .. sub0 + 63 of a mask (uniform).
 __device__ __forceinline__ uint64_t mask_from(uint64_t lo, uint64_t hi, int32_t sub0) {
@@ -495,16 +504,16 @@ __device__ __forceinline__ uint64_t mask_from(uint64_t lo, uint64_t hi, int32_t 
     return sub0 ? lo >> sub0 | hi << (64 - sub0) : lo;
 }
 
-// The first U diagonals of group g, added to the two sums of this lane.  All
-// loads go out before the products; a row without a diagonal keeps its sum.
+// The first U diagonals of group g, added to the lane's two sums.  All loads
+// go out before the products; a row without a diagonal keeps its sum.
 // vals: the group's first block of per-row values.  WHOLE: every row of the
 // pass has every diagonal.  EDGE: every load address is a row's own or one of
 // its columns; else any row plus any of the slice's offsets is inside the
-// vector.  live (EDGE): the lane's rows exist.
-template <typename V, int U, int MODE, int KIND, bool WHOLE, bool EDGE>
+// vector.  NT: the values are loaded past the caches.
+template <typename V, int U, int MODE, int KIND, bool WHOLE, bool EDGE, bool NT>
 __device__ __forceinline__ void dia_group(const DevMatrix &m, const double *in, int32_t g,
                                           const V *vals, const DiaLane &l, int32_t rbytes,
-                                          const bool (&live)[2], double (&s)[2]) {
+                                          double (&s)[2]) {
     typedef int v16i __attribute__((ext_vector_type(16), aligned(64)));
     typedef uint64_t v8u __attribute__((ext_vector_type(8), aligned(64)));
     const v16i h = ld_const(reinterpret_cast<const v16i *>(m.dgroup + g));
@@ -520,10 +529,15 @@ __device__ __forceinline__ void dia_group(const DevMatrix &m, const double *in, 
         a[u][0] = a[u][1] = __longlong_as_double((long long)ub);
         if (KIND == kDiaPerRow || (KIND == kDiaMixed && (h[5] >> u & 1))) {   // uniform
             if constexpr (MODE == kOneRhs) {
-                load_2(a[u], vals + (uint32_t)l.row[0]);
+                typedef V v2v __attribute__((ext_vector_type(2)));   // aligned to both
+                const v2v t = load_matrix<NT>(
+                    reinterpret_cast<const v2v *>(vals + (uint32_t)l.row[0]));
+                a[u][0] = static_cast<double>(t.x);
+                a[u][1] = static_cast<double>(t.y);
             } else {
-                a[u][0] = a[u][1] = static_cast<double>(vals[(uint32_t)l.row[0]]);
-                if (MODE == kOdd) a[u][1] = static_cast<double>(vals[(uint32_t)l.row[1]]);
+                a[u][0] = a[u][1] = static_cast<double>(load_matrix<NT>(vals + (uint32_t)l.row[0]));
+                if (MODE == kOdd)
+                    a[u][1] = static_cast<double>(load_matrix<NT>(vals + (uint32_t)l.row[1]));
             }
             vals += kDiaRows;
         }
@@ -557,8 +571,8 @@ __device__ __forceinline__ void dia_group(const DevMatrix &m, const double *in, 
             const uint32_t d = (uint32_t)(h[u] * rbytes);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                bit[u][i] = bit[u][i] && live[i];
-                const uint32_t q = (live[i] ? l.at + 8u * i : 0u) + (bit[u][i] ? d : 0u);
+                bit[u][i] = bit[u][i] && l.live[i];
+                const uint32_t q = (l.live[i] ? l.at + 8u * i : 0u) + (bit[u][i] ? d : 0u);
                 x[u][i] = *reinterpret_cast<const double *>(p + q);
             }
         }
@@ -572,101 +586,110 @@ __device__ __forceinline__ void dia_group(const DevMatrix &m, const double *in, 
         }
 }
 // All `count` diagonals from group g on.
-template <typename V, int MODE, int KIND, bool WHOLE, bool EDGE>
+template <typename V, int MODE, int KIND, bool WHOLE, bool EDGE, bool NT>
 __device__ __forceinline__ void dia_sum(const DevMatrix &m, const double *in, int32_t g,
                                         int32_t count, const V *vals, const DiaLane &l,
-                                        int32_t rbytes, const bool (&live)[2], double (&s)[2]) {
+                                        int32_t rbytes, double (&s)[2]) {
     for (; count >= 4; count -= 4, ++g) {
-        dia_group<V, 4, MODE, KIND, WHOLE, EDGE>(m, in, g, vals, l, rbytes, live, s);
+        dia_group<V, 4, MODE, KIND, WHOLE, EDGE, NT>(m, in, g, vals, l, rbytes, s);
         if (KIND == kDiaPerRow) vals += 4 * kDiaRows;
         if (KIND == kDiaMixed)
             vals += (size_t)__popc((unsigned)ld_const(&m.dgroup[g].vary)) * kDiaRows;
     }
     switch (count) {   // uniform
-    case 3: dia_group<V, 3, MODE, KIND, WHOLE, EDGE>(m, in, g, vals, l, rbytes, live, s); break;
-    case 2: dia_group<V, 2, MODE, KIND, WHOLE, EDGE>(m, in, g, vals, l, rbytes, live, s); break;
-    case 1: dia_group<V, 1, MODE, KIND, WHOLE, EDGE>(m, in, g, vals, l, rbytes, live, s); break;
+    case 3: dia_group<V, 3, MODE, KIND, WHOLE, EDGE, NT>(m, in, g, vals, l, rbytes, s); break;
+    case 2: dia_group<V, 2, MODE, KIND, WHOLE, EDGE, NT>(m, in, g, vals, l, rbytes, s); break;
+    case 1: dia_group<V, 1, MODE, KIND, WHOLE, EDGE, NT>(m, in, g, vals, l, rbytes, s); break;
     }
 }
-template <typename V, int MODE, int KIND>
+template <typename V, int MODE, int KIND, bool NT>
 __device__ __forceinline__ void dia_sum(const DevMatrix &m, const double *in, int32_t g,
                                         int32_t count, const V *vals, const DiaLane &l,
                                         int32_t rbytes, bool whole, double (&s)[2]) {
-    const bool live[2] = {true, true};
     if (MODE != kOneRhs && whole)   // uniform
-        dia_sum<V, MODE, KIND, true, false>(m, in, g, count, vals, l, rbytes, live, s);
+        dia_sum<V, MODE, KIND, true, false, NT>(m, in, g, count, vals, l, rbytes, s);
     else
-        dia_sum<V, MODE, KIND, false, false>(m, in, g, count, vals, l, rbytes, live, s);
+        dia_sum<V, MODE, KIND, false, false, NT>(m, in, g, count, vals, l, rbytes, s);
 }
 
-// Pass q of slice s (both uniform) by one wave.
-template <typename V, int MODE, bool WT, bool ACC>
+// Pass q of slice s (both uniform) by one wave.  STREAM: the power's data is
+// larger than the memory-side cache: results are stored past it, and so are the
+// per-row values loaded of all but `keep` of every 16 slices.
+template <typename V, int MODE, bool WT, bool ACC, bool STREAM>
 __device__ __forceinline__ void dia_pass(const DevMatrix &m, const PowerIO &io, int32_t R,
-                                         int32_t s, int32_t q) {
+                                         int32_t s, int32_t q, int32_t keep) {
     typedef int v8i __attribute__((ext_vector_type(8), aligned(16)));
     const v8i ds = ld_const(reinterpret_cast<const v8i *>(m.dsl + s));
     const int lane = (int)(threadIdx.x & (kWave - 1));
-    const int32_t f = q * 128 + 2 * lane;   // element of the slice
-    const size_t idx = (size_t)s * kDiaRows * R + f;
+    const size_t base = (size_t)s * kDiaRows * R;
+    const int32_t inv = (65536 + R - 1) / R;   // f / R = f * inv >> 16 for f < 128 * 16
     DiaLane l;
     bool whole = false;
+    const int32_t f0 = q * 128, f = f0 + 2 * lane;   // elements of the slice
+    const size_t idx = base + f;
+    l.at = (uint32_t)idx * (uint32_t)sizeof(double);
     if constexpr (MODE == kOneRhs) {
         l.row[0] = f;
         l.row[1] = f + 1;
         l.sub0 = 0;
     } else {
-        // f / R for f < 128 * 16: by a rounded-up reciprocal, exact there
-        const int32_t inv = (65536 + R - 1) / R;
         l.row[0] = f * inv >> 16;
         l.row[1] = MODE == kEven ? l.row[0] : (f + 1) * inv >> 16;
-        l.sub0 = q * 128 * inv >> 16;
-        const int32_t k = ((q * 128 + 127) * inv >> 16) + 1 - l.sub0;   // 8 .. 64 rows
+        l.sub0 = f0 * inv >> 16;
+        const int32_t k = ((f0 + 127) * inv >> 16) + 1 - l.sub0;   // 8 .. 64 rows
         const uint64_t sub = ~0ull >> (64 - k);
         const uint64_t lo = (uint64_t)(uint32_t)ds[4] | (uint64_t)(uint32_t)ds[5] << 32;
         const uint64_t hi = (uint64_t)(uint32_t)ds[6] | (uint64_t)(uint32_t)ds[7] << 32;
         whole = (mask_from(lo, hi, l.sub0) & sub) == sub;
     }
-    l.at = (uint32_t)idx * (uint32_t)sizeof(double);
     const int32_t rbytes = R * (int32_t)sizeof(double);
-    const V *vals = static_cast<const V *>(m.dvals) + (size_t)ds.z * kDiaRows;
+    const V *vals = static_cast<const V *>(m.dvals) + (size_t)ds[2] * kDiaRows;
     double sum[2] = {0.0, 0.0};
-    if (ds.y >= 0 && ds.w < kDiaEdge) {
-        if (ds.w == kDiaShared)
-            dia_sum<V, MODE, kDiaShared>(m, io.in, ds.x, ds.y, vals, l, rbytes, whole, sum);
-        else if (ds.w == kDiaPerRow)
-            dia_sum<V, MODE, kDiaPerRow>(m, io.in, ds.x, ds.y, vals, l, rbytes, whole, sum);
+    if (ds[1] >= 0 && ds[3] < kDiaEdge) {
+        double y2[2] = {0.0, 0.0};
+        if (needs_prev<ACC>(io)) load_2(y2, io.prev + idx);
+        if (ds[3] == kDiaShared)
+            dia_sum<V, MODE, kDiaShared, false>(m, io.in, ds[0], ds[1], vals, l, rbytes, whole, sum);
+        else if (ds[3] != kDiaPerRow)
+            dia_sum<V, MODE, kDiaMixed, false>(m, io.in, ds[0], ds[1], vals, l, rbytes, whole, sum);
+        else if (STREAM && (s & 15) >= keep)
+            dia_sum<V, MODE, kDiaPerRow, true>(m, io.in, ds[0], ds[1], vals, l, rbytes, whole, sum);
         else
-            dia_sum<V, MODE, kDiaMixed>(m, io.in, ds.x, ds.y, vals, l, rbytes, whole, sum);
-        finish_2<WT, ACC>(io, sum, idx);
+            dia_sum<V, MODE, kDiaPerRow, false>(m, io.in, ds[0], ds[1], vals, l, rbytes, whole, sum);
+        finish_2<WT, ACC, STREAM>(io, sum, y2, idx);
         return;
     }
-    const bool live[2] = {s * kDiaRows + l.row[0] < m.n, s * kDiaRows + l.row[1] < m.n};
-    if (ds.y >= 0) {
-        dia_sum<V, MODE, kDiaMixed, false, true>(m, io.in, ds.x, ds.y, vals, l, rbytes, live, sum);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) l.live[i] = s * kDiaRows + l.row[i] < m.n;
+    if (ds[1] >= 0) {
+        dia_sum<V, MODE, kDiaMixed, false, true, false>(m, io.in, ds[0], ds[1], vals, l, rbytes, sum);
     } else {   // rows as the sliced layout holds them
         const V *sval = static_cast<const V *>(m.sval);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            if (!live[i]) continue;
+            if (!l.live[i]) continue;
             const int32_t row = s * kDiaRows + l.row[i], pr = m.drow ? m.drow[row] : row;
-            const int32_t rr = (f + i) - l.row[i] * R, L = m.rlen[pr];
-            const int64_t base = m.soff[pr / kSellRows] + pr % kSellRows;
+            const int32_t rr = (int32_t)(idx + i - base) - l.row[i] * R, L = m.rlen[pr];
+            const int64_t b = m.soff[pr / kSellRows] + pr % kSellRows;
+            double t = 0.0;
             for (int32_t j = 0; j < L; j += 4) {
                 double a[4], x[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int64_t e = base + (int64_t)min(j + u, L - 1) * kSellRows;
-                    a[u] = static_cast<double>(sval[e]);
-                    x[u] = io.in[(size_t)m.scol[e] * R + rr];
+                    const int64_t c = b + (int64_t)min(j + u, L - 1) * kSellRows;
+                    a[u] = static_cast<double>(sval[c]);
+                    x[u] = io.in[(size_t)m.scol[c] * R + rr];
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (j + u < L) sum[i] = sum[i] + a[u] * x[u];
+                    if (j + u < L) t = t + a[u] * x[u];
             }
+            sum[i] = t;
         }
     }
-    if (live[0]) finish<WT, ACC>(io, sum[0], idx);
-    if (live[1]) finish<WT, ACC>(io, sum[1], idx + 1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        if (l.live[i]) finish<WT, ACC>(io, sum[i], idx + i);
 }
 
 // Products staged per thread and buffer: the slice path for R < 4 (R = 0 is
@@ -824,19 +847,39 @@ __global__ __launch_bounds__(kBlock) void spmv_sell_kernel(DevMatrix m, PowerIO 
                                                                    min(m.n, r0 + step));
 }
 
-// One power from the diagonal slices.  A wave takes one pass of one slice,
-// blocks dealt so that every XCD sweeps a contiguous eighth of the slices
-// (workgroup b runs on XCD b mod 8): a row's neighbours then mostly lie in the
-// same XCD's L2.
-template <typename V, int MODE, bool ACC>
-__global__ __launch_bounds__(kBlock) void spmv_dia_kernel(DevMatrix m, PowerIO io, int32_t R,
-                                                          int32_t units, int32_t per_xcd) {
-    const int32_t b = (int32_t)(blockIdx.x & 7) * per_xcd + (int32_t)(blockIdx.x >> 3);
+// u / d = u * inv >> 32 with inv = ceil(2^32 / d), exact while u * d < 2^32.
+struct FastDiv {
+    int32_t d;
+    uint32_t inv;   // (d = 1: not used; 0: every quotient is 0)
+    __device__ __forceinline__ int32_t operator()(int32_t u) const {
+        return d == 1 ? u : (int32_t)__umulhi((uint32_t)u, inv);
+    }
+};
+FastDiv fast_div(int32_t d) {
+    return FastDiv{d, d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d)};
+}
+
+// One power from the diagonal slices.  A wave takes one pass of one slice (per:
+// passes per slice); workgroup b runs on XCD b mod 8, and the blocks are dealt
+// in runs: XCD x takes run x, then run x + 8, ...
+//
+// Bound by: 27-point 128^3, one right-hand side: 18.6 us per power against
+// 125 from the sliced layout; the texture units (27 loads of 1 KB per 128 rows,
+// 453 MB at 24 TB/s) and launches are the time, HBM traffic is 35 MB.  With
+// general coefficients 71 against 125 us: 446 MB of values and 34 MB of
+// vectors, 6.7 TB/s.  Anderson 160^3 with 8 right-hand sides, recurrence: 185
+// against 364 us, 800 MB of vectors, 4.3 TB/s (a 4 GB copy: 4.8 TB/s).
+template <typename V, int MODE, bool ACC, bool STREAM>
+__global__ __launch_bounds__(kBlock, MODE == kOneRhs ? 6 : 1) void spmv_dia_kernel(
+        DevMatrix m, PowerIO io, int32_t R, int32_t units, FastDiv per, FastDiv run,
+        int32_t keep) {
+    const int32_t j = (int32_t)(blockIdx.x >> 3), c = run(j);
+    const int32_t b = (c * 8 + (int32_t)(blockIdx.x & 7)) * run.d + (j - c * run.d);
     const int32_t u = b * (kBlock / kWave) +
                       __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x / kWave));
     if (u >= units) return;
-    const int32_t s = MODE == kOneRhs ? u : u / R;
-    dia_pass<V, MODE, false, ACC>(m, io, R, s, u - s * R);
+    const int32_t s = per(u);
+    dia_pass<V, MODE, false, ACC, STREAM>(m, io, R, s, u - s * per.d, keep);
 }
 
 // ------------------------------------------------------------------ level-blocked
@@ -1394,7 +1437,7 @@ __global__ __launch_bounds__(kBlock) void load_probe_local_kernel(const double2 
 
 using SpmvFn = void (*)(DevMatrix, PowerIO, int32_t, DevSlices, int32_t, int32_t);
 using SpmvSellFn = void (*)(DevMatrix, PowerIO, int32_t);
-using SpmvDiaFn = void (*)(DevMatrix, PowerIO, int32_t, int32_t, int32_t);
+using SpmvDiaFn = void (*)(DevMatrix, PowerIO, int32_t, int32_t, FastDiv, FastDiv, int32_t);
 using LbFn = void (*)(LBParams, Coefs);
 using LbAccFn = void (*)(LBParams, Coefs, AccCoefs);
 using StepFn = void (*)(DevMatrix, DevSlices, const int32_t *, const int32_t *, const int32_t *,
@@ -1477,14 +1520,20 @@ SpmvSellFn spmv_sell_fn(int value_bits, int R, bool acc) {
     if (value_bits == 32) return acc ? t32().spmv_sell_acc[i] : t32().spmv_sell[i];
     return acc ? t64().spmv_sell_acc[i] : t64().spmv_sell[i];
 }
-template <typename V>
-SpmvDiaFn spmv_dia_of(int R, bool acc) {
-    if (R == 1) return acc ? spmv_dia_kernel<V, kOneRhs, true> : spmv_dia_kernel<V, kOneRhs, false>;
-    if (R % 2 == 0) return acc ? spmv_dia_kernel<V, kEven, true> : spmv_dia_kernel<V, kEven, false>;
-    return acc ? spmv_dia_kernel<V, kOdd, true> : spmv_dia_kernel<V, kOdd, false>;
+template <typename V, int MODE>
+SpmvDiaFn spmv_dia_of(bool acc, bool stream) {
+    if (stream)
+        return acc ? spmv_dia_kernel<V, MODE, true, true> : spmv_dia_kernel<V, MODE, false, true>;
+    return acc ? spmv_dia_kernel<V, MODE, true, false> : spmv_dia_kernel<V, MODE, false, false>;
 }
-SpmvDiaFn spmv_dia_fn(int value_bits, int R, bool acc) {
-    return value_bits == 32 ? spmv_dia_of<float>(R, acc) : spmv_dia_of<double>(R, acc);
+template <typename V>
+SpmvDiaFn spmv_dia_of(int R, bool acc, bool stream) {
+    if (R == 1) return spmv_dia_of<V, kOneRhs>(acc, stream);
+    return R % 2 == 0 ? spmv_dia_of<V, kEven>(acc, stream) : spmv_dia_of<V, kOdd>(acc, stream);
+}
+SpmvDiaFn spmv_dia_fn(int value_bits, int R, bool acc, bool stream) {
+    return value_bits == 32 ? spmv_dia_of<float>(R, acc, stream)
+                            : spmv_dia_of<double>(R, acc, stream);
 }
 // skip: the skip-ahead kernel (LDS-staged rows); else sell picks the
 // sliced-layout kernel
@@ -1585,11 +1634,40 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
         io.fb = acc->fb;
     }
     if (dia_fits(m, R)) {
-        const int32_t units = (m.n + kDiaRows - 1) / kDiaRows * R;   // passes of a wave
+        const int32_t per = R;   // passes of a slice, one wave each
+        const int32_t units = (m.n + kDiaRows - 1) / kDiaRows * per;
         const int32_t blocks = (units + kBlock / kWave - 1) / (kBlock / kWave);
-        const int32_t per = (blocks + 7) / 8;
-        hipLaunchKernelGGL(spmv_dia_fn(m.value_bits, R, acc != nullptr), dim3((unsigned)per * 8),
-                           dim3(kBlock), 0, (hipStream_t)stream, m, io, R, units, per);
+        // Each XCD sweeps an eighth of the rows, where the rows that its sweep
+        // reads ahead and behind fit its 4 MB L2 (27-point 64^3 with 16
+        // right-hand sides: 31.5 us per power against 34-35 for shorter runs).
+        // Where they do not (160^3 with 8: 3.3 MB), a run is an eighth of the
+        // farthest diagonal's reach, so that the same XCD reads a row's
+        // neighbours in the planes before and after, and its share of the
+        // window is an eighth (178 -> 159 us).
+        bool wide = (int64_t)m.dreach * 2 * R * 8 > ((int64_t)3 << 20);
+        const int64_t step = (int64_t)kDiaRows * (kBlock / kWave) * 8;   // elements of 8 blocks
+        int64_t run = ((int64_t)m.dreach * R + step / 2) / step;
+        int64_t grid = run ? (blocks + 8 * run - 1) / (8 * run) * 8 * run : 0;
+        wide = wide && grid / 8 * run < ((int64_t)1 << 32);   // FastDiv
+        if (!wide) {
+            run = (blocks + 7) / 8;
+            grid = 8 * run;
+        }
+        const FastDiv by_run = wide ? fast_div((int32_t)run) : FastDiv{(int32_t)run, 0u};
+        // What one power reads and writes, against the memory-side cache
+        // (256 MiB).  Where it does not fit, results go past the cache (160^3
+        // with 8 right-hand sides 190 -> 180 us; 27-point 64^3 with 16, which
+        // fits, 31.5 -> 38), and of every 16 slices' values only as many are
+        // cached as fit beside the vectors: those stay from one power to the
+        // next while the others stream (27-point 128^3, 446 MB of values: none
+        // cached 82 us, half 71, all 88).
+        const int64_t vecs = (int64_t)m.n * R * 8 * (recur && inm1 ? 3 : 2);
+        const bool past = vecs + m.dval_bytes > kMallBytes - ((int64_t)16 << 20);
+        const int32_t keep = (int32_t)std::min<int64_t>(
+            16, (kMallBytes - ((int64_t)32 << 20)) * 16 / std::max<int64_t>(1, m.dval_bytes));
+        hipLaunchKernelGGL(spmv_dia_fn(m.value_bits, R, acc != nullptr, past), dim3((unsigned)grid),
+                           dim3(kBlock), 0, (hipStream_t)stream, m, io, R, units, fast_div(per),
+                           by_run, keep);
         return (int)hipGetLastError();
     }
     if (m.scol) {  // sliced layout: row blocks of 256 / R rows, grid-stride

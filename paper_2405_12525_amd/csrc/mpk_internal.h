@@ -239,6 +239,8 @@ struct DevMatrix {
     const void *dvals;        // blocks of kDiaRows per-row values (double or float)
     const int32_t *drow;      // plan row of a vector's row (null: the same)
     int32_t dgroups;          // groups of the longest list
+    int32_t dreach;           // the farthest diagonal of a typical slice, in rows
+    int64_t dval_bytes;       // of the per-row values
 };
 
 // Whether a run of R right-hand sides reads the diagonal slices: their gathers

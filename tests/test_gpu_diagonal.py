@@ -139,3 +139,27 @@ def test_unaligned_vectors_and_captured_run():
     torch.cuda.synchronize()
     assert int(status[0]) == 0 and np.array_equal(Y.cpu().numpy(), ref)
     P.close()
+
+
+@pytest.mark.parametrize("R", [1, 4, 16])
+def test_vectors_past_the_caches(R):
+    """A periodic lattice whose planes are wider than an XCD's L2 holds and
+    whose vectors exceed the memory-side cache: streamed results and values,
+    blocks dealt in runs of an eighth of a plane; the persistent kernel, which
+    reads the sliced layout, gives the same bits."""
+    side, planes = (330, 40) if R == 1 else (160, 64 // R * 8)
+    offs = [(0, 0, -1), (0, -1, 0), (-1, 0, 0), (0, 0, 0), (1, 0, 0), (0, 1, 0), (0, 0, 1)]
+    n = side * side * planes
+    g = np.random.default_rng(R)
+    A = w._lattice_stencil((side, side, planes), offs, [0.25] * 7, True, "torus")
+    if R == 1:                       # a value per entry: 244 MB of them
+        A.val = g.standard_normal(A.nnz)
+    x = torch.from_numpy(g.uniform(-1, 1, (n, R))).cuda()
+    co = mpk.chebyshev_coefficients(3)
+    P = mpk.Plan(A, reorder="none")
+    Y, Z = P.run(x, 3), P.run_recur(x, *co)
+    P.tune(schedule="powers", workgroups=512)
+    Yp, Zp = P.run(x, 3), P.run_recur(x, *co)
+    P.sync()
+    assert torch.equal(Y, Yp) and torch.equal(Z, Zp)
+    P.close()
