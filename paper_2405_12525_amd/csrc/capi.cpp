@@ -674,6 +674,48 @@ mpk_status_t spmv_slices(mpk_plan_t plan, int R, SliceSet **out) {
     return MPK_OK;
 }
 
+// The kernel arguments of the segment of ps powers after power `base` (Y the p
+// outputs, or with poly the two-slot ring).
+void segment_args(mpk_plan_t plan, const double *x, double *Y, int base, int ps, int nrhs,
+                  const double *alpha, const double *beta, const double *gamma, const Poly *poly,
+                  SegArgs &a, Coefs &cf, AccCoefs &ac) {
+    const size_t stride = (size_t)plan->n * nrhs;
+    a = SegArgs{};
+    if (poly) {  // ring of two: power g in slot (g-1) mod 2
+        a.in0 = base == 0 ? x : Y + (size_t)((base - 1) & 1) * stride;
+        a.inm1 = base == 0 ? nullptr : (base == 1 ? x : Y + (size_t)((base - 2) & 1) * stride);
+        a.Y = Y;
+        a.acc_a = poly->acc_a;
+        a.acc_b = poly->acc_b;
+    } else {
+        a.in0 = base == 0 ? x : Y + (size_t)(base - 1) * stride;
+        a.inm1 = base == 0 ? nullptr : (base == 1 ? x : Y + (size_t)(base - 2) * stride);
+        a.Y = Y + (size_t)base * stride;
+    }
+    a.k0 = base;
+    a.p = ps;
+    a.R = nrhs;
+    a.recur = alpha ? 1 : 0;
+    cf = Coefs{};
+    if (alpha)
+        for (int j = 0; j < ps; ++j) {
+            cf.alpha[j] = alpha[base + j];
+            cf.beta[j] = beta[base + j];
+            cf.gamma[j] = gamma[base + j];
+        }
+    ac = AccCoefs{};
+    if (poly) {  // weights of the sequence's powers base-1 .. base+ps
+        for (int i = 0; i < ps + 2; ++i) {
+            ac.wa[i] = poly->w(poly->wa, base - 1 + i);
+            ac.wb[i] = poly->w(poly->wb, base - 1 + i);
+        }
+        for (int j = 0; j < ps; ++j) {
+            ac.fa[j] = poly->fa[(size_t)(base + j + 1)];
+            ac.fb[j] = poly->fb[(size_t)(base + j + 1)];
+        }
+    }
+}
+
 // The powers one after the other, one launch each (Y the p outputs, or with
 // poly the two-slot ring).
 mpk_status_t launch_powers(mpk_plan_t plan, const SliceSet *sl, const double *x, int p, int nrhs,
@@ -682,6 +724,18 @@ mpk_status_t launch_powers(mpk_plan_t plan, const SliceSet *sl, const double *x,
     const bool recur = alpha != nullptr;
     const size_t stride = (size_t)plan->n * nrhs;
     const DevMatrix m = plan->matrix();
+    if (dia_small(m)) {
+        for (int base = 0; base < p; base += kMaxSegPowers) {
+            SegArgs a;
+            Coefs cf;
+            AccCoefs ac;
+            segment_args(plan, x, Y, base, std::min(kMaxSegPowers, p - base), nrhs, alpha, beta,
+                         gamma, poly, a, cf, ac);
+            int rc = launch_small(m, a, cf, poly ? &ac : nullptr, stream_v);
+            if (rc) return hip_fail((hipError_t)rc, "small kernel launch");
+        }
+        return MPK_OK;
+    }
     for (int k = 1; k <= p; ++k) {
         // with poly, Y is a ring of two: power k in slot (k-1) mod 2
         const size_t o_in = poly ? (size_t)((k - 2) & 1) : (size_t)(k - 2);
@@ -844,40 +898,10 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
                         "no schedule for this p: call mpk_plan_prepare or run once outside capture first");
         SchedEntry *se = nullptr;
         if ((st = get_schedule(plan, ps, &se, wg_default))) return st;
-        SegArgs a{};
-        if (poly) {  // ring of two: power g in slot (g-1) mod 2
-            a.in0 = base == 0 ? x : Y + (size_t)((base - 1) & 1) * stride;
-            a.inm1 = base == 0 ? nullptr : (base == 1 ? x : Y + (size_t)((base - 2) & 1) * stride);
-            a.Y = Y;
-            a.acc_a = poly->acc_a;
-            a.acc_b = poly->acc_b;
-        } else {
-            a.in0 = base == 0 ? x : Y + (size_t)(base - 1) * stride;
-            a.inm1 = base == 0 ? nullptr : (base == 1 ? x : Y + (size_t)(base - 2) * stride);
-            a.Y = Y + (size_t)base * stride;
-        }
-        a.k0 = base;
-        a.p = ps;
-        a.R = nrhs;
-        a.recur = recur ? 1 : 0;
-        Coefs cf{};
-        if (recur)
-            for (int j = 0; j < ps; ++j) {
-                cf.alpha[j] = alpha[base + j];
-                cf.beta[j] = beta[base + j];
-                cf.gamma[j] = gamma[base + j];
-            }
-        AccCoefs ac{};
-        if (poly) {  // weights of the sequence's powers base-1 .. base+ps
-            for (int i = 0; i < ps + 2; ++i) {
-                ac.wa[i] = poly->w(poly->wa, base - 1 + i);
-                ac.wb[i] = poly->w(poly->wb, base - 1 + i);
-            }
-            for (int j = 0; j < ps; ++j) {
-                ac.fa[j] = poly->fa[(size_t)(base + j + 1)];
-                ac.fb[j] = poly->fb[(size_t)(base + j + 1)];
-            }
-        }
+        SegArgs a;
+        Coefs cf;
+        AccCoefs ac;
+        segment_args(plan, x, Y, base, ps, nrhs, alpha, beta, gamma, poly, a, cf, ac);
         const AccCoefs *acp = poly ? &ac : nullptr;
         SliceSet *ss = nullptr;
         if ((capturing || na) && !se->slices.count(slice_nnz(kTaskKP, nrhs)))

@@ -95,7 +95,7 @@ __device__ __forceinline__ void store_out(double *p, double v);
 // contraction; the sum's first term starts it.
 template <bool WT>
 __device__ __forceinline__ void accumulate(double *acc, int f, double w2, double w1, double w0,
-                                           double y2, const PowerIO &io, double v, size_t idx) {
+                                           double y2, const double *y1, double v, size_t idx) {
     if (!f) return;
     double r = 0.0;
     if (!(f & kAccZero)) {
@@ -107,7 +107,7 @@ __device__ __forceinline__ void accumulate(double *acc, int f, double w2, double
             have = true;
         }
         if (f & kAccT1) {
-            const double t = w1 * io.in[idx];
+            const double t = w1 * *y1;
             r = have ? r + t : t;
             have = true;
         }
@@ -161,8 +161,8 @@ __device__ __forceinline__ void finish(const PowerIO &io, double s, size_t idx) 
         }
     }
     store_out<WT>(io.out + idx, v);
-    accumulate<WT>(io.acc_a, io.fa, io.wa2, io.wa1, io.wa0, y2, io, v, idx);
-    accumulate<WT>(io.acc_b, io.fb, io.wb2, io.wb1, io.wb0, y2, io, v, idx);
+    accumulate<WT>(io.acc_a, io.fa, io.wa2, io.wa1, io.wa0, y2, io.in + idx, v, idx);
+    accumulate<WT>(io.acc_b, io.fb, io.wb2, io.wb1, io.wb0, y2, io.in + idx, v, idx);
 }
 
 // Loads of a slice with 1 <= nz nonzeros starting at nb, rows [rb, re):
@@ -612,22 +612,18 @@ __device__ __forceinline__ void dia_sum(const DevMatrix &m, const double *in, in
         dia_sum<V, MODE, KIND, false, false, NT>(m, in, g, count, vals, l, rbytes, s);
 }
 
-// Pass q of slice s (both uniform) by one wave.  STREAM: the power's data is
-// larger than the memory-side cache: results are stored past it, and so are the
-// per-row values loaded of all but `keep` of every 16 slices.
-template <typename V, int MODE, bool WT, bool ACC, bool STREAM>
-__device__ __forceinline__ void dia_pass(const DevMatrix &m, const PowerIO &io, int32_t R,
-                                         int32_t s, int32_t q, int32_t keep) {
-    typedef int v8i __attribute__((ext_vector_type(8), aligned(16)));
-    const v8i ds = ld_const(reinterpret_cast<const v8i *>(m.dsl + s));
+// The lane's place in pass q of slice s (both uniform; ds: the slice's record).
+// inv = ceil(2^16 / R): f / R = f * inv >> 16 for f < 128 * 16.  Returns whether
+// every row of the pass has every diagonal.
+typedef int v8i __attribute__((ext_vector_type(8), aligned(16)));
+template <int MODE>
+__device__ __forceinline__ bool dia_place(const v8i &ds, int32_t R, int32_t inv, int32_t s,
+                                          int32_t q, DiaLane &l, size_t &idx) {
     const int lane = (int)(threadIdx.x & (kWave - 1));
-    const size_t base = (size_t)s * kDiaRows * R;
-    const int32_t inv = (65536 + R - 1) / R;   // f / R = f * inv >> 16 for f < 128 * 16
-    DiaLane l;
-    bool whole = false;
     const int32_t f0 = q * 128, f = f0 + 2 * lane;   // elements of the slice
-    const size_t idx = base + f;
+    idx = (size_t)s * kDiaRows * R + f;
     l.at = (uint32_t)idx * (uint32_t)sizeof(double);
+    bool whole = false;
     if constexpr (MODE == kOneRhs) {
         l.row[0] = f;
         l.row[1] = f + 1;
@@ -642,34 +638,48 @@ __device__ __forceinline__ void dia_pass(const DevMatrix &m, const PowerIO &io, 
         const uint64_t hi = (uint64_t)(uint32_t)ds[6] | (uint64_t)(uint32_t)ds[7] << 32;
         whole = (mask_from(lo, hi, l.sub0) & sub) == sub;
     }
+    return whole;
+}
+// Whether every row of the slice exists and reads inside the vector wherever
+// its diagonals point.
+__device__ __forceinline__ bool dia_inner(const v8i &ds) { return ds[1] >= 0 && ds[3] < kDiaEdge; }
+
+// The lane's two row sums in an inner slice.  STREAM: the per-row values of all
+// but `keep` of every 16 slices are loaded past the caches.
+template <typename V, int MODE, bool STREAM>
+__device__ __forceinline__ void inner_sums(const DevMatrix &m, const double *in, int32_t R,
+                                           const v8i &ds, int32_t s, const DiaLane &l, bool whole,
+                                           int32_t keep, double (&sum)[2]) {
     const int32_t rbytes = R * (int32_t)sizeof(double);
     const V *vals = static_cast<const V *>(m.dvals) + (size_t)ds[2] * kDiaRows;
-    double sum[2] = {0.0, 0.0};
-    if (ds[1] >= 0 && ds[3] < kDiaEdge) {
-        double y2[2] = {0.0, 0.0};
-        if (needs_prev<ACC>(io)) load_2(y2, io.prev + idx);
-        if (ds[3] == kDiaShared)
-            dia_sum<V, MODE, kDiaShared, false>(m, io.in, ds[0], ds[1], vals, l, rbytes, whole, sum);
-        else if (ds[3] != kDiaPerRow)
-            dia_sum<V, MODE, kDiaMixed, false>(m, io.in, ds[0], ds[1], vals, l, rbytes, whole, sum);
-        else if (STREAM && (s & 15) >= keep)
-            dia_sum<V, MODE, kDiaPerRow, true>(m, io.in, ds[0], ds[1], vals, l, rbytes, whole, sum);
-        else
-            dia_sum<V, MODE, kDiaPerRow, false>(m, io.in, ds[0], ds[1], vals, l, rbytes, whole, sum);
-        finish_2<WT, ACC, STREAM>(io, sum, y2, idx);
-        return;
-    }
+    if (ds[3] == kDiaShared)
+        dia_sum<V, MODE, kDiaShared, false>(m, in, ds[0], ds[1], vals, l, rbytes, whole, sum);
+    else if (ds[3] != kDiaPerRow)
+        dia_sum<V, MODE, kDiaMixed, false>(m, in, ds[0], ds[1], vals, l, rbytes, whole, sum);
+    else if (STREAM && (s & 15) >= keep)
+        dia_sum<V, MODE, kDiaPerRow, true>(m, in, ds[0], ds[1], vals, l, rbytes, whole, sum);
+    else
+        dia_sum<V, MODE, kDiaPerRow, false>(m, in, ds[0], ds[1], vals, l, rbytes, whole, sum);
+}
+// The same in any other slice; sets l.live.
+template <typename V, int MODE>
+__device__ __forceinline__ void outer_sums(const DevMatrix &m, const double *in, int32_t R,
+                                           const v8i &ds, int32_t s, DiaLane &l,
+                                           double (&sum)[2]) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) l.live[i] = s * kDiaRows + l.row[i] < m.n;
     if (ds[1] >= 0) {
-        dia_sum<V, MODE, kDiaMixed, false, true, false>(m, io.in, ds[0], ds[1], vals, l, rbytes, sum);
+        const V *vals = static_cast<const V *>(m.dvals) + (size_t)ds[2] * kDiaRows;
+        dia_sum<V, MODE, kDiaMixed, false, true, false>(m, in, ds[0], ds[1], vals, l,
+                                                        R * (int32_t)sizeof(double), sum);
     } else {   // rows as the sliced layout holds them
         const V *sval = static_cast<const V *>(m.sval);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             if (!l.live[i]) continue;
             const int32_t row = s * kDiaRows + l.row[i], pr = m.drow ? m.drow[row] : row;
-            const int32_t rr = (int32_t)(idx + i - base) - l.row[i] * R, L = m.rlen[pr];
+            const int32_t rr = (int32_t)(l.at / 8u + i - (uint32_t)row * (uint32_t)R);
+            const int32_t L = m.rlen[pr];
             const int64_t b = m.soff[pr / kSellRows] + pr % kSellRows;
             double t = 0.0;
             for (int32_t j = 0; j < L; j += 4) {
@@ -678,7 +688,7 @@ __device__ __forceinline__ void dia_pass(const DevMatrix &m, const PowerIO &io, 
                 for (int u = 0; u < 4; ++u) {
                     const int64_t c = b + (int64_t)min(j + u, L - 1) * kSellRows;
                     a[u] = static_cast<double>(sval[c]);
-                    x[u] = io.in[(size_t)m.scol[c] * R + rr];
+                    x[u] = in[(size_t)m.scol[c] * R + rr];
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
@@ -687,6 +697,26 @@ __device__ __forceinline__ void dia_pass(const DevMatrix &m, const PowerIO &io, 
             sum[i] = t;
         }
     }
+}
+
+// Pass q of slice s by one wave.  STREAM: the power's data is larger than the
+// memory-side cache: results are stored past it too.
+template <typename V, int MODE, bool WT, bool ACC, bool STREAM>
+__device__ __forceinline__ void dia_pass(const DevMatrix &m, const PowerIO &io, int32_t R,
+                                         int32_t inv, int32_t s, int32_t q, int32_t keep) {
+    const v8i ds = ld_const(reinterpret_cast<const v8i *>(m.dsl + s));
+    DiaLane l;
+    size_t idx;
+    const bool whole = dia_place<MODE>(ds, R, inv, s, q, l, idx);
+    double sum[2] = {0.0, 0.0};
+    if (__builtin_expect(dia_inner(ds), 1)) {
+        double y2[2] = {0.0, 0.0};
+        if (needs_prev<ACC>(io)) load_2(y2, io.prev + idx);
+        inner_sums<V, MODE, STREAM>(m, io.in, R, ds, s, l, whole, keep, sum);
+        finish_2<WT, ACC, STREAM>(io, sum, y2, idx);
+        return;
+    }
+    outer_sums<V, MODE>(m, io.in, R, ds, s, l, sum);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
         if (l.live[i]) finish<WT, ACC>(io, sum[i], idx + i);
@@ -870,16 +900,98 @@ FastDiv fast_div(int32_t d) {
 // vectors, 6.7 TB/s.  Anderson 160^3 with 8 right-hand sides, recurrence: 185
 // against 364 us, 800 MB of vectors, 4.3 TB/s (a 4 GB copy: 4.8 TB/s).
 template <typename V, int MODE, bool ACC, bool STREAM>
-__global__ __launch_bounds__(kBlock, MODE == kOneRhs ? 6 : 1) void spmv_dia_kernel(
-        DevMatrix m, PowerIO io, int32_t R, int32_t units, FastDiv per, FastDiv run,
+__global__ __launch_bounds__(kBlock, MODE == kOneRhs ? 8 : 1) void spmv_dia_kernel(
+        DevMatrix m, PowerIO io, int32_t R, int32_t inv, int32_t units, FastDiv per, FastDiv run,
         int32_t keep) {
     const int32_t j = (int32_t)(blockIdx.x >> 3), c = run(j);
     const int32_t b = (c * 8 + (int32_t)(blockIdx.x & 7)) * run.d + (j - c * run.d);
     const int32_t u = b * (kBlock / kWave) +
                       __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x / kWave));
     if (u >= units) return;
-    const int32_t s = per(u);
-    dia_pass<V, MODE, false, ACC, STREAM>(m, io, R, s, u - s * per.d, keep);
+    const int32_t s = MODE == kOneRhs ? u : per(u);
+    dia_pass<V, MODE, false, ACC, STREAM>(m, io, MODE == kOneRhs ? 1 : R, inv, s,
+                                          MODE == kOneRhs ? 0 : u - s * per.d, keep);
+}
+
+// All powers of a segment in one launch: right-hand sides do not depend on each
+// other, so workgroup r computes column r alone, with the last two vectors in
+// LDS and a barrier between the powers.  A launch per power takes 3.7 us
+// however little it does; here a power of 5-point 32^2 takes 0.9 us and one of
+// 64^2 2.5, by then the compute unit's instruction issue (some 250
+// instructions per 128 rows; with the vectors in memory 3.1 us, by latency).
+constexpr int kSmallBlock = 1024;
+// Barrier of the workgroup that orders LDS only: stores to memory, which no
+// other thread reads in this launch, stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+template <typename V, bool ACC>
+__device__ __forceinline__ void small_body(const DevMatrix &m, const SegArgs &a, const Coefs &cf,
+                                           const AccCoefs *ac) {
+    // y_{k-1} and y_{k-2}, whose place y_k takes (each element by its own lane)
+    __shared__ double buf[2][kSmallRows];
+    const int32_t R = a.R, r = (int32_t)blockIdx.x;
+    for (int32_t i = threadIdx.x; i < m.n; i += kSmallBlock) {
+        buf[0][i] = a.in0[(size_t)i * R + r];
+        if (a.inm1) buf[1][i] = a.inm1[(size_t)i * R + r];
+    }
+    __syncthreads();
+    const int32_t n_sl = (m.n + kDiaRows - 1) / kDiaRows;
+    for (int32_t k = 1; k <= a.p; ++k) {
+        PowerIO io = power_io<ACC>(a, cf, ac, k, m.n);
+        const double *in = buf[(k - 1) & 1];
+        double *out = buf[k & 1];
+        const bool prev = io.prev != nullptr;
+        for (int32_t s = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x / kWave)); s < n_sl;
+             s += kSmallBlock / kWave) {
+            const v8i ds = ld_const(reinterpret_cast<const v8i *>(m.dsl + s));
+            DiaLane l;
+            size_t idx;
+            dia_place<kOneRhs>(ds, 1, 0, s, 0, l, idx);
+            double sum[2] = {0.0, 0.0};
+            l.live[0] = l.live[1] = true;
+            if (dia_inner(ds)) inner_sums<V, kOneRhs, false>(m, in, 1, ds, s, l, false, 0, sum);
+            else outer_sums<V, kOneRhs>(m, in, 1, ds, s, l, sum);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if (!l.live[i]) continue;
+                const int32_t row = s * kDiaRows + l.row[i];
+                const size_t e = (size_t)row * R + r;
+                // as finish(), with the last two vectors from LDS
+                const double y2 = prev ? out[row] : 0.0;
+                double v = sum[i];
+                if (io.recur) {
+                    v = io.alpha * sum[i];
+                    if (io.beta != 0.0) {
+                        const double t = io.beta * in[row];
+                        v = v + t;
+                    }
+                    if (prev && io.gamma != 0.0) {
+                        const double t = io.gamma * y2;
+                        v = v + t;
+                    }
+                }
+                out[row] = v;
+                io.out[e] = v;
+                if constexpr (ACC) {
+                    accumulate<false>(io.acc_a, io.fa, io.wa2, io.wa1, io.wa0, y2, in + row, v, e);
+                    accumulate<false>(io.acc_b, io.fb, io.wb2, io.wb1, io.wb0, y2, in + row, v, e);
+                }
+            }
+        }
+        lds_barrier();
+    }
+}
+template <typename V>
+__global__ __launch_bounds__(kSmallBlock) void small_dia_kernel(DevMatrix m, SegArgs a, Coefs cf) {
+    small_body<V, false>(m, a, cf, nullptr);
+}
+template <typename V>
+__global__ __launch_bounds__(kSmallBlock) void small_dia_acc_kernel(DevMatrix m, SegArgs a,
+                                                                    Coefs cf, AccCoefs ac) {
+    small_body<V, true>(m, a, cf, &ac);
 }
 
 // ------------------------------------------------------------------ level-blocked
@@ -1437,7 +1549,8 @@ __global__ __launch_bounds__(kBlock) void load_probe_local_kernel(const double2 
 
 using SpmvFn = void (*)(DevMatrix, PowerIO, int32_t, DevSlices, int32_t, int32_t);
 using SpmvSellFn = void (*)(DevMatrix, PowerIO, int32_t);
-using SpmvDiaFn = void (*)(DevMatrix, PowerIO, int32_t, int32_t, FastDiv, FastDiv, int32_t);
+using SpmvDiaFn = void (*)(DevMatrix, PowerIO, int32_t, int32_t, int32_t, FastDiv, FastDiv,
+                           int32_t);
 using LbFn = void (*)(LBParams, Coefs);
 using LbAccFn = void (*)(LBParams, Coefs, AccCoefs);
 using StepFn = void (*)(DevMatrix, DevSlices, const int32_t *, const int32_t *, const int32_t *,
@@ -1666,7 +1779,8 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
         const int32_t keep = (int32_t)std::min<int64_t>(
             16, (kMallBytes - ((int64_t)32 << 20)) * 16 / std::max<int64_t>(1, m.dval_bytes));
         hipLaunchKernelGGL(spmv_dia_fn(m.value_bits, R, acc != nullptr, past), dim3((unsigned)grid),
-                           dim3(kBlock), 0, (hipStream_t)stream, m, io, R, units, fast_div(per),
+                           dim3(kBlock), 0, (hipStream_t)stream, m, io, R,
+                           (65536 + R - 1) / R, units, fast_div(per),
                            by_run, keep);
         return (int)hipGetLastError();
     }
@@ -1681,6 +1795,21 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
     const int32_t grid = (n_slices + per - 1) / per;
     hipLaunchKernelGGL(spmv_fn(m.value_bits, R, acc != nullptr), dim3((unsigned)grid), dim3(kBlock), 0,
                        (hipStream_t)stream, m, io, R, sl, n_slices, per);
+    return (int)hipGetLastError();
+}
+
+int launch_small(const DevMatrix &m, const SegArgs &a, const Coefs &cf, const AccCoefs *acc,
+                 void *stream) {
+    if (a.R < 1 || a.R > 16 || a.p < 1 || a.p > kMaxSegPowers || m.n > kSmallRows || !m.dsl)
+        return (int)hipErrorInvalidValue;
+    const dim3 grid((unsigned)a.R), block(kSmallBlock);
+    if (acc)
+        hipLaunchKernelGGL(m.value_bits == 32 ? small_dia_acc_kernel<float>
+                                              : small_dia_acc_kernel<double>,
+                           grid, block, 0, (hipStream_t)stream, m, a, cf, *acc);
+    else
+        hipLaunchKernelGGL(m.value_bits == 32 ? small_dia_kernel<float> : small_dia_kernel<double>,
+                           grid, block, 0, (hipStream_t)stream, m, a, cf);
     return (int)hipGetLastError();
 }
 

@@ -256,6 +256,17 @@ inline bool dia_fits(const DevMatrix &m, int R) {
            (R == 1 || m.dgroups <= 2 || elements >= 3 * 256 * 128);
 }
 
+// Whether all powers run in one launch, a workgroup per right-hand side with
+// its vectors in LDS: small matrices, where a power on one compute unit takes
+// less than a launch.  us for p = 16, launches against this: 5-point 32^2 48
+// and 24, 64^2 53 and 45; Anderson 12^3 65 and 42; 27-point 12^3 85 and 69; but
+// Anderson 16^3 66 and 66, 27-point 16^3 92 and 121, 5-point 90^2 55 and 79.
+constexpr int kSmallRows = 4096;
+inline bool dia_small(const DevMatrix &m) {
+    return m.dsl && (m.n <= kSmallRows / 2 ? m.dgroups <= 8
+                                           : m.n <= kSmallRows && m.dgroups <= 2);
+}
+
 constexpr int kMaxSegPowers = 64;   // powers per kernel launch
 
 // Slices: runs of consecutive rows whose nonzeros fit one LDS staging buffer
@@ -402,6 +413,9 @@ int launch_lb(const DevMatrix &m, const DevSchedule &s, const DevWorkspace &ws,
 int launch_step(const DevMatrix &m, DevSlices sl, const int32_t *chunk_sptr,
                 const int32_t *chunk_row, const int32_t *tasks, int32_t n_tasks,
                 const SegArgs &a, const Coefs *cf, const AccCoefs *acc, void *stream);
+// All powers of a segment, a workgroup per right-hand side (dia_small).
+int launch_small(const DevMatrix &m, const SegArgs &a, const Coefs &cf, const AccCoefs *acc,
+                 void *stream);
 // One power over all rows; workgroup b walks slices [b*per, (b+1)*per).
 // acc may be null (no weighted sums).
 int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_t per,

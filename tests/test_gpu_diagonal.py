@@ -115,6 +115,25 @@ def test_recurrence_and_sums(R):
         P.close()
 
 
+@pytest.mark.parametrize("side,R", [(5, 1), (12, 3), (16, 2)])
+def test_more_powers_than_a_segment_holds(side, R):
+    """p = 70 on one workgroup per column (5^3, 12^3) and on launches (16^3)."""
+    A = w.anderson_3d(side)
+    x = w.random_sign_unit_vectors(A.n, R, side)
+    xd = torch.from_numpy(x).cuda()
+    al, be, ga, wa, wb = mpk.cheb_time_coefficients(70, 3.0)
+    P = mpk.Plan(A)
+    ref = oracle.recur(A, x, al, be, ga)
+    assert np.array_equal(P.run_recur(xd, al, be, ga).cpu().numpy(), ref)
+    assert np.array_equal(P.run(xd, 70).cpu().numpy(), oracle.powers(A, x, 70))
+    ra, rb = oracle.poly_sums(A, x, al, be, ga, wa, wb)
+    acc, ring = P.run_poly(xd, wa, wb, al, be, ga)
+    acc = acc.cpu().numpy()
+    assert np.array_equal(acc[0], ra) and np.array_equal(acc[1], rb)
+    assert np.array_equal(ring.cpu().numpy()[1], ref[69])
+    P.close()
+
+
 def test_unaligned_vectors_and_captured_run():
     A = w.stencil_3d27(12)
     x = w.uniform_vectors(A.n, 1, 4)
