@@ -136,6 +136,20 @@ struct Workspace {
     }
 };
 
+// Vectors in the caller's numbering, for one run_converted at a time.
+struct VecSpace {
+    DevBuf buf;
+    hipEvent_t ev = nullptr;   // after the last run that used it
+    hipStream_t last_stream = nullptr;
+    bool recorded = false;
+    ~VecSpace() {
+        if (!ev) return;
+        (void)hipEventSynchronize(ev);
+        (void)hipEventDestroy(ev);
+    }
+};
+constexpr size_t kVecSpaces = 4;   // per plan: as many runs at once convert
+
 double now_ms() {
     using namespace std::chrono;
     return duration<double, std::milli>(steady_clock::now().time_since_epoch()).count();
@@ -171,7 +185,7 @@ struct mpk_plan_s {
     const DiaGroup *dgroup = nullptr;
     const DiaRowMask *dmask = nullptr;
     const void *dvals = nullptr;
-    const int32_t *drow = nullptr;
+    const int32_t *drow = nullptr;           // caller's row -> plan row (permuted plans)
     int32_t dgroups = 0, dreach = 0;
     int64_t dval_bytes = 0;
     int64_t sell_entries = 0;
@@ -182,6 +196,7 @@ struct mpk_plan_s {
     std::map<int, std::unique_ptr<SchedEntry>> scheds;
     std::vector<std::unique_ptr<SchedEntry>> retired;
     std::vector<std::unique_ptr<Workspace>> pool;
+    std::vector<std::unique_ptr<VecSpace>> vectors;   // of runs that convert
     std::map<long long, int> wg_cache;
     std::set<std::pair<int, int>> shapes;         // (powers, slice size) run or prepared unscheduled
     std::map<hipStream_t, hipEvent_t> stream_ev;  // last run issued per stream
@@ -189,12 +204,19 @@ struct mpk_plan_s {
     std::map<hipStream_t, int> status_slot;       // stream -> its word
     uint64_t fingerprint = 0;                     // of the input CSR and options
 
-    DevMatrix matrix() const {
+    // Whether the diagonal slices are in another numbering than the vectors.
+    bool dia_converts() const { return order == MPK_ORDER_PLAN && drow; }
+    // The matrix as runs on the plan's vectors take it, or (callers) for vectors
+    // in the caller's numbering in a plan with dia_converts(): diagonals only.
+    DevMatrix matrix(bool callers = false) const {
+        const bool dia = callers || !dia_converts();
         return DevMatrix{d_rowptr.as<int32_t>(), d_col.as<int32_t>(), d_val.ptr,
                          d_outrow.as<int32_t>(), (int32_t)n, value_bits,
-                         d_soff.as<const int64_t>(), d_rlen.as<int32_t>(), d_scol.as<int32_t>(),
-                         d_sdel.as<int16_t>(), d_sval.ptr,
-                         dsl, dgroup, dmask, dvals, drow, dgroups, dreach, dval_bytes};
+                         d_soff.as<const int64_t>(), d_rlen.as<int32_t>(),
+                         callers ? nullptr : d_scol.as<int32_t>(), d_sdel.as<int16_t>(),
+                         d_sval.ptr,
+                         dia ? dsl : nullptr, dgroup, dmask, dvals, drow, dgroups,
+                         dreach, dval_bytes};
     }
     ~mpk_plan_s() {
         if (!host_only) {
@@ -432,10 +454,11 @@ mpk_status_t build_dia(mpk_plan_t plan) {
     mpk_status_t st;
     const size_t n = (size_t)plan->n, n_sl = (n + kDiaRows - 1) / kDiaRows;
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    // device buffers: the rows' places in the sliced layout (permuted plans,
-    // whose vectors stay in the caller's order) and the counts; then one block
+    // device buffers: the rows' places in the sliced layout (permuted plans)
+    // and the counts; then one block
     // for all that the kernels read (each hipMalloc and hipFree costs ~0.3 ms)
-    const bool permuted = plan->d_outrow.ptr != nullptr;
+    const bool permuted = plan->d_perm.ptr != nullptr;
+    const int32_t *cmap = plan->order == MPK_ORDER_PLAN ? plan->d_perm.as<int32_t>() : nullptr;
     const size_t row_b = permuted ? up(n * 4) : 0;
     if ((st = plan->d_dcount.alloc(row_b + n_sl * sizeof(DiaCount)))) return st;
     char *c0 = plan->d_dcount.as<char>();
@@ -447,12 +470,13 @@ mpk_status_t build_dia(mpk_plan_t plan) {
     const int64_t *soff = plan->d_soff.as<const int64_t>();
     const int32_t *rlen = plan->d_rlen.as<int32_t>(), *scol = plan->d_scol.as<int32_t>();
     std::vector<DiaCount> cnt;
-    int rc = gpu_dia_count(plan->n, drow, soff, rlen, scol, plan->d_sval.ptr, plan->value_bits,
+    int rc = gpu_dia_count(plan->n, drow, cmap, soff, rlen, scol, plan->d_sval.ptr, plan->value_bits,
                            plan->d_sdel.ptr ? 16 : 32, reinterpret_cast<DiaCount *>(c0 + row_b), cnt);
     if (rc) return hip_fail((hipError_t)rc, "diagonal slices");
     size_t taken = 0;
     for (const DiaCount &c : cnt) taken += c.count >= 0;
-    if (2 * taken < n_sl) {
+    // (the sliced layout cannot stand in for a slice in another numbering)
+    if (2 * taken < n_sl || (cmap && taken < n_sl)) {
         plan->d_dcount.release();
         return MPK_OK;
     }
@@ -506,7 +530,7 @@ mpk_status_t build_dia(mpk_plan_t plan) {
         uint8_t *demit = reinterpret_cast<uint8_t *>(b + g_b + m_b + s_b);
         void *dvals = b + g_b + m_b + s_b + e_b;
         int differ = 0;
-        rc = gpu_dia_fill(plan->n, drow, soff, rlen, scol, plan->d_sval.ptr, plan->value_bits, sl,
+        rc = gpu_dia_fill(plan->n, drow, cmap, soff, rlen, scol, plan->d_sval.ptr, plan->value_bits, sl,
                           emit, groups, dsl, demit, dgroup, dmask, dvals, &differ);
         if (rc) return hip_fail((hipError_t)rc, "diagonal slices");
         if (!differ) {
@@ -774,8 +798,9 @@ mpk_status_t launch_powers(mpk_plan_t plan, const SliceSet *sl, const double *x,
 // with 8 right-hand sides, p = 16: 7568 against 3023 us), its runs need that
 // invalidation (random band of 2^22 rows in BFS order, p = 6: 4245 against
 // 2405 us) or the rows are staged from CSR (the same band in its own order:
-// 3450 against 2230 us).  Elsewhere it stays (27-point 96^3 in plan order, p =
-// 8: 340 against 444 us).
+// 3450 against 2230 us), and below 2^19 elements (5-point 300^2 in plan order, p
+// = 12: 100 against 63 us).  Elsewhere it stays (27-point 96^3 in plan order, p =
+// 8: 340 against 442 us).
 bool library_order(const mpk_tune_t &t) {
     return t.schedule == MPK_SCHED_WAVE && t.lag == 0 && t.workgroups == 0 && t.skip_ahead == 0 &&
            !t.acquire_always;
@@ -784,7 +809,7 @@ bool library_order(const mpk_tune_t &t) {
 // Whether such a run can do without a schedule: whatever the right-hand sides
 // and pointers, it takes one launch per power.
 bool never_scheduled(mpk_plan_t plan) {
-    return library_order(plan->tune) && plan->dsl &&
+    return library_order(plan->tune) && plan->dsl && !plan->dia_converts() &&
            plan->n / kChunkRows + 1 + kMaxQueues + 2 <= kScratchWords;
 }
 
@@ -801,6 +826,63 @@ mpk_status_t check_scratch(int32_t n_chunks) {
                                       " chunks; the no-allocation run holds at most " +
                                       std::to_string(kScratchWords - kMaxQueues - 2) +
                                       " (raise tune.chunk_nnz)");
+}
+
+// A run of a plan in its own order whose diagonal slices are in the caller's
+// numbering: x is converted once, the powers run one launch each on a ring of
+// two vectors in the caller's numbering, and each result is gathered into Y.
+// Returns false, nothing launched, where the vectors cannot be had: kVecSpaces
+// runs are under way, or memory is short (plan->mu held; not under capture).
+bool run_converted(mpk_plan_t plan, const double *x, int p, int nrhs, const double *alpha,
+                   const double *beta, const double *gamma, double *Y, hipStream_t stream,
+                   mpk_status_t &st) {
+    const size_t vec = (size_t)plan->n * nrhs, bytes = 3 * vec * sizeof(double);
+    auto idle = [&](const VecSpace &w) {
+        return !w.recorded || hipEventQuery(w.ev) == hipSuccess;
+    };
+    VecSpace *vs = nullptr;
+    for (auto &w : plan->vectors)
+        if (!vs && w->buf.bytes >= bytes && (w->last_stream == stream || idle(*w))) vs = w.get();
+    if (!vs) {   // an idle one made larger, or one more
+        for (auto &w : plan->vectors)
+            if (!vs && idle(*w)) vs = w.get();
+        if (!vs) {
+            if (plan->vectors.size() >= kVecSpaces) return false;
+            auto w = std::make_unique<VecSpace>();
+            if (hipEventCreateWithFlags(&w->ev, hipEventDisableTiming) != hipSuccess) {
+                w->ev = nullptr;
+                return false;
+            }
+            vs = w.get();
+            plan->vectors.push_back(std::move(w));
+        }
+        vs->recorded = false;
+        if (vs->buf.alloc(bytes)) {
+            (void)hipGetLastError();
+            return false;
+        }
+    }
+    double *xc = vs->buf.as<double>(), *ring = xc + vec;
+    const DevMatrix m = plan->matrix(true);
+    const bool recur = alpha != nullptr;
+    int rc = launch_permute(plan->drow, plan->n, false, x, xc, 1, nrhs, stream);
+    for (int k = 1; k <= p && !rc; ++k) {
+        const double *in = k == 1 ? xc : ring + (size_t)(k & 1) * vec;
+        double *out = ring + (size_t)((k - 1) & 1) * vec;
+        const double *prev = k == 1 ? nullptr : k == 2 ? xc : out;   // y_{k-2}, element by element
+        rc = launch_spmv_power(m, DevSlices{}, 0, kSpmvSlicesPerWG, in, prev, out, nrhs,
+                               recur ? 1 : 0, recur ? alpha[k - 1] : 1.0, recur ? beta[k - 1] : 0.0,
+                               recur ? gamma[k - 1] : 0.0, nullptr, stream);
+        if (!rc)
+            rc = launch_permute(plan->d_perm.as<int32_t>(), plan->n, false, out,
+                                Y + (size_t)(k - 1) * vec, 1, nrhs, stream);
+    }
+    st = rc ? hip_fail((hipError_t)rc, "kernel launch") : MPK_OK;
+    hipError_t e = hipEventRecord(vs->ev, stream);
+    if (e != hipSuccess && !st) st = hip_fail(e, "hipEventRecord");
+    vs->recorded = true;
+    vs->last_stream = stream;
+    return true;
 }
 
 // What a run of a segment of ps powers fetches first (plan->mu held): the
@@ -880,8 +962,27 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
     const bool lines_can = !poly && !plan->d_outrow.ptr &&
                            ((size_t)plan->n * nrhs) % kLineRows == 0 &&
                            reinterpret_cast<uintptr_t>(Y) % 128 == 0;
+    const int64_t elements = (int64_t)plan->n * nrhs;
     const bool per_power = library_order(plan->tune) &&
-                           (m.dsl || !m.scol || !lines_can);
+                           (m.dsl || !m.scol || !lines_can || elements < ((int64_t)1 << 19));
+    // Converting adds a launch and two passes over a vector per power.  us, one
+    // launch per power in the plan's order against converted: 27-point 96^3, p =
+    // 8: 442 and 149; Anderson 100^3, 16 right-hand sides, p = 10: 2001 and 1633;
+    // but 5-point 300^2, p = 12: 63 and 88; general 27-point 64^3, 8 right-hand
+    // sides, p = 8: 512 and 602.
+    if (library_order(plan->tune) && plan->dia_converts() && !poly && !na && !capturing &&
+        dia_addressable(plan->matrix(true), nrhs) &&
+        elements >= (int64_t)1 << (nrhs == 1 ? 19 : 23)) {
+        // what a capture or a no-allocation run of the same shape may ask for next
+        for (int base = 0; base < p; base += seg)
+            if ((st = prepare_segment(plan, std::min(seg, p - base), nrhs, wg_default, stream,
+                                      false)))
+                return st;
+        SliceSet *sl = nullptr;
+        if ((st = spmv_slices(plan, nrhs, &sl))) return st;
+        if (run_converted(plan, x, p, nrhs, alpha, beta, gamma, Y, stream, st))
+            return st ? st : note_stream(plan, stream);
+    }
     for (int base = 0; base < p; base += seg) {
         const int ps = std::min(seg, p - base);
         if (unscheduled) {
@@ -1749,7 +1850,10 @@ mpk_status_t mpk_permute(mpk_plan_t plan, int to_plan, const double *in, double 
         e = hipMemcpyAsync(out, in, bytes, hipMemcpyDeviceToDevice, static_cast<hipStream_t>(stream));
         return e == hipSuccess ? MPK_OK : hip_fail(e, "hipMemcpyAsync");
     }
-    int rc = launch_permute(plan->d_perm.as<int32_t>(), plan->n, to_plan, in, out, nvec, nrhs, stream);
+    // gathered into place where that map is there, else scattered
+    const bool gather = to_plan || plan->drow;
+    int rc = launch_permute(to_plan || !gather ? plan->d_perm.as<int32_t>() : plan->drow, plan->n,
+                            !gather, in, out, nvec, nrhs, stream);
     return rc ? hip_fail((hipError_t)rc, "permute kernel launch") : MPK_OK;
 }
 

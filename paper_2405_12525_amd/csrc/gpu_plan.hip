@@ -689,11 +689,12 @@ struct DiaStep {
 // fn is called for each.  Returns the number of diagonals, or -1 where a row's
 // columns do not ascend strictly or there are more than max_slots.
 template <typename V, typename F>
-__device__ int32_t walk_slice(int64_t n, const int32_t *drow, const int64_t *soff,
+__device__ int32_t walk_slice(int64_t n, const int32_t *drow, const int32_t *cmap, const int64_t *soff,
                               const int32_t *rlen, const int32_t *scol, const V *sval, int64_t s,
                               int32_t max_slots, F &&fn) {
     const int lane = (int)(threadIdx.x & 63);
     const int64_t r0 = s * kDiaRows + 2 * lane;
+    auto column = [&](int64_t at) { return cmap ? cmap[scol[at]] : scol[at]; };
     int32_t L[2], e[2] = {0, 0}, d[2];   // length, cursor, offset of the next entry
     int64_t q[2];
     for (int i = 0; i < 2; ++i) {
@@ -704,7 +705,7 @@ __device__ int32_t walk_slice(int64_t n, const int32_t *drow, const int64_t *sof
             L[i] = rlen[pr];
             q[i] = soff[pr / kSellRows] + pr % kSellRows;
         }
-        d[i] = L[i] > 0 ? scol[q[i]] - (int32_t)(r0 + i) : INT32_MAX;   // |offset| < INT32_MAX
+        d[i] = L[i] > 0 ? column(q[i]) - (int32_t)(r0 + i) : INT32_MAX;   // |offset| < INT32_MAX
     }
     bool ok = true;
     int32_t step = 0;
@@ -728,7 +729,7 @@ __device__ int32_t walk_slice(int64_t n, const int32_t *drow, const int64_t *sof
         for (int i = 0; i < 2; ++i)
             if (d[i] == t.off) {
                 ++e[i];
-                d[i] = e[i] < L[i] ? scol[q[i] + (int64_t)e[i] * kSellRows] - (int32_t)(r0 + i)
+                d[i] = e[i] < L[i] ? column(q[i] + (int64_t)e[i] * kSellRows) - (int32_t)(r0 + i)
                                    : INT32_MAX;
                 if (d[i] <= t.off) ok = false;
             }
@@ -740,7 +741,7 @@ __device__ int32_t walk_slice(int64_t n, const int32_t *drow, const int64_t *sof
 // long as its longest row and list and values take no more bytes than its
 // entries in the sliced layout (col_bits: the width of the columns there).
 template <typename V>
-__global__ void dia_count_kernel(int64_t n, const int32_t *drow, const int64_t *soff,
+__global__ void dia_count_kernel(int64_t n, const int32_t *drow, const int32_t *cmap, const int64_t *soff,
                                  const int32_t *rlen, const int32_t *scol, const V *sval,
                                  int col_bits, DiaCount *out) {
     const int64_t n_sl = (n + kDiaRows - 1) / kDiaRows;
@@ -763,7 +764,7 @@ __global__ void dia_count_kernel(int64_t n, const int32_t *drow, const int64_t *
     }
     DiaCount c{0, 0, INT32_MAX, -INT32_MAX, {0, 0}, kHashBasis};
     uint64_t even = ~0ull, odd = ~0ull;
-    c.count = walk_slice<V>(n, drow, soff, rlen, scol, sval, s, 2 * width,
+    c.count = walk_slice<V>(n, drow, cmap, soff, rlen, scol, sval, s, 2 * width,
                             [&](const DiaStep<V> &t) {
                                 uint64_t h = c.hash;
                                 h = (h ^ (uint32_t)t.off) * kHashPrime;
@@ -796,7 +797,7 @@ __device__ __forceinline__ double value_of_bits(uint64_t bits) {
 }
 
 template <typename V>
-__global__ void dia_fill_kernel(int64_t n, const int32_t *drow, const int64_t *soff,
+__global__ void dia_fill_kernel(int64_t n, const int32_t *drow, const int32_t *cmap, const int64_t *soff,
                                 const int32_t *rlen, const int32_t *scol, const V *sval,
                                 const DiaSlice *slices, const uint8_t *emit, DiaGroup *groups,
                                 DiaRowMask *mask, V *vals) {
@@ -808,7 +809,7 @@ __global__ void dia_fill_kernel(int64_t n, const int32_t *drow, const int64_t *s
     const int lane = (int)(threadIdx.x & 63);
     const bool list = emit[s] != 0;
     int32_t vb = 0;
-    walk_slice<V>(n, drow, soff, rlen, scol, sval, s, ds.count, [&](const DiaStep<V> &t) {
+    walk_slice<V>(n, drow, cmap, soff, rlen, scol, sval, s, ds.count, [&](const DiaStep<V> &t) {
         if (list && lane == 0) {
             DiaGroup &g = groups[(int64_t)ds.first + t.step / 4];
             DiaRowMask &k = mask[(int64_t)ds.first + t.step / 4];
@@ -836,7 +837,7 @@ __global__ void dia_fill_kernel(int64_t n, const int32_t *drow, const int64_t *s
 
 // Every slice's own list against the pattern it was given.
 template <typename V>
-__global__ void dia_verify_kernel(int64_t n, const int32_t *drow, const int64_t *soff,
+__global__ void dia_verify_kernel(int64_t n, const int32_t *drow, const int32_t *cmap, const int64_t *soff,
                                   const int32_t *rlen, const int32_t *scol, const V *sval,
                                   const DiaSlice *slices, const DiaGroup *groups, int32_t *bad) {
     const int64_t n_sl = (n + kDiaRows - 1) / kDiaRows;
@@ -847,7 +848,7 @@ __global__ void dia_verify_kernel(int64_t n, const int32_t *drow, const int64_t 
     bool differs = false;
     int32_t vb = 0;
     const int32_t cnt = walk_slice<V>(
-        n, drow, soff, rlen, scol, sval, s, ds.count, [&](const DiaStep<V> &t) {
+        n, drow, cmap, soff, rlen, scol, sval, s, ds.count, [&](const DiaStep<V> &t) {
             const DiaGroup &g = groups[(int64_t)ds.first + t.step / 4];
             const int u = t.step & 3;
             differs |= g.off[u] != t.off || (g.vary >> u & 1) != (t.same ? 0 : 1) ||
@@ -864,7 +865,7 @@ __global__ void dia_verify_kernel(int64_t n, const int32_t *drow, const int64_t 
 inline dim3 wave_grid(int64_t n_sl) { return dim3((unsigned)((n_sl * 64 + kThreads - 1) / kThreads)); }
 
 template <typename V>
-int dia_fill(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t *rlen,
+int dia_fill(int64_t n, const int32_t *drow, const int32_t *cmap, const int64_t *soff, const int32_t *rlen,
              const int32_t *scol, const V *sval, const std::vector<DiaSlice> &slices,
              const std::vector<uint8_t> &emit, int64_t n_groups, DiaSlice *d_slices,
              uint8_t *d_emit, DiaGroup *groups, DiaRowMask *mask, V *vals, int *mismatch) {
@@ -878,9 +879,9 @@ int dia_fill(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t 
                        reinterpret_cast<int32_t *>(groups), words, 0);
     hipLaunchKernelGGL(fill_kernel, dim3(grid_for(words / 2)), dim3(kThreads), 0, 0,
                        reinterpret_cast<int32_t *>(mask), words / 2, 0);
-    hipLaunchKernelGGL(dia_fill_kernel<V>, wave_grid(n_sl), dim3(kThreads), 0, 0, n, drow, soff,
+    hipLaunchKernelGGL(dia_fill_kernel<V>, wave_grid(n_sl), dim3(kThreads), 0, 0, n, drow, cmap, soff,
                        rlen, scol, sval, d_slices, d_emit, groups, mask, vals);
-    hipLaunchKernelGGL(dia_verify_kernel<V>, wave_grid(n_sl), dim3(kThreads), 0, 0, n, drow, soff,
+    hipLaunchKernelGGL(dia_verify_kernel<V>, wave_grid(n_sl), dim3(kThreads), 0, 0, n, drow, cmap, soff,
                        rlen, scol, sval, d_slices, groups, bad);
     MPK_TRY(hipGetLastError());
     int32_t b = 0;
@@ -891,7 +892,7 @@ int dia_fill(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t 
 
 }  // namespace
 
-int gpu_dia_count(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t *rlen,
+int gpu_dia_count(int64_t n, const int32_t *drow, const int32_t *cmap, const int64_t *soff, const int32_t *rlen,
                   const int32_t *scol, const void *sval, int value_bits, int col_bits,
                   DiaCount *scratch, std::vector<DiaCount> &out) {
     const int64_t n_sl = (n + kDiaRows - 1) / kDiaRows;
@@ -899,17 +900,17 @@ int gpu_dia_count(int64_t n, const int32_t *drow, const int64_t *soff, const int
     if (n_sl == 0) return 0;
     if (value_bits == 32)
         hipLaunchKernelGGL(dia_count_kernel<float>, wave_grid(n_sl), dim3(kThreads), 0, 0, n, drow,
-                           soff, rlen, scol, static_cast<const float *>(sval), col_bits, scratch);
+                           cmap, soff, rlen, scol, static_cast<const float *>(sval), col_bits, scratch);
     else
         hipLaunchKernelGGL(dia_count_kernel<double>, wave_grid(n_sl), dim3(kThreads), 0, 0, n,
-                           drow, soff, rlen, scol, static_cast<const double *>(sval), col_bits,
+                           drow, cmap, soff, rlen, scol, static_cast<const double *>(sval), col_bits,
                            scratch);
     MPK_TRY(hipGetLastError());
     MPK_TRY(hipMemcpy(out.data(), scratch, (size_t)n_sl * sizeof(DiaCount), hipMemcpyDeviceToHost));
     return 0;
 }
 
-int gpu_dia_fill(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t *rlen,
+int gpu_dia_fill(int64_t n, const int32_t *drow, const int32_t *cmap, const int64_t *soff, const int32_t *rlen,
                  const int32_t *scol, const void *sval, int value_bits,
                  const std::vector<DiaSlice> &slices, const std::vector<uint8_t> &emit,
                  int64_t n_groups, DiaSlice *d_slices, uint8_t *d_emit, DiaGroup *groups,
@@ -917,10 +918,10 @@ int gpu_dia_fill(int64_t n, const int32_t *drow, const int64_t *soff, const int3
     *mismatch = 0;
     if (n == 0) return 0;
     if (value_bits == 32)
-        return dia_fill<float>(n, drow, soff, rlen, scol, static_cast<const float *>(sval), slices,
+        return dia_fill<float>(n, drow, cmap, soff, rlen, scol, static_cast<const float *>(sval), slices,
                                emit, n_groups, d_slices, d_emit, groups, mask,
                                static_cast<float *>(vals), mismatch);
-    return dia_fill<double>(n, drow, soff, rlen, scol, static_cast<const double *>(sval), slices,
+    return dia_fill<double>(n, drow, cmap, soff, rlen, scol, static_cast<const double *>(sval), slices,
                             emit, n_groups, d_slices, d_emit, groups, mask,
                             static_cast<double *>(vals), mismatch);
 }

@@ -1459,20 +1459,26 @@ __global__ void xcc_probe_kernel(int32_t *out) {
     if (threadIdx.x == 0) out[blockIdx.x] = xcc_id();
 }
 
-__global__ void permute_kernel(const int32_t *perm, int64_t n, int to_plan, const double *in,
-                               double *out, int nvec, int R) {
-    const int64_t total = n * (int64_t)R * nvec;
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total;
-         g += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t v = g / (n * R);
-        const int64_t rem = g - v * n * R;
-        const int64_t i = rem / R, r = rem - i * R;
-        const int64_t base = v * n * R;
-        if (to_plan)
-            out[base + i * R + r] = in[base + (int64_t)perm[i] * R + r];
-        else
-            out[base + (int64_t)perm[i] * R + r] = in[base + i * R + r];
+// Rows of nvec vectors from one numbering to the other: thread (li, r) of a
+// block moves column r of one row in every vector, four vectors in flight.
+template <bool SCATTER>
+__global__ __launch_bounds__(kBlock) void permute_kernel(const int32_t *src, int64_t n,
+                                                         const double *in, double *out, int nvec,
+                                                         int R) {
+    const int rows = kBlock / R, li = (int)threadIdx.x / R, r = (int)threadIdx.x - li * R;
+    const int64_t i = (int64_t)blockIdx.x * rows + li;
+    if (li >= rows || i >= n) return;
+    const int64_t here = i * R + r, there = (int64_t)src[i] * R + r;
+    const int64_t from = SCATTER ? here : there, to = SCATTER ? there : here, vec = n * R;
+    int v = 0;
+    for (; v + 4 <= nvec; v += 4) {
+        double t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] = in[(v + u) * vec + from];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) out[(v + u) * vec + to] = t[u];
     }
+    for (; v < nvec; ++v) out[v * vec + to] = in[v * vec + from];
 }
 
 // Complex states from the two weighted sums, on column pairs (column 2j the
@@ -1746,7 +1752,7 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
         io.fa = acc->fa;
         io.fb = acc->fb;
     }
-    if (dia_fits(m, R)) {
+    if (m.scol ? dia_fits(m, R) : dia_addressable(m, R)) {
         const int32_t per = R;   // passes of a slice, one wave each
         const int32_t units = (m.n + kDiaRows - 1) / kDiaRows * per;
         const int32_t blocks = (units + kBlock / kWave - 1) / (kBlock / kWave);
@@ -1784,6 +1790,7 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
                            by_run, keep);
         return (int)hipGetLastError();
     }
+    if (m.dsl && !m.scol) return (int)hipErrorInvalidValue;
     if (m.scol) {  // sliced layout: row blocks of 256 / R rows, grid-stride
         const int64_t nblk = ((int64_t)m.n + kBlock / R - 1) / (kBlock / R);
         const int64_t grid = std::min<int64_t>(nblk, kSpmvSellGrid);
@@ -1922,14 +1929,14 @@ int detect_xcds(int device) {
     return k;
 }
 
-int launch_permute(const int32_t *perm, int64_t n, int to_plan, const double *in, double *out,
+int launch_permute(const int32_t *src, int64_t n, bool scatter, const double *in, double *out,
                    int nvec, int R, void *stream) {
-    const int64_t total = n * (int64_t)R * nvec;
-    if (total == 0) return 0;
-    int64_t grid = (total + 255) / 256;
-    if (grid > 65536) grid = 65536;
-    hipLaunchKernelGGL(permute_kernel, dim3((unsigned)grid), dim3(256), 0, (hipStream_t)stream,
-                       perm, n, to_plan, in, out, nvec, R);
+    if (R < 1 || R > 16 || nvec < 0) return (int)hipErrorInvalidValue;
+    if (n == 0 || nvec == 0) return 0;
+    const int64_t rows = kBlock / R, grid = (n + rows - 1) / rows;
+    hipLaunchKernelGGL(scatter ? permute_kernel<true> : permute_kernel<false>,
+                       dim3((unsigned)grid), dim3(kBlock), 0, (hipStream_t)stream, src, n, in, out,
+                       nvec, R);
     return (int)hipGetLastError();
 }
 

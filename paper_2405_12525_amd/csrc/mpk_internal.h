@@ -105,8 +105,7 @@ int gpu_sell_fill(int64_t n, const int32_t *rowptr, const int32_t *col, const vo
                   int value_bits, const int64_t *soff, int64_t entries, int32_t *rlen,
                   int32_t *scol, int16_t *sdel, void *sval, int32_t *max_offset);
 // Diagonal slices, a second layout in slices of kDiaRows consecutive rows in
-// the numbering of the vectors (the caller's, or the plan's with
-// MPK_ORDER_PLAN).  Where the rows of a slice store their entries in ascending
+// the caller's numbering.  Where the rows of a slice store their entries in ascending
 // column order, the slice is a list of diagonals in that order.  A diagonal
 // holds the column offset its entries share (col = row + off), the rows that
 // have it (one bit each) and either the one value they all store or the place
@@ -153,12 +152,13 @@ struct DiaCount {
 // bytes longer), the values of every slice with count >= 0 into vals, the lists
 // of those with emit[s] != 0 into groups / mask, then *mismatch = 1 if any
 // slice's own list differs from the one slices[s].first names.  The matrix is
-// read from the sliced layout; drow[r] is row r's place there (null: r).
+// read from the sliced layout; drow[r] is row r's place there (null: r),
+// cmap[c] the caller's number of a column c there (null: c).
 // hipError_t results.
-int gpu_dia_count(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t *rlen,
+int gpu_dia_count(int64_t n, const int32_t *drow, const int32_t *cmap, const int64_t *soff, const int32_t *rlen,
                   const int32_t *scol, const void *sval, int value_bits, int col_bits,
                   DiaCount *scratch, std::vector<DiaCount> &out);
-int gpu_dia_fill(int64_t n, const int32_t *drow, const int64_t *soff, const int32_t *rlen,
+int gpu_dia_fill(int64_t n, const int32_t *drow, const int32_t *cmap, const int64_t *soff, const int32_t *rlen,
                  const int32_t *scol, const void *sval, int value_bits,
                  const std::vector<DiaSlice> &slices, const std::vector<uint8_t> &emit,
                  int64_t n_groups, DiaSlice *d_slices, uint8_t *d_emit, DiaGroup *groups,
@@ -224,7 +224,8 @@ struct DevMatrix {
     const int32_t *out_row;   // nullptr: output row = plan row
     int32_t n;
     int32_t value_bits;
-    // the sliced layout (null when the plan has none: too much padding)
+    // the sliced layout (null when the plan has none: too much padding; or, with
+    // dsl there, when its rows and columns are numbered otherwise than the vectors)
     const int64_t *soff;      // n_slices + 1 slot offsets
     const int32_t *rlen;      // n row lengths
     const int32_t *scol;      // slotted columns
@@ -237,7 +238,7 @@ struct DevMatrix {
     const DiaGroup *dgroup;   // the patterns' diagonals
     const DiaRowMask *dmask;  // their rows
     const void *dvals;        // blocks of kDiaRows per-row values (double or float)
-    const int32_t *drow;      // plan row of a vector's row (null: the same)
+    const int32_t *drow;      // plan row of a caller's row (null: the same)
     int32_t dgroups;          // groups of the longest list
     int32_t dreach;           // the farthest diagonal of a typical slice, in rows
     int64_t dval_bytes;       // of the per-row values
@@ -250,10 +251,13 @@ struct DevMatrix {
 // right-hand sides 7.9 against 6.8 us per power, 48^3 10.2 against 17.3 us;
 // lists of two groups are short enough (5-point 100^2 with 4: 3.6 against 4.0).
 // One right-hand side gains at every size, by its 16-byte loads.
+constexpr int64_t kDiaElements = 3 * 256 * 128;
+inline bool dia_addressable(const DevMatrix &m, int R) {
+    return m.dsl && (int64_t)m.n * R * (int64_t)sizeof(double) < ((int64_t)1 << 32);
+}
 inline bool dia_fits(const DevMatrix &m, int R) {
-    const int64_t elements = (int64_t)m.n * R;
-    return m.dsl && elements * (int64_t)sizeof(double) < ((int64_t)1 << 32) &&
-           (R == 1 || m.dgroups <= 2 || elements >= 3 * 256 * 128);
+    return dia_addressable(m, R) &&
+           (R == 1 || m.dgroups <= 2 || (int64_t)m.n * R >= kDiaElements);
 }
 
 // Whether all powers run in one launch, a workgroup per right-hand side with
@@ -426,7 +430,9 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
 // for the n rows of R (even) columns.
 int launch_combine_complex(const double *a, const double *b, int64_t n, int R, double *out,
                            void *stream);
-int launch_permute(const int32_t *perm, int64_t n, int to_plan, const double *in, double *out,
+// out[v][i] = in[v][src[i]] for the n rows of R columns of nvec vectors, or
+// (scatter) out[v][src[i]] = in[v][i].
+int launch_permute(const int32_t *src, int64_t n, bool scatter, const double *in, double *out,
                    int nvec, int R, void *stream);
 int launch_load_probe(const double *buf, int64_t n_doubles, int passes, int workgroups,
                       double *sink, void *stream);

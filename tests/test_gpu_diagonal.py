@@ -182,3 +182,66 @@ def test_vectors_past_the_caches(R):
     P.sync()
     assert torch.equal(Y, Yp) and torch.equal(Z, Zp)
     P.close()
+
+
+@pytest.mark.parametrize("side,R,bits", [(23, 1, 64), (24, 3, 32), (82, 1, 64), (84, 1, 32),
+                                         (83, 16, 64)])
+def test_plan_order_runs_on_diagonals_of_the_callers_order(side, R, bits):
+    """BFS plans in their own order: small ones as they are, large ones (2^19 rows,
+    2^23 elements) converted, on two streams at once, after which a captured and
+    a no-allocation run of the same shape are taken as before."""
+    A = w.stencil_3d27(side)
+    p = 5
+    x = w.uniform_vectors(A.n, R, side)
+    ref = oracle.powers(A, x, p, value_bits=bits)
+    co = mpk.chebyshev_coefficients(p)
+    cref = oracle.recur(A, x, *co, value_bits=bits)
+    P = mpk.Plan(A, value_bits=bits, order="plan")
+    xp = P.permute(torch.from_numpy(x).cuda(), to_plan=True)
+    assert np.array_equal(xp.cpu().numpy(), x[P.levels()[1]])
+    torch.cuda.synchronize()
+
+    def back(Y):
+        return P.permute(Y.reshape(p, A.n, R), to_plan=False).cpu().numpy()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    jobs = []
+    for i in range(6):
+        with torch.cuda.stream(streams[i % 2]):
+            Y = torch.empty((p, A.n, R), dtype=torch.float64, device="cuda")
+            (P.run if i < 4 else lambda x, p, Y, stream: P.run_recur(x, *co, Y=Y, stream=stream))(
+                xp, p, Y, stream=streams[i % 2])
+            jobs.append(Y)
+    P.sync()
+    torch.cuda.synchronize()
+    for i, Y in enumerate(jobs):
+        assert np.array_equal(back(Y), ref if i < 4 else cref), i
+    Y = torch.empty((p, A.n, R), dtype=torch.float64, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=streams[0]):
+        P.run(xp, p, Y=Y, stream=streams[0])
+    for _ in range(2):
+        Y.fill_(np.nan)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(back(Y), ref)
+    Y.fill_(np.nan)
+    P.run_noalloc(xp, p, Y)
+    assert np.array_equal(back(Y), ref)
+    assert np.array_equal(back(P.run_baseline(xp, p)), ref)
+    del g
+    P.close()
+
+
+@pytest.mark.parametrize("R", [1, 2, 3, 7, 16])
+@pytest.mark.parametrize("nvec", [1, 3, 4, 9])
+def test_permute_moves_every_row(R, nvec):
+    for A in (w.stencil_3d27(11), w.banded_random(3000, half_width=90)):   # with and without the inverse map
+        P = mpk.Plan(A, order="plan")
+        perm = P.levels()[1]
+        v = np.random.default_rng(R).standard_normal((nvec, A.n, R))
+        vd = torch.from_numpy(v).cuda()
+        q = P.permute(vd, to_plan=True)
+        assert np.array_equal(q.cpu().numpy(), v[:, perm])
+        assert np.array_equal(P.permute(q, to_plan=False).cpu().numpy(), v)
+        P.close()
