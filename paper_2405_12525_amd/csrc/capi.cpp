@@ -22,6 +22,11 @@ using namespace mpk;
 
 namespace {
 
+// Smallest matrix that gets windowed rows: four chunks for every compute unit,
+// so that a ring serves several (us per power, staged CSR rows against
+// windowed: band of 2^20 rows 105 and 78, 2^22 rows 400 and 274).
+constexpr int64_t kWinMinRows = 1 << 20;
+
 // Slices per workgroup of the p x SpMV kernel (consecutive slices pipeline).
 constexpr int32_t kSpmvSlicesPerWG = 2;
 
@@ -180,6 +185,8 @@ struct mpk_plan_s {
     DevBuf d_rowptr, d_col, d_val, d_outrow, d_perm;
     DevBuf d_soff, d_rlen, d_scol, d_sval;   // sliced layout (empty if not built)
     DevBuf d_sdel;                           // its 16-bit column offsets (if they fit)
+    DevBuf d_win;                            // windowed rows (empty if not built)
+    WinMatrix win{};
     DevBuf d_dcount, d_dia;                  // diagonal slices (empty if not built)
     const DiaSlice *dsl = nullptr;           // parts of d_dia
     const DiaGroup *dgroup = nullptr;
@@ -555,6 +562,122 @@ mpk_status_t build_dia(mpk_plan_t plan) {
     return MPK_OK;   // not reached: a list of its own always matches
 }
 
+// The windowed rows, where the plan has no diagonal slices, enough chunks that
+// a workgroup's ring serves several, and few entries outside the windows.
+mpk_status_t build_win(mpk_plan_t plan) {
+    const int64_t n = plan->n, nnz = plan->nnz;
+    if (plan->dsl || n < kWinMinRows || nnz < 4 * n) return MPK_OK;
+    // chunks within a level (short levels together): a row's columns lie in its
+    // own and the two adjacent levels
+    std::vector<int32_t> start;
+    const auto &lp = plan->lv.level_ptr;
+    int32_t from = 0;
+    auto cut = [&](int32_t to) {   // rows [from, to) in even chunks
+        const int32_t parts = (to - from + kWinRows - 1) / kWinRows;
+        for (int32_t i = 0; i < parts; ++i)
+            start.push_back(from + (int32_t)((int64_t)(to - from) * i / parts));
+        from = to;
+    };
+    for (size_t l = 0; l + 1 < lp.size(); ++l) {
+        if (lp[l + 1] - from > kWinRows && lp[l] > from) cut(lp[l]);
+        if (lp[l + 1] - from >= kWinRows / 2) cut(lp[l + 1]);
+    }
+    if (from < n) cut((int32_t)n);
+    const int64_t nch = (int64_t)start.size();
+    start.push_back((int32_t)n);
+    if (nch * kWinRows > 2 * n) return MPK_OK;
+    // windows: at least what the chunk reads, about kWinRows rows on from the
+    // one before (loaded while that one computes), at most what the ring holds
+    // from the first row that this or a later chunk still reads
+    std::vector<int32_t> end((size_t)nch), need((size_t)nch), first((size_t)nch),
+        cost((size_t)nch);
+    int64_t wide = 0;
+#pragma omp parallel for schedule(static) reduction(+ : wide)
+    for (int64_t c = 0; c < nch; ++c) {
+        int32_t lo = INT32_MAX, hi = 0;
+        for (int32_t r = start[c]; r < start[c + 1]; ++r) {
+            lo = std::min(lo, plan->row_lo[r]);
+            hi = std::max(hi, plan->row_hi[r] + 1);
+        }
+        wide += hi - lo > kWinRing;
+        cost[c] = hi - lo > kWinRing ? 8 : 1;
+        need[c] = hi;
+        first[c] = lo;
+    }
+    for (int64_t c = nch - 2; c >= 0; --c) first[c] = std::min(first[c], first[c + 1]);
+    if (8 * wide > nch) return MPK_OK;
+    int32_t h = 0;
+    for (int64_t c = 0; c < nch; ++c) {
+        const int64_t most = std::min<int64_t>(n, (int64_t)first[c] + kWinRing);
+        const int64_t want = std::max<int64_t>(need[c], (int64_t)h + kWinRows);
+        h = std::max<int32_t>(h, (int32_t)std::min(want, most));
+        end[c] = h;
+    }
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const size_t n_sl = (size_t)nch * (kWinRows / 64), end_b = up((size_t)(nch + 1) * 4),
+                 row_b = up((size_t)nch * kWinRows * 4), off_b = up((n_sl + 1) * 4);
+    DevBuf rows, inv;   // start | sorted rows
+    mpk_status_t st;
+    if ((st = rows.alloc(end_b + row_b))) return st;
+    hipError_t e = hipMemcpy(rows.ptr, start.data(), (size_t)(nch + 1) * 4, hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
+    std::vector<int32_t> width;
+    int rc = gpu_win_rows(rows.as<int32_t>(), nch, plan->d_rowptr.as<int32_t>(),
+                          reinterpret_cast<uint32_t *>(rows.as<char>() + end_b), width);
+    if (rc) return hip_fail((hipError_t)rc, "windowed rows");
+    std::vector<int32_t> off(n_sl + 1);
+    int64_t slots = 0;   // of 64 entries
+    for (size_t s = 0; s < n_sl; ++s) {
+        if (width[s] >= 1 << 22) return MPK_OK;   // does not fit beside the row
+        off[s] = (int32_t)slots;
+        slots += width[s];
+    }
+    off[n_sl] = (int32_t)slots;
+    if (slots * 64 > nnz + nnz / 4 + 65536) return MPK_OK;
+    slots += kWinPad;
+    // chunks to workgroups, one per compute unit.  A chunk whose columns do not
+    // fit the ring costs several others, and such chunks come together (2^22
+    // rows, 102 of 4430 chunks: counted as 2, 4, 8 and 16 others 388, 298, 274
+    // and 289 us per power; 641 by number)
+    constexpr int kParts = 256;
+    std::vector<int32_t> part(kParts + 1, (int32_t)nch);
+    int64_t total = 0, sum = 0;
+    for (int64_t c = 0; c < nch; ++c) total += cost[c];
+    for (int64_t c = 0, b = 0; c < nch; ++c) {
+        while (b < kParts && sum >= total * b / kParts) part[b++] = (int32_t)c;
+        sum += cost[c];
+    }
+    const size_t place_b = up((size_t)slots * 128), vb = (size_t)plan->value_bits / 8,
+                 part_b = up(part.size() * 4);
+    if ((st = plan->d_win.alloc(2 * end_b + row_b + off_b + part_b + place_b +
+                                (size_t)slots * 64 * vb)))
+        return st;
+    char *b = plan->d_win.as<char>(), *b_end = b + end_b + row_b, *b_off = b_end + end_b,
+         *b_part = b_off + off_b;
+    uint16_t *place = reinterpret_cast<uint16_t *>(b_part + part_b);
+    void *val = b_part + part_b + place_b;
+    plan->win = WinMatrix{reinterpret_cast<const int32_t *>(b),
+                          reinterpret_cast<const int32_t *>(b_end),
+                          reinterpret_cast<const uint32_t *>(b + end_b),
+                          reinterpret_cast<const int32_t *>(b_off),
+                          reinterpret_cast<const int32_t *>(b_part), place, val,
+                          (int32_t)nch, kParts, slots * 64 * (int64_t)(2 + vb)};
+    e = hipMemcpy(b, rows.ptr, end_b + row_b, hipMemcpyDeviceToDevice);
+    if (e == hipSuccess) e = hipMemcpy(b_end, end.data(), (size_t)nch * 4, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(b_off, off.data(), off.size() * 4, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(b_part, part.data(), part.size() * 4, hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
+    if (plan->d_outrow.ptr &&   // the stored columns are the caller's
+        (st = inv.upload(plan->lv.iperm.data(), (size_t)n * 4)))
+        return st;
+    int64_t far = 0;
+    rc = gpu_win_fill(slots, plan->d_rowptr.as<int32_t>(), plan->d_col.as<int32_t>(), plan->d_val.ptr,
+                      plan->value_bits, inv.as<int32_t>(), plan->win, place, val, &far);
+    if (rc) return hip_fail((hipError_t)rc, "windowed rows");
+    if (far > nnz / 32) plan->d_win.release();
+    return MPK_OK;
+}
+
 // Device-side state every device plan holds from the start (allocated
 // outside any capture): the zeroed failure words.
 mpk_status_t init_device_state(mpk_plan_t plan) {
@@ -782,7 +905,8 @@ mpk_status_t launch_powers(mpk_plan_t plan, const SliceSet *sl, const double *x,
         int rc = launch_spmv_power(m, sl->view(), sl->n_slices, kSpmvSlicesPerWG, in, prev, out,
                                    nrhs, recur ? 1 : 0, recur ? alpha[k - 1] : 1.0,
                                    recur ? beta[k - 1] : 0.0, recur ? gamma[k - 1] : 0.0,
-                                   poly ? &as : nullptr, stream_v);
+                                   poly ? &as : nullptr, plan->d_win.ptr ? &plan->win : nullptr,
+                                   stream_v);
         if (rc) return hip_fail((hipError_t)rc, "spmv kernel launch");
     }
     return MPK_OK;
@@ -872,7 +996,7 @@ bool run_converted(mpk_plan_t plan, const double *x, int p, int nrhs, const doub
         const double *prev = k == 1 ? nullptr : k == 2 ? xc : out;   // y_{k-2}, element by element
         rc = launch_spmv_power(m, DevSlices{}, 0, kSpmvSlicesPerWG, in, prev, out, nrhs,
                                recur ? 1 : 0, recur ? alpha[k - 1] : 1.0, recur ? beta[k - 1] : 0.0,
-                               recur ? gamma[k - 1] : 0.0, nullptr, stream);
+                               recur ? gamma[k - 1] : 0.0, nullptr, nullptr, stream);
         if (!rc)
             rc = launch_permute(plan->d_perm.as<int32_t>(), plan->n, false, out,
                                 Y + (size_t)(k - 1) * vec, 1, nrhs, stream);
@@ -1450,6 +1574,7 @@ mpk_status_t mpk_plan(const mpk_csr_t *A, const mpk_plan_opts_t *opts, mpk_plan_
     }
     if (!host_only && (st = build_sell(plan.get()))) return st;
     if (!host_only && (st = build_dia(plan.get()))) return st;
+    if (!host_only && (st = build_win(plan.get()))) return st;
     plan->plan_ms = now_ms() - t0;
     *out = plan.release();
     return MPK_OK;
@@ -1586,6 +1711,7 @@ mpk_status_t mpk_plan_device(const mpk_csr_t *A, const mpk_plan_opts_t *opts, mp
         plan->fingerprint = fingerprint(n, nnz, o, rph, sample);
         mpk_status_t st2 = build_sell(plan.get());
         if (!st2) st2 = build_dia(plan.get());
+        if (!st2) st2 = build_win(plan.get());
         if (st2) return st2;
     } catch (const std::bad_alloc &) {
         return fail(MPK_ENOMEM, "host allocation failed");

@@ -926,4 +926,107 @@ int gpu_dia_fill(int64_t n, const int32_t *drow, const int32_t *cmap, const int6
                             static_cast<double *>(vals), mismatch);
 }
 
+// ------------------------------------------------------------------ windowed rows
+
+namespace {
+
+// One block of kWinRows threads per chunk: its rows by falling length (a
+// counting sort; lengths from 255 on share a bin), and the longest row of each
+// of its 16 slices.
+__global__ __launch_bounds__(kWinRows) void win_rows_kernel(const int32_t *start,
+                                                            const int32_t *rowptr, uint32_t *row,
+                                                            int32_t *width) {
+    __shared__ int32_t bin[256], at[256];
+    const int t = (int)threadIdx.x;
+    const int32_t r = start[blockIdx.x] + t;
+    const int32_t L = r < start[blockIdx.x + 1] ? rowptr[r + 1] - rowptr[r] : 0;
+    const int b = 255 - min(L, 255);
+    if (t < 256) bin[t] = 0;
+    __syncthreads();
+    atomicAdd(&bin[b], 1);
+    __syncthreads();
+    if (t == 0) {
+        int32_t sum = 0;
+        for (int i = 0; i < 256; ++i) {
+            at[i] = sum;
+            sum += bin[i];
+        }
+    }
+    __syncthreads();
+    __shared__ uint32_t sorted[kWinRows];
+    sorted[atomicAdd(&at[b], 1)] = (uint32_t)t | (uint32_t)L << 10;
+    __syncthreads();
+    const uint32_t v = sorted[t];
+    row[(int64_t)blockIdx.x * kWinRows + t] = v;
+    int32_t w = (int32_t)(v >> 10);
+    for (int o = 32; o > 0; o >>= 1) w = max(w, __shfl_xor(w, o));
+    if ((t & 63) == 0) width[(int64_t)blockIdx.x * (kWinRows / 64) + t / 64] = w;
+}
+
+template <typename V>
+__global__ __launch_bounds__(kWinRows) void win_fill_kernel(const int32_t *rowptr,
+                                                            const int32_t *col, const V *val,
+                                                            const int32_t *inv, WinMatrix w,
+                                                            uint16_t *place, V *out,
+                                                            unsigned long long *n_far) {
+    const int64_t c = blockIdx.x;
+    const int t = (int)threadIdx.x;
+    const uint32_t info = w.row[c * kWinRows + t];
+    const int32_t L = (int32_t)(info >> 10), hi = w.end[c], lo = hi - kWinRing;
+    if (L == 0) return;
+    const int32_t e0 = rowptr[w.start[c] + (int32_t)(info & 1023)];
+    const int64_t base = (int64_t)w.off[c * (kWinRows / 64) + t / 64] * 64 + (t & 63);
+    unsigned long long far = 0;
+    for (int32_t j = 0; j < L; ++j) {
+        const int32_t pc = inv ? inv[col[e0 + j]] : col[e0 + j];
+        const bool in = pc >= lo && pc < hi;
+        far += !in;
+        place[base + (int64_t)j * 64] = in ? (uint16_t)(pc % kWinRing) : kWinFar;
+        out[base + (int64_t)j * 64] = val[e0 + j];
+    }
+    if (far) atomicAdd(n_far, far);
+}
+
+}  // namespace
+
+int gpu_win_rows(const int32_t *start, int64_t nch, const int32_t *rowptr, uint32_t *row,
+                 std::vector<int32_t> &width) {
+    width.assign((size_t)nch * (kWinRows / 64), 0);
+    if (nch == 0) return 0;
+    Scratch s;
+    int32_t *d;
+    MPK_TRY(s.get(&d, width.size()));
+    hipLaunchKernelGGL(win_rows_kernel, dim3((unsigned)nch), dim3(kWinRows), 0, 0, start,
+                       rowptr, row, d);
+    MPK_TRY(hipGetLastError());
+    MPK_TRY(hipMemcpy(width.data(), d, width.size() * 4, hipMemcpyDeviceToHost));
+    return 0;
+}
+
+int gpu_win_fill(int64_t slots, const int32_t *rowptr, const int32_t *col, const void *val,
+                 int value_bits, const int32_t *inv, const WinMatrix &w, uint16_t *place,
+                 void *out_val, int64_t *n_far) {
+    Scratch s;
+    unsigned long long *far, got = 0;
+    MPK_TRY(s.get(&far, 1));
+    hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(kThreads), 0, 0, reinterpret_cast<int32_t *>(far),
+                       (int64_t)2, 0);
+    // padding: place 0 (of values, whose products are not added, any will do)
+    hipLaunchKernelGGL(fill_kernel, dim3(grid_for(slots * 32)), dim3(kThreads), 0, 0,
+                       reinterpret_cast<int32_t *>(place), slots * 32, 0);
+    const dim3 grid((unsigned)w.n_chunks), block(kWinRows);
+    if (value_bits == 32)
+        hipLaunchKernelGGL(win_fill_kernel<float>, grid, block, 0, 0, rowptr, col,
+                           static_cast<const float *>(val), inv, w, place,
+                           static_cast<float *>(out_val), far);
+    else
+        hipLaunchKernelGGL(win_fill_kernel<double>, grid, block, 0, 0, rowptr, col,
+                           static_cast<const double *>(val), inv, w, place,
+                           static_cast<double *>(out_val), far);
+    MPK_TRY(hipGetLastError());
+    MPK_TRY(hipMemcpy(&got, far, 8, hipMemcpyDeviceToHost));
+    *n_far = (int64_t)got;
+    return 0;
+}
+
 }  // namespace mpk

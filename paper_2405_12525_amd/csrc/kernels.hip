@@ -25,6 +25,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "mpk_internal.h"
 
@@ -875,6 +876,107 @@ __global__ __launch_bounds__(kBlock) void spmv_sell_kernel(DevMatrix m, PowerIO 
     for (int32_t r0 = blockIdx.x * step; r0 < m.n; r0 += gridDim.x * step)
         run_sell<V, RC, false, ACC, SpmvSellU<RC>::value, RC == 1>(m, io, R, r0,
                                                                    min(m.n, r0 + step));
+}
+
+// One power from the windowed rows, one right-hand side: workgroup b takes the
+// chunks [part[b], part[b + 1]), its ring of input rows moving on with them.  Each
+// input row is gathered from memory about twice a power (a ring's first fill
+// included) instead of once per entry, and the entries gather from LDS.  Random
+// band, 2^22 rows, 67 M entries: 274 us per power against 400 from CSR rows
+// staged in LDS, whose gathers take a cache line each; 670 MB of entries at
+// 2.4 TB/s, bound by the chain of loads, sum and barriers of a chunk (13 us with
+// one workgroup per compute unit, which the ring allows).
+template <typename V, bool ACC>
+__global__ __launch_bounds__(kWinRows) void spmv_win_kernel(DevMatrix m, PowerIO io, WinMatrix w,
+                                                            int32_t keep) {
+    constexpr int U = kWinPad;
+    __shared__ double ring[kWinRing];
+    const int t = (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(t / kWave), lane = t & (kWave - 1);
+    const int32_t c0 = ld_const(w.part + blockIdx.x), c1 = ld_const(w.part + blockIdx.x + 1);
+    if (c0 >= c1) return;   // uniform
+    const int32_t *map = m.out_row;
+    // vector row of plan row r, -1 from `to` on
+    auto place_of = [&](int32_t r, int32_t to) { return r < to ? (map ? map[r] : r) : -1; };
+    // ring rows [from, to), eight loads of a thread in flight
+    auto fill = [&](int32_t from, int32_t to) {
+        for (int32_t r = from + t; r < to; r += 8 * kWinRows) {
+            int32_t g[8];
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) g[u] = place_of(r + u * kWinRows, to);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = g[u] >= 0 ? io.in[g[u]] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (g[u] >= 0) ring[(r + u * kWinRows) % kWinRing] = v[u];
+        }
+    };
+    int32_t h0 = ld_const(w.end + c0), h1 = c0 + 1 < c1 ? ld_const(w.end + c0 + 1) : h0;
+    fill(max(0, h0 - kWinRing), h0);
+    int32_t next_at = place_of(h0 + t, h1);
+    uint32_t info = w.row[(size_t)c0 * kWinRows + t];
+    __syncthreads();
+    for (int32_t c = c0; c < c1; ++c) {
+        // The first rows that the next window adds, whose places were loaded a
+        // chunk ago, and the same a chunk on.
+        const double next = next_at >= 0 ? io.in[next_at] : 0.0;
+        const int32_t h2 = c + 2 < c1 ? ld_const(w.end + c + 2) : h1;
+        next_at = place_of(h1 + t, h2);
+        const int32_t L = (int32_t)(info >> 10);
+        const int32_t prow = ld_const(w.start + c) + (int32_t)(info & 1023);
+        const bool there = prow < ld_const(w.start + c + 1);
+        const int32_t o = there ? (map ? map[prow] : prow) : 0;
+        const int32_t off = ld_const(w.off + c * (kWinRows / kWave) + wave);
+        const int32_t width = ld_const(w.off + c * (kWinRows / kWave) + wave + 1) - off;
+        if (c + 1 < c1) info = w.row[(size_t)(c + 1) * kWinRows + t];
+        const uint16_t *place = w.place + (size_t)off * kWave + lane;
+        const V *val = static_cast<const V *>(w.val) + (size_t)off * kWave + lane;
+        double s = 0.0;
+        auto sum = [&](auto nt) {
+            constexpr bool NT = decltype(nt)::value;
+            for (int32_t j = 0; j < width; j += U) {   // uniform
+                uint32_t q[U];
+                double a[U], x[U];
+                bool far = false;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {   // padded: places 0 past a row's end
+                    q[u] = load_matrix<NT>(place + (size_t)(j + u) * kWave);
+                    a[u] = static_cast<double>(load_matrix<NT>(val + (size_t)(j + u) * kWave));
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (j + u >= L) q[u] = 0;   // the next slice's
+                    far |= q[u] == kWinFar;
+                    x[u] = ring[q[u] == kWinFar ? 0 : q[u]];
+                }
+                if (__any(far)) {   // the columns, then the inputs, all at once
+                    const int32_t *col = m.col + m.rowptr[there ? prow : 0];
+                    int32_t g[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) g[u] = q[u] == kWinFar ? col[j + u] : 0;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const double y = io.in[g[u]];
+                        x[u] = q[u] == kWinFar ? y : x[u];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (j + u < L) s = s + a[u] * x[u];
+            }
+        };
+        if ((c & 15) >= keep) sum(std::true_type());   // uniform
+        else sum(std::false_type());
+        if (there) finish<false, ACC>(io, s, (size_t)o);
+        if (c + 1 == c1) break;   // uniform
+        __syncthreads();          // the window's oldest rows are no longer read
+        if (h0 + t < h1 && h0 + t >= h1 - kWinRing) ring[(h0 + t) % kWinRing] = next;
+        fill(max(h0 + kWinRows, h1 - kWinRing), h1);
+        __syncthreads();
+        h0 = h1;
+        h1 = h2;
+    }
 }
 
 // u / d = u * inv >> 32 with inv = ceil(2^32 / d), exact while u * d < 2^32.
@@ -1733,7 +1835,7 @@ int launch_status_copy(int32_t *status_word, int32_t *out, void *stream) {
 int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_t per,
                       const double *in, const double *inm1, double *out, int32_t R, int recur,
                       double alpha, double beta, double gamma, const AccStep *acc,
-                      void *stream) {
+                      const WinMatrix *win, void *stream) {
     if (R < 1 || R > 16 || per < 1) return (int)hipErrorInvalidValue;
     if (m.n == 0) return 0;
     PowerIO io{in, inm1, out, alpha, beta, gamma, recur};
@@ -1751,6 +1853,18 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
         io.wb0 = acc->wb[2];
         io.fa = acc->fa;
         io.fb = acc->fb;
+    }
+    if (win && R == 1) {
+        // one workgroup per compute unit, for the LDS; of every 16 chunks as many
+        // are cached as fit the memory-side cache (as with the diagonals)
+        const int32_t keep = (int32_t)std::min<int64_t>(
+            16, (kMallBytes - ((int64_t)64 << 20)) * 16 / std::max<int64_t>(1, win->bytes));
+        const dim3 grid((unsigned)win->n_parts);
+        auto fn = m.value_bits == 32
+                      ? (acc ? spmv_win_kernel<float, true> : spmv_win_kernel<float, false>)
+                      : (acc ? spmv_win_kernel<double, true> : spmv_win_kernel<double, false>);
+        hipLaunchKernelGGL(fn, grid, dim3(kWinRows), 0, (hipStream_t)stream, m, io, *win, keep);
+        return (int)hipGetLastError();
     }
     if (m.scol ? dia_fits(m, R) : dia_addressable(m, R)) {
         const int32_t per = R;   // passes of a slice, one wave each

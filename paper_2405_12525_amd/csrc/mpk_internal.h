@@ -163,6 +163,37 @@ int gpu_dia_fill(int64_t n, const int32_t *drow, const int32_t *cmap, const int6
                  const std::vector<DiaSlice> &slices, const std::vector<uint8_t> &emit,
                  int64_t n_groups, DiaSlice *d_slices, uint8_t *d_emit, DiaGroup *groups,
                  DiaRowMask *mask, void *vals, int *mismatch);
+// Windowed rows, a layout for one right-hand side of matrices whose plan order
+// keeps a row's columns near each other but not on shared diagonals: chunks
+// of at most kWinRows plan rows of one level, whose input a workgroup holds in
+// LDS, in a ring of the kWinRing plan rows before end[c] that moves on with the
+// chunks.  A chunk's
+// rows are sorted by length, slot-major in slices of 64, an entry's column
+// being its place in the ring (kWinFar: outside the window, read from memory).
+constexpr int kWinRows = 1024;
+constexpr int kWinRing = 19456;        // 152 of the 160 KB of LDS
+constexpr uint16_t kWinFar = 0xffff;
+constexpr int kWinPad = 8;             // slots that are loaded at a time
+struct WinMatrix {
+    const int32_t *start;     // n_chunks + 1: first plan row of each chunk
+    const int32_t *end;       // n_chunks: plan row after each chunk's window
+    const uint32_t *row;      // n_chunks * kWinRows: row of the chunk | length << 10
+    const int32_t *off;       // n_chunks * 16 + 1: first slot of each slice, in 64 entries
+    const int32_t *part;      // n_parts + 1: first chunk of each workgroup
+    const uint16_t *place;    // slots, kWinPad more than there are
+    const void *val;          // slots (double or float)
+    int32_t n_chunks, n_parts;
+    int64_t bytes;            // of place and val
+};
+// gpu_win_rows: the sorted rows and every slice's width (host copy).
+// gpu_win_fill: places and values, and the number of far entries.  rowptr / col /
+// val: the plan's CSR; inv (null: identity): plan row of a stored column.
+// hipError_t results.
+int gpu_win_rows(const int32_t *start, int64_t n_chunks, const int32_t *rowptr, uint32_t *row,
+                 std::vector<int32_t> &width);
+int gpu_win_fill(int64_t slots, const int32_t *rowptr, const int32_t *col, const void *val,
+                 int value_bits, const int32_t *inv, const WinMatrix &w, uint16_t *place,
+                 void *out_val, int64_t *n_far);
 // Levels from far[] (order_levels' rule): level 0 = row 0, level j+1 ends
 // just past the farthest neighbour of level j.
 Levels levels_from_far(int64_t n, const std::vector<int32_t> &far);
@@ -421,11 +452,11 @@ int launch_step(const DevMatrix &m, DevSlices sl, const int32_t *chunk_sptr,
 int launch_small(const DevMatrix &m, const SegArgs &a, const Coefs &cf, const AccCoefs *acc,
                  void *stream);
 // One power over all rows; workgroup b walks slices [b*per, (b+1)*per).
-// acc may be null (no weighted sums).
+// acc may be null (no weighted sums), win too (no windowed rows).
 int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_t per,
                       const double *in, const double *inm1, double *out, int32_t R, int recur,
                       double alpha, double beta, double gamma, const AccStep *acc,
-                      void *stream);
+                      const WinMatrix *win, void *stream);
 // out[i][2j] = a[i][2j] - b[i][2j+1], out[i][2j+1] = a[i][2j+1] + b[i][2j]
 // for the n rows of R (even) columns.
 int launch_combine_complex(const double *a, const double *b, int64_t n, int R, double *out,

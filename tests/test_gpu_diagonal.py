@@ -245,3 +245,51 @@ def test_permute_moves_every_row(R, nvec):
         assert np.array_equal(q.cpu().numpy(), v[:, perm])
         assert np.array_equal(P.permute(q, to_plan=False).cpu().numpy(), v)
         P.close()
+
+
+def near_band(n, seed, wide):
+    """Rows with one to 23 symmetric neighbours within 600 rows, shuffled within
+    windows of 3000 rows; wide: 40 rows also have one anywhere."""
+    g = np.random.default_rng(seed)
+    cnt = g.integers(0, 12, size=n)
+    src = np.repeat(np.arange(n, dtype=np.int64), cnt)
+    dst = src + g.integers(1, 601, size=src.size)
+    src, dst = src[dst < n], dst[dst < n]
+    if wide:
+        src = np.concatenate([src, g.integers(0, n, size=40)])
+        dst = np.concatenate([dst, g.integers(0, n, size=40)])
+    i = np.arange(n, dtype=np.int64)
+    new = np.argsort(np.argsort(i // 3000 + g.random(n)))
+    src, dst = new[src], new[dst]
+    key = np.unique(np.concatenate([src * n + dst, dst * n + src, i * n + i]))
+    rp = np.zeros(n + 1, np.int64)
+    rp[1:] = np.cumsum(np.bincount(key // n, minlength=n))
+    return w.CSR(n, rp.astype(np.int32), (key % n).astype(np.int32), g.standard_normal(key.size))
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("order,bits", [("original", 64), ("original", 32), ("plan", 64)])
+def test_windowed_rows(wide, order, bits):
+    """A shuffled band in BFS order, read through a ring of input rows in LDS by
+    one right-hand side: powers, recurrence and weighted sums give the oracle's
+    bits, also where some entries lie outside the windows."""
+    A = near_band((1 << 20) + 333, 5 + wide, wide)
+    x = w.uniform_vectors(A.n, 1, 9)
+    P = mpk.Plan(A, value_bits=bits, order=order)
+    xd = torch.from_numpy(x).cuda()
+    if order == "plan":
+        xd = P.permute(xd, to_plan=True)
+
+    def back(Y):
+        Y = Y.reshape(-1, A.n, 1)
+        return (P.permute(Y, to_plan=False) if order == "plan" else Y).cpu().numpy()
+    al, be, ga, wa, wb = mpk.cheb_time_coefficients(3, 0.4)
+    be = be + 0.5
+    assert np.array_equal(back(P.run(xd, 3)), oracle.powers(A, x, 3, value_bits=bits))
+    assert np.array_equal(back(P.run_baseline_recur(xd, al, be, ga)),
+                          oracle.recur(A, x, al, be, ga, value_bits=bits))
+    acc, _ = P.run_poly(xd, wa, wb, al, be, ga)
+    ra, rb = oracle.poly_sums(A, x, al, be, ga, wa, wb, value_bits=bits)
+    got = back(acc)
+    assert np.array_equal(got[0], ra) and np.array_equal(got[1], rb)
+    P.close()
