@@ -878,6 +878,57 @@ __global__ __launch_bounds__(kBlock) void spmv_sell_kernel(DevMatrix m, PowerIO 
                                                                    min(m.n, r0 + step));
 }
 
+// Few elements (few_elements): a wave per workgroup, a thread per (row,
+// right-hand side).  A power then takes as long as one thread's chain of loads,
+// so a batch holds a whole row of up to 8 slots, half a 27-point row otherwise,
+// and the waves spread over the compute units.
+template <typename V, int U>
+__device__ __forceinline__ double few_sum(const DevMatrix &m, const double *in, int32_t row,
+                                          int32_t L, uint32_t R, uint32_t rr) {
+    const int64_t base = m.soff[row / kSellRows] + row % kSellRows;
+    const V *sval = static_cast<const V *>(m.sval);
+    double s = 0.0;
+    for (int32_t j = 0; j < L; j += U) {
+        int32_t c[U];
+        double a[U], xv[U];
+        if (m.sdel) {  // row + offset, wrapped into [0, n)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t q = base + (int64_t)min(j + u, L - 1) * kSellRows;
+                int32_t cc = row + (int32_t)m.sdel[q];
+                cc += cc < 0 ? m.n : 0;
+                c[u] = cc >= m.n ? cc - m.n : cc;
+                a[u] = static_cast<double>(sval[q]);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t q = base + (int64_t)min(j + u, L - 1) * kSellRows;
+                c[u] = m.scol[q];
+                a[u] = static_cast<double>(sval[q]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) xv[u] = in[(size_t)c[u] * R + rr];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (j + u < L) s = s + a[u] * xv[u];
+    }
+    return s;
+}
+template <typename V, bool ACC>
+__global__ __launch_bounds__(kWave) void spmv_few_kernel(DevMatrix m, PowerIO io, int32_t R) {
+    const uint32_t e = blockIdx.x * kWave + threadIdx.x;
+    const int32_t row = (int32_t)(e / (uint32_t)R);
+    if (row >= m.n) return;
+    const uint32_t rr = e - (uint32_t)row * (uint32_t)R;
+    const int32_t L = m.rlen[row];
+    const int32_t o = m.out_row ? m.out_row[row] : row;
+    const double s = __any(L > 8) ? few_sum<V, 16>(m, io.in, row, L, R, rr)
+                                  : few_sum<V, 8>(m, io.in, row, L, R, rr);
+    finish<false, ACC>(io, s, (size_t)o * R + rr);
+}
+
 // One power from the windowed rows, one right-hand side: workgroup b takes the
 // chunks [part[b], part[b + 1]), its ring of input rows moving on with them.  Each
 // input row is gathered from memory about twice a power (a ring's first fill
@@ -1864,6 +1915,14 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
                       ? (acc ? spmv_win_kernel<float, true> : spmv_win_kernel<float, false>)
                       : (acc ? spmv_win_kernel<double, true> : spmv_win_kernel<double, false>);
         hipLaunchKernelGGL(fn, grid, dim3(kWinRows), 0, (hipStream_t)stream, m, io, *win, keep);
+        return (int)hipGetLastError();
+    }
+    if (few_elements(m, R)) {
+        const dim3 grid((unsigned)(((int64_t)m.n * R + kWave - 1) / kWave));
+        auto fn = m.value_bits == 32
+                      ? (acc ? spmv_few_kernel<float, true> : spmv_few_kernel<float, false>)
+                      : (acc ? spmv_few_kernel<double, true> : spmv_few_kernel<double, false>);
+        hipLaunchKernelGGL(fn, grid, dim3(kWave), 0, (hipStream_t)stream, m, io, R);
         return (int)hipGetLastError();
     }
     if (m.scol ? dia_fits(m, R) : dia_addressable(m, R)) {

@@ -291,6 +291,20 @@ inline bool dia_fits(const DevMatrix &m, int R) {
            (R == 1 || m.dgroups <= 2 || (int64_t)m.n * R >= kDiaElements);
 }
 
+// Whether a power is too small to fill the device, and takes as long as one
+// thread's chain of loads: a thread per element, its row in one or two batches.
+// us per power, diagonals (one right-hand side) or 4-slot batches against this,
+// rows in BFS order: 27-point 13^3 with 1, 2 and 8 right-hand sides 8.1, 6.7, 7.1
+// and 4.9, 4.9, 5.2; 20^3 with 8 7.5 and 6.3; Anderson 20^3 with 1 and 8 4.1, 4.2
+// and 3.4, 3.7; 27-point 32^3 with 2 7.3 and 6.6.  But diagonals win from 32^3
+// with 1 (5.8 and 6.1), 4-slot batches from 32^3 with 4 (6.5 and 7.5), and on
+// 5-point rows the diagonals, with two lists to read, at 200^2 (3.3 and 3.8).
+constexpr int64_t kFewElements = 1 << 16;
+inline bool few_elements(const DevMatrix &m, int R) {
+    return m.scol && !(m.dsl && m.dgroups <= 2) &&
+           (int64_t)m.n * R <= (R == 1 ? kFewElements * 3 / 8 : kFewElements);
+}
+
 // Whether all powers run in one launch, a workgroup per right-hand side with
 // its vectors in LDS: small matrices, where a power on one compute unit takes
 // less than a launch.  us for p = 16, launches against this: 5-point 32^2 48

@@ -293,3 +293,35 @@ def test_windowed_rows(wide, order, bits):
     got = back(acc)
     assert np.array_equal(got[0], ra) and np.array_equal(got[1], rb)
     P.close()
+
+
+@pytest.mark.parametrize("rem", [1, 127, 128, 129])
+@pytest.mark.parametrize("R", [1, 3, 16])
+def test_slice_height_where_every_power_fills_the_device(rem, R):
+    n = (1 << 15) + rem
+    check(banded(n, OFFS, rem, vary=(-3, 1, 40), drop=0.1), R, p=2)
+    check(banded(n, OFFS, rem, vary=(1,), drop=0.05, odd_rows=True), R, p=2, value_bits=32)
+
+
+@pytest.mark.parametrize("slots", [8, 9, 16, 17])
+@pytest.mark.parametrize("n,R", [(63, 1), (65, 5), (4096, 16), (4097, 16), (24576, 1)])
+def test_few_elements(slots, n, R):
+    """Rows without common offsets, about `slots` long, empty ones among them,
+    with sizes on both sides of the limits: the oracle's bits."""
+    g = np.random.default_rng(slots)
+    cnt = np.minimum(n, slots - (g.random(n) < 0.1))
+    cnt[::64] = 0
+    rp = np.zeros(n + 1, np.int32)
+    rp[1:] = np.cumsum(cnt)
+    A = w.CSR(n, rp, g.integers(0, n, size=rp[-1]).astype(np.int32), g.standard_normal(rp[-1]))
+    x = w.uniform_vectors(n, R, 4)
+    al, be, ga, wa, wb = mpk.cheb_time_coefficients(4, 0.6)
+    for bits, reorder in ((64, "none"), (32, "none"), (64, "bfs")):
+        P = mpk.Plan(A, value_bits=bits, reorder=reorder)
+        xd = torch.from_numpy(x).cuda()
+        for Y, ref in ((P.run_baseline(xd, 3), oracle.powers(A, x, 3, value_bits=bits)),
+                       (P.run_recur(xd, al, be, ga), oracle.recur(A, x, al, be, ga, value_bits=bits)),
+                       (P.run_baseline_poly(xd, wa, wb, al, be, ga)[0],
+                        np.stack(oracle.poly_sums(A, x, al, be, ga, wa, wb, value_bits=bits)))):
+            assert np.array_equal(Y.cpu().numpy().reshape(ref.shape), ref), (bits, reorder)
+        P.close()
