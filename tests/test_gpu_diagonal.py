@@ -301,6 +301,7 @@ def test_slice_height_where_every_power_fills_the_device(rem, R):
     n = (1 << 15) + rem
     check(banded(n, OFFS, rem, vary=(-3, 1, 40), drop=0.1), R, p=2)
     check(banded(n, OFFS, rem, vary=(1,), drop=0.05, odd_rows=True), R, p=2, value_bits=32)
+    check(banded(n, OFFS, rem, vary=OFFS, drop=0.19), R, p=2)   # near the limit on missing entries
 
 
 @pytest.mark.parametrize("slots", [8, 9, 16, 17])
