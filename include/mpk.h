@@ -146,7 +146,11 @@ typedef struct {
                                 matrices still fill the device; WAVE and POWERS
                                 cut chunks on multiples of 256 rows)            */
     int lag;                 /* WAVE, XCD: slack in chunks; 0 = from the budget
-                                and the running workgroups                      */
+                                and the running workgroups.  WAVE with lag,
+                                workgroups and skip_ahead 0 and no
+                                acquire_always (the default) leaves the order
+                                to the library: one launch per power where
+                                that is faster (mpk_run)                        */
     int workgroups;          /* persistent schedules: workgroups; 0 = as many as
                                 fit, at most two per compute unit (four with the
                                 sliced layout)                                  */
@@ -309,7 +313,9 @@ mpk_status_t mpk_plan_schedule_xcd(mpk_plan_t plan, int p, int32_t *dep_ptr, int
  * the chunks its rows read are done at the previous power (the Lp-diagram
  * dependency of Sec. "RACE Applied to the Matrix Power Kernel": level i at
  * power k needs levels i-1..i+1 at power k-1).  STEPS orders tasks by kernel
- * launches; the persistent schedules by per-chunk completion flags.
+ * launches; the persistent schedules by per-chunk completion flags.  With the
+ * default tuning the library runs the powers one after the other, a launch
+ * each (small matrices: one launch), where its layouts make that faster.
  * x: n*nrhs doubles; Y: p*n*nrhs doubles (device).  1 <= nrhs <= 16.
  * Errors: MPK_EINVAL (p < 1, NULL), MPK_EUNSUPPORTED (nrhs), MPK_ENODEVICE.
  */

@@ -3,7 +3,10 @@
 // persistent dataflow forms: in ticket order, with skip-ahead parking, and
 // with per-XCD queues), permutation, reset and a load-bandwidth probe.
 //
-// Every run kernel goes through one row routine.  For R < 4 right-hand sides
+// One launch per power, from the layout that suits the matrix: diagonal slices
+// (dia_pass), few elements (few_sum), windowed rows (spmv_win_kernel), the sliced
+// layout (run_sell) or CSR.  The level-blocked kernels use the last two.
+// CSR rows go through one row routine.  For R < 4 right-hand sides
 // (run_slices) the host cuts the rows into slices (consecutive rows whose
 // products fit one LDS staging buffer, at most 256 rows; a longer row is a
 // slice of its own) and a workgroup walks a range of slices:
