@@ -307,13 +307,17 @@ inline bool few_elements(const DevMatrix &m, int R) {
 
 // Whether all powers run in one launch, a workgroup per right-hand side with
 // its vectors in LDS: small matrices, where a power on one compute unit takes
-// less than a launch.  us for p = 16, launches against this: 5-point 32^2 48
-// and 24, 64^2 53 and 45; Anderson 12^3 65 and 42; 27-point 12^3 85 and 69; but
-// Anderson 16^3 66 and 66, 27-point 16^3 92 and 121, 5-point 90^2 55 and 79.
+// less than a launch.  us for p = 16, launches (from the third on few_elements)
+// against this: 5-point 32^2 48 and 24, 64^2 53 and 45; Anderson 12^3 52 and 41;
+// 27-point 12^3 76 and 68; but Anderson 16^3 52 and 66, 5-point 90^2 55 and 79.
+// Rows with most values of their own read them through one compute unit: general
+// 27-point 12^3 76 and 85, with 16 right-hand sides 85 and 97.
 constexpr int kSmallRows = 4096;
 inline bool dia_small(const DevMatrix &m) {
-    return m.dsl && (m.n <= kSmallRows / 2 ? m.dgroups <= 8
-                                           : m.n <= kSmallRows && m.dgroups <= 2);
+    return m.dsl && (m.n <= kSmallRows / 2
+                         ? m.dgroups <= 8 && (m.n <= kSmallRows / 4 ||
+                                              m.dval_bytes <= (int64_t)m.n * 32)
+                         : m.n <= kSmallRows && m.dgroups <= 2);
 }
 
 constexpr int kMaxSegPowers = 64;   // powers per kernel launch
