@@ -26,6 +26,9 @@ namespace {
 // so that a ring serves several (us per power, staged CSR rows against
 // windowed: band of 2^20 rows 105 and 78, 2^22 rows 400 and 274).
 constexpr int64_t kWinMinRows = 1 << 20;
+// Longest row of a matrix with windowed rows: its entries >> kWinRowShift
+// (build_win).
+constexpr int kWinRowShift = 17;
 
 // Slices per workgroup of the p x SpMV kernel (consecutive slices pipeline).
 constexpr int32_t kSpmvSlicesPerWG = 2;
@@ -563,10 +566,21 @@ mpk_status_t build_dia(mpk_plan_t plan) {
 }
 
 // The windowed rows, where the plan has no diagonal slices, enough chunks that
-// a workgroup's ring serves several, and few entries outside the windows.
+// a workgroup's ring serves several, few entries outside the windows and no
+// row long enough to hold the others up: one thread adds a row, 44 ns an
+// entry, and the gain over staged CSR rows, which take longer rows in parts,
+// is 0.5 to 1.9 us per power and million entries (near band of 1.1 M rows, 13 M
+// entries, us per power with a longest row of 23, 512, 1024 and 8192 entries:
+// 37, 60, 87 and 460, staged 43, 43, 43 and 336).
 mpk_status_t build_win(mpk_plan_t plan) {
     const int64_t n = plan->n, nnz = plan->nnz;
     if (plan->dsl || n < kWinMinRows || nnz < 4 * n) return MPK_OK;
+    int32_t longest = 0;
+    for (int64_t r = 0; r < n; ++r)
+        longest = std::max(longest, plan->rowptr[r + 1] - plan->rowptr[r]);
+    // (win_rows_kernel's row word holds lengths below 2^22)
+    static_assert((INT32_MAX >> kWinRowShift) < 1 << 22, "length field");
+    if (longest > nnz >> kWinRowShift) return MPK_OK;
     // chunks within a level (short levels together): a row's columns lie in its
     // own and the two adjacent levels
     std::vector<int32_t> start;
@@ -628,7 +642,6 @@ mpk_status_t build_win(mpk_plan_t plan) {
     std::vector<int32_t> off(n_sl + 1);
     int64_t slots = 0;   // of 64 entries
     for (size_t s = 0; s < n_sl; ++s) {
-        if (width[s] >= 1 << 22) return MPK_OK;   // does not fit beside the row
         off[s] = (int32_t)slots;
         slots += width[s];
     }

@@ -936,7 +936,7 @@ namespace {
 
 // One block of kWinRows threads per chunk: its rows by falling length (a
 // counting sort; lengths from 255 on share a bin), and the longest row of each
-// of its 16 slices.
+// of its 16 slices.  Lengths are below 2^22 (build_win).
 __global__ __launch_bounds__(kWinRows) void win_rows_kernel(const int32_t *start,
                                                             const int32_t *rowptr, uint32_t *row,
                                                             int32_t *width) {

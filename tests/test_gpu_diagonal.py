@@ -326,3 +326,25 @@ def test_few_elements(slots, n, R):
                         np.stack(oracle.poly_sums(A, x, al, be, ga, wa, wb, value_bits=bits)))):
             assert np.array_equal(Y.cpu().numpy().reshape(ref.shape), ref), (bits, reorder)
         P.close()
+
+
+@pytest.mark.parametrize("length", [500, (1 << 22) + 100])
+def test_band_with_a_long_row(length):
+    """One row of a wide irregular band is long (repeated columns, taken
+    literally), beyond 2^22 entries in the second case: every entry counts."""
+    A = near_band((1 << 20) + 333, 11, False)
+    g = np.random.default_rng(length)
+    row, e0, e1 = 4000, int(A.rowptr[4000]), int(A.rowptr[4001])
+    col = g.integers(row - 500, row + 501, size=length).astype(np.int32)
+    val = g.integers(-8, 9, size=length).astype(np.float64)
+    rp = A.rowptr.copy()
+    rp[row + 1:] += length - (e1 - e0)
+    A = w.CSR(A.n, rp, np.concatenate([A.col[:e0], col, A.col[e1:]]),
+              np.concatenate([A.val[:e0], val, A.val[e1:]]))
+    x = w.uniform_vectors(A.n, 1, 3)
+    P = mpk.Plan(A, reorder="none")
+    xd = torch.from_numpy(x).cuda()
+    ref = oracle.powers(A, x, 2)
+    assert np.array_equal(P.run_baseline(xd, 2).cpu().numpy().reshape(ref.shape), ref)
+    assert np.array_equal(P.run(xd, 2).cpu().numpy().reshape(ref.shape), ref)
+    P.close()
