@@ -30,9 +30,6 @@ constexpr int64_t kWinMinRows = 1 << 20;
 // (build_win).
 constexpr int kWinRowShift = 17;
 
-// Slices per workgroup of the p x SpMV kernel (consecutive slices pipeline).
-constexpr int32_t kSpmvSlicesPerWG = 2;
-
 thread_local std::string g_err;
 
 mpk_status_t fail(mpk_status_t st, const std::string &msg) {
@@ -198,6 +195,7 @@ struct mpk_plan_s {
     const int32_t *drow = nullptr;           // caller's row -> plan row (permuted plans)
     int32_t dgroups = 0, dreach = 0;
     int64_t dval_bytes = 0;
+    int32_t longest_row = 0;                 // entries (without the sliced layout)
     int64_t sell_entries = 0;
     std::map<int, std::unique_ptr<SliceSet>> spmv_slices;  // p x SpMV, by slice size
     // schedules and workspaces
@@ -574,13 +572,12 @@ mpk_status_t build_dia(mpk_plan_t plan) {
 // 37, 60, 87 and 460, staged 43, 43, 43 and 336).
 mpk_status_t build_win(mpk_plan_t plan) {
     const int64_t n = plan->n, nnz = plan->nnz;
-    if (plan->dsl || n < kWinMinRows || nnz < 4 * n) return MPK_OK;
-    int32_t longest = 0;
+    if (plan->d_scol.ptr ? plan->dsl || n < kWinMinRows : n == 0) return MPK_OK;
     for (int64_t r = 0; r < n; ++r)
-        longest = std::max(longest, plan->rowptr[r + 1] - plan->rowptr[r]);
+        plan->longest_row = std::max(plan->longest_row, plan->rowptr[r + 1] - plan->rowptr[r]);
     // (win_rows_kernel's row word holds lengths below 2^22)
     static_assert((INT32_MAX >> kWinRowShift) < 1 << 22, "length field");
-    if (longest > nnz >> kWinRowShift) return MPK_OK;
+    if (n < kWinMinRows || nnz < 4 * n || plan->longest_row > nnz >> kWinRowShift) return MPK_OK;
     // chunks within a level (short levels together): a row's columns lie in its
     // own and the two adjacent levels
     std::vector<int32_t> start;
@@ -915,7 +912,7 @@ mpk_status_t launch_powers(mpk_plan_t plan, const SliceSet *sl, const double *x,
             as.fa = poly->fa[(size_t)k];
             as.fb = poly->fb[(size_t)k];
         }
-        int rc = launch_spmv_power(m, sl->view(), sl->n_slices, kSpmvSlicesPerWG, in, prev, out,
+        int rc = launch_spmv_power(m, sl->view(), sl->n_slices, in, prev, out,
                                    nrhs, recur ? 1 : 0, recur ? alpha[k - 1] : 1.0,
                                    recur ? beta[k - 1] : 0.0, recur ? gamma[k - 1] : 0.0,
                                    poly ? &as : nullptr, plan->d_win.ptr ? &plan->win : nullptr,
@@ -926,21 +923,35 @@ mpk_status_t launch_powers(mpk_plan_t plan, const SliceSet *sl, const double *x,
 }
 
 // Tunings that leave the order of the work to the library (the default
-// schedule with no slack or workgroup count asked for): the powers then run
-// one launch each.  The persistent kernel pays a dependency check, a barrier
-// and write-through stores per task, and where rows are permuted an L2
-// invalidation too; with the slack that this tuning would give it, it was
-// slower wherever the plan has diagonal slices (5-point 64^2, p = 4: 33
-// against 18 us; 27-point 128^3, p = 8: 1067 against 156 us; Anderson 160^3
-// with 8 right-hand sides, p = 16: 7568 against 3023 us), its runs need that
-// invalidation (random band of 2^22 rows in BFS order, p = 6: 4245 against
-// 2405 us) or the rows are staged from CSR (the same band in its own order:
-// 3450 against 2230 us), and below 2^19 elements (5-point 300^2 in plan order, p
-// = 12: 100 against 63 us).  Elsewhere it stays (27-point 96^3 in plan order, p =
-// 8: 340 against 442 us).
+// schedule with no slack or workgroup count asked for): powers_in_turn says
+// where the powers then run one launch each.
 bool library_order(const mpk_tune_t &t) {
     return t.schedule == MPK_SCHED_WAVE && t.lag == 0 && t.workgroups == 0 && t.skip_ahead == 0 &&
            !t.acquire_always;
+}
+
+// Whether they do.  The persistent kernel pays a dependency check, a barrier and
+// write-through stores per task, and where rows are permuted an L2 invalidation
+// too (lines_can false); with the slack that this tuning would give it, it was
+// slower
+// * wherever the plan has diagonal slices (5-point 64^2, p = 4: 33 against 18 us;
+//   27-point 128^3, p = 8: 1067 against 156 us; Anderson 160^3 with 8 right-hand
+//   sides, p = 16: 7568 against 3023 us);
+// * on CSR rows: random bands of 8192, 60 k, 200 k and 800 k rows, p = 8, one
+//   right-hand side 66, 110, 231 and 681 against 42, 61, 182 and 544 us, four 130,
+//   169, 332 and 1465 against 42, 94, 249 and 895, sixteen (to 400 k) 339, 441, 850
+//   and 1525 against 48, 215, 630 and 1243.  But a power ends with its longest
+//   row, which one thread adds, and no other power's work goes on beside it: with
+//   a row of 6000 or 12000 entries among every 40000, 1.1 M rows, 1 to 4
+//   right-hand sides, the persistent kernel is up to 25% faster (natural order,
+//   four: 3% slower);
+// * in the sliced layout, where its runs need the invalidation and below 2^19
+//   elements (5-point 300^2 in plan order, p = 12: 100 against 63 us; 27-point
+//   96^3 in plan order, p = 8: 340 against 442 us).
+bool powers_in_turn(mpk_plan_t plan, const DevMatrix &m, int nrhs, bool lines_can) {
+    if (m.dsl) return true;
+    if (!m.scol) return plan->longest_row <= kSpmvKP * 256;
+    return !lines_can || plan->n * nrhs < (int64_t)1 << 19;
 }
 
 // Whether such a run can do without a schedule: whatever the right-hand sides
@@ -1007,7 +1018,7 @@ bool run_converted(mpk_plan_t plan, const double *x, int p, int nrhs, const doub
         const double *in = k == 1 ? xc : ring + (size_t)(k & 1) * vec;
         double *out = ring + (size_t)((k - 1) & 1) * vec;
         const double *prev = k == 1 ? nullptr : k == 2 ? xc : out;   // y_{k-2}, element by element
-        rc = launch_spmv_power(m, DevSlices{}, 0, kSpmvSlicesPerWG, in, prev, out, nrhs,
+        rc = launch_spmv_power(m, DevSlices{}, 0, in, prev, out, nrhs,
                                recur ? 1 : 0, recur ? alpha[k - 1] : 1.0, recur ? beta[k - 1] : 0.0,
                                recur ? gamma[k - 1] : 0.0, nullptr, nullptr, stream);
         if (!rc)
@@ -1100,8 +1111,8 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
                            ((size_t)plan->n * nrhs) % kLineRows == 0 &&
                            reinterpret_cast<uintptr_t>(Y) % 128 == 0;
     const int64_t elements = (int64_t)plan->n * nrhs;
-    const bool per_power = library_order(plan->tune) &&
-                           (m.dsl || !m.scol || !lines_can || elements < ((int64_t)1 << 19));
+    const bool per_power =
+        library_order(plan->tune) && powers_in_turn(plan, m, nrhs, lines_can);
     // Converting adds a launch and two passes over a vector per power.  us, one
     // launch per power in the plan's order against converted: 27-point 96^3, p =
     // 8: 442 and 149; Anderson 100^3, 16 right-hand sides, p = 10: 2001 and 1633;

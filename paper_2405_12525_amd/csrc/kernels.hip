@@ -327,6 +327,7 @@ struct SpmvSellU {
 };
 constexpr int64_t kMallBytes = (int64_t)256 << 20;   // memory-side cache
 constexpr int64_t kSpmvSellGrid = 4096;   // baseline workgroups per power (sliced layout)
+constexpr int64_t kSpmvRowsGrid = 1 << 22;   // 2^30 threads: a launch holds fewer than 2^32
 // DEL: the columns come from the 16-bit offsets (col = row + offset, wrapped
 // into [0, n)).  NT: the matrix is loaded non-temporally: by the one-launch-
 // per-power baseline with one right-hand side, which reads each line once per
@@ -860,15 +861,40 @@ __device__ __forceinline__ PowerIO power_io(const SegArgs &a, const Coefs &cf,
 
 // ------------------------------------------------------------------ baseline
 
-// One power: workgroup b walks slices [b*per, min((b+1)*per, n_slices)).
+// One power of R >= 4 right-hand sides from CSR rows: workgroup b takes row
+// blocks b, b + grid, ... of 256/R rows each.  A row is one thread's chain of
+// loads for each right-hand side, so the chains of a power have to run side by
+// side: a workgroup per block.  Random bands of 16 entries a row, us per power of
+// 16 right-hand sides at 8192 and 200 k rows with 1, 4 and 16 blocks per
+// workgroup: 5.9, 12, 39 and 79, 82, 99 (two slices of 4096 entries each, as
+// fewer right-hand sides take them: 75 and 116).
+template <typename V, int RC, bool ACC>
+__device__ __forceinline__ void rows_power(const DevMatrix &m, const PowerIO &io, int32_t R) {
+    const int32_t step = kBlock / (RC ? RC : R);
+    for (int64_t r0 = (int64_t)blockIdx.x * step; r0 < m.n; r0 += (int64_t)gridDim.x * step)
+        run_rows<V, RC, false, ACC>(m, io, R, (int32_t)r0, (int32_t)min((int64_t)m.n, r0 + step));
+}
+// Any count without an instantiation of its own (no LDS, which that of
+// spmv_power_kernel holds for three).
+template <typename V, bool ACC>
+__global__ __launch_bounds__(kBlock) void spmv_rows_kernel(DevMatrix m, PowerIO io, int32_t R) {
+    rows_power<V, 0, ACC>(m, io, R);
+}
+
+// One power from CSR rows: R < 4, workgroup b walks slices [b*per, min((b+1)*per,
+// n_slices)); else row blocks.
 template <typename V, int RC, bool ACC>
 __global__ __launch_bounds__(kBlock, 2) void spmv_power_kernel(DevMatrix m, PowerIO io, int32_t R,
                                                            DevSlices sl, int32_t n_slices,
                                                            int32_t per) {
-    __shared__ RowSmem<Staging<RC, kSpmvKP>::value> sm;
-    const int32_t s0 = blockIdx.x * per;
-    const int32_t s1 = min(n_slices, s0 + per);
-    run_slices<V, RC, Staging<RC, kSpmvKP>::value, false, ACC>(m, io, R, sl, s0, s1, sm);
+    if constexpr (RC >= 4) {
+        rows_power<V, RC, ACC>(m, io, R);
+    } else {
+        __shared__ RowSmem<Staging<RC, kSpmvKP>::value> sm;
+        const int32_t s0 = blockIdx.x * per;
+        const int32_t s1 = min(n_slices, s0 + per);
+        run_slices<V, RC, Staging<RC, kSpmvKP>::value, false, ACC>(m, io, R, sl, s0, s1, sm);
+    }
 }
 
 // One power in the sliced layout: workgroup b walks row blocks b, b + grid,
@@ -1790,6 +1816,10 @@ SpmvFn spmv_fn(int value_bits, int R, bool acc) {
     if (value_bits == 32) return acc ? t32().spmv_acc[i] : t32().spmv[i];
     return acc ? t64().spmv_acc[i] : t64().spmv[i];
 }
+SpmvSellFn spmv_rows_fn(int value_bits, bool acc) {
+    if (value_bits == 32) return acc ? spmv_rows_kernel<float, true> : spmv_rows_kernel<float, false>;
+    return acc ? spmv_rows_kernel<double, true> : spmv_rows_kernel<double, false>;
+}
 SpmvSellFn spmv_sell_fn(int value_bits, int R, bool acc) {
     const int i = r_index(R);
     if (value_bits == 32) return acc ? t32().spmv_sell_acc[i] : t32().spmv_sell[i];
@@ -1886,11 +1916,11 @@ int launch_status_copy(int32_t *status_word, int32_t *out, void *stream) {
     return (int)hipGetLastError();
 }
 
-int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_t per,
-                      const double *in, const double *inm1, double *out, int32_t R, int recur,
-                      double alpha, double beta, double gamma, const AccStep *acc,
-                      const WinMatrix *win, void *stream) {
-    if (R < 1 || R > 16 || per < 1) return (int)hipErrorInvalidValue;
+int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, const double *in,
+                      const double *inm1, double *out, int32_t R, int recur, double alpha,
+                      double beta, double gamma, const AccStep *acc, const WinMatrix *win,
+                      void *stream) {
+    if (R < 1 || R > 16) return (int)hipErrorInvalidValue;
     if (m.n == 0) return 0;
     PowerIO io{in, inm1, out, alpha, beta, gamma, recur};
     io.acc_a = io.acc_b = nullptr;
@@ -1974,8 +2004,27 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_
                            dim3(kBlock), 0, (hipStream_t)stream, m, io, R);
         return (int)hipGetLastError();
     }
-    if (n_slices == 0) return 0;
-    const int32_t grid = (n_slices + per - 1) / per;
+    int64_t grid;
+    int32_t per = 0;
+    if (R >= 4) {
+        const int32_t step = kBlock / R;
+        grid = std::min<int64_t>(((int64_t)m.n + step - 1) / step, kSpmvRowsGrid);
+        if (r_index(R) == 5) {
+            hipLaunchKernelGGL(spmv_rows_fn(m.value_bits, acc != nullptr), dim3((unsigned)grid),
+                               dim3(kBlock), 0, (hipStream_t)stream, m, io, R);
+            return (int)hipGetLastError();
+        }
+    } else {
+        if (n_slices == 0) return 0;
+        // A workgroup forms one slice's products while the next slice's entries
+        // load, but with fewer than eight such pairs for each compute unit more
+        // workgroups are worth more: bands of 8192, 60 k, 200 k and 400 k rows, us
+        // per power one by one and in pairs, one right-hand side 5.3, 7.7, 22.7,
+        // 38 and 8.5, 11, 22.8, 43, three 7.1, 14, 35, 63 and 10, 15, 35, 64;
+        // from 2.5 M rows 3% the other way.
+        per = n_slices < 4096 ? 1 : 2;
+        grid = (n_slices + per - 1) / per;
+    }
     hipLaunchKernelGGL(spmv_fn(m.value_bits, R, acc != nullptr), dim3((unsigned)grid), dim3(kBlock), 0,
                        (hipStream_t)stream, m, io, R, sl, n_slices, per);
     return (int)hipGetLastError();

@@ -469,12 +469,12 @@ int launch_step(const DevMatrix &m, DevSlices sl, const int32_t *chunk_sptr,
 // All powers of a segment, a workgroup per right-hand side (dia_small).
 int launch_small(const DevMatrix &m, const SegArgs &a, const Coefs &cf, const AccCoefs *acc,
                  void *stream);
-// One power over all rows; workgroup b walks slices [b*per, (b+1)*per).
+// One power over all rows (sl: the CSR rows' slices, for R < 4).
 // acc may be null (no weighted sums), win too (no windowed rows).
-int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, int32_t per,
-                      const double *in, const double *inm1, double *out, int32_t R, int recur,
-                      double alpha, double beta, double gamma, const AccStep *acc,
-                      const WinMatrix *win, void *stream);
+int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, const double *in,
+                      const double *inm1, double *out, int32_t R, int recur, double alpha,
+                      double beta, double gamma, const AccStep *acc, const WinMatrix *win,
+                      void *stream);
 // out[i][2j] = a[i][2j] - b[i][2j+1], out[i][2j+1] = a[i][2j+1] + b[i][2j]
 // for the n rows of R (even) columns.
 int launch_combine_complex(const double *a, const double *b, int64_t n, int R, double *out,
