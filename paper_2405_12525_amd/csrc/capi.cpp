@@ -945,13 +945,26 @@ bool library_order(const mpk_tune_t &t) {
 //   a row of 6000 or 12000 entries among every 40000, 1.1 M rows, 1 to 4
 //   right-hand sides, the persistent kernel is up to 25% faster (natural order,
 //   four: 3% slower);
-// * in the sliced layout, where its runs need the invalidation and below 2^19
-//   elements (5-point 300^2 in plan order, p = 12: 100 against 63 us; 27-point
-//   96^3 in plan order, p = 8: 340 against 442 us).
+// * in the sliced layout, where its runs need the invalidation and at small
+//   sizes.  Several right-hand sides: below 2^19 elements (p = 8, us: 27-point
+//   52^3 with 3 in plan order 264 against 143, 56^3, beyond, equal; 16 entries a row
+//   within +-2000, 250 k rows with 2 192 against 163).  One: with 32-bit columns
+//   and on lattices of at most two lists, too (random columns, 350 k and 450 k
+//   rows 396 and 470 against 360 and 423; 5-point 700^2 in plan order 94 against
+//   79).  With other lists and 16-bit offsets below 2^18 rows (27-point 60^3 and
+//   64^3 162 and 147 against 151 and 159; 8 entries within +-2000, 200 k and 300 k
+//   rows 0.95 and 1.32 of the persistent kernel's time), without any lists below
+//   3 M entries (16 within +-2000, 170 k and 200 k rows 0.91 and 1.15), of at most
+//   32 a row, whose two-slot batches are the time (33, 40 and 100, 30 k rows:
+//   1.04, 1.13 and 1.58), unless few_elements has its own.
 bool powers_in_turn(mpk_plan_t plan, const DevMatrix &m, int nrhs, bool lines_can) {
     if (m.dsl) return true;
     if (!m.scol) return plan->longest_row <= kSpmvKP * 256;
-    return !lines_can || plan->n * nrhs < (int64_t)1 << 19;
+    if (!lines_can || few_elements(m, nrhs)) return true;
+    if (nrhs > 1 || !m.sdel || (plan->dsl && plan->dgroups <= 2))
+        return plan->n * nrhs < (int64_t)1 << 19;
+    return plan->n < (int64_t)1 << 18 && plan->nnz <= 32 * plan->n &&
+           (plan->dsl || plan->nnz < (int64_t)3 << 20);
 }
 
 // Whether such a run can do without a schedule: whatever the right-hand sides
