@@ -989,6 +989,25 @@ mpk_status_t check_scratch(int32_t n_chunks) {
                                       " (raise tune.chunk_nnz)");
 }
 
+// Whether a run of a plan whose diagonal slices are in another numbering than its
+// vectors converts them (run_converted), which adds a launch and two passes over
+// a vector per power.  us, one launch per power in the plan's order against
+// converted: 27-point 96^3, p = 8: 442 and 149; Anderson 100^3, 16 right-hand
+// sides, p = 10: 2001 and 1633; but 5-point 300^2, p = 12: 63 and 88; general
+// 27-point 64^3, 8 right-hand sides, p = 8: 512 and 602.  Rows of about five entries
+// have the least to gain, and while the persistent kernel can do without
+// invalidations and finds the matrix in the memory-side cache it is faster there
+// (5-point, one right-hand side, p = 8, persistent against converted: 1040^2 150
+// and 169, 1500^2 264 and 309, 1700^2 335 and 381; but 1000^2 172 and 155, 1900^2
+// 463 and 437, 3000^2 1277 and 1011).
+bool worth_converting(mpk_plan_t plan, int nrhs, bool lines_can) {
+    if (!plan->dia_converts() || !dia_addressable(plan->matrix(true), nrhs) ||
+        plan->n * nrhs < (int64_t)1 << (nrhs == 1 ? 19 : 23))
+        return false;
+    return nrhs > 1 || !lines_can || plan->nnz > 6 * plan->n || plan->n < (int64_t)1 << 20 ||
+           plan->n > (int64_t)13 << 18;
+}
+
 // A run of a plan in its own order whose diagonal slices are in the caller's
 // numbering: x is converted once, the powers run one launch each on a ring of
 // two vectors in the caller's numbering, and each result is gathered into Y.
@@ -1126,14 +1145,8 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
     const int64_t elements = (int64_t)plan->n * nrhs;
     const bool per_power =
         library_order(plan->tune) && powers_in_turn(plan, m, nrhs, lines_can);
-    // Converting adds a launch and two passes over a vector per power.  us, one
-    // launch per power in the plan's order against converted: 27-point 96^3, p =
-    // 8: 442 and 149; Anderson 100^3, 16 right-hand sides, p = 10: 2001 and 1633;
-    // but 5-point 300^2, p = 12: 63 and 88; general 27-point 64^3, 8 right-hand
-    // sides, p = 8: 512 and 602.
-    if (library_order(plan->tune) && plan->dia_converts() && !poly && !na && !capturing &&
-        dia_addressable(plan->matrix(true), nrhs) &&
-        elements >= (int64_t)1 << (nrhs == 1 ? 19 : 23)) {
+    if (library_order(plan->tune) && !poly && !na && !capturing &&
+        worth_converting(plan, nrhs, lines_can)) {
         // what a capture or a no-allocation run of the same shape may ask for next
         for (int base = 0; base < p; base += seg)
             if ((st = prepare_segment(plan, std::min(seg, p - base), nrhs, wg_default, stream,
