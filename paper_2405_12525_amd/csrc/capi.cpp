@@ -967,11 +967,17 @@ bool powers_in_turn(mpk_plan_t plan, const DevMatrix &m, int nrhs, bool lines_ca
            (plan->dsl || plan->nnz < (int64_t)3 << 20);
 }
 
-// Whether such a run can do without a schedule: whatever the right-hand sides
-// and pointers, it takes one launch per power.
-bool never_scheduled(mpk_plan_t plan) {
-    return library_order(plan->tune) && plan->dsl && !plan->dia_converts() &&
-           plan->n / kChunkRows + 1 + kMaxQueues + 2 <= kScratchWords;
+// Whether such a run can do without a schedule: whatever the pointers, and for
+// every number of right-hand sides that shares its slice table, it takes one
+// launch per power.
+bool never_scheduled(mpk_plan_t plan, int nrhs) {
+    if (!library_order(plan->tune) ||
+        plan->n / kChunkRows + 1 + kMaxQueues + 2 > kScratchWords)
+        return false;
+    const DevMatrix m = plan->matrix();
+    const bool lines = !plan->d_outrow.ptr;
+    if (nrhs == 2 || nrhs == 3) return powers_in_turn(plan, m, nrhs, lines);
+    return powers_in_turn(plan, m, 1, lines) && powers_in_turn(plan, m, MPK_MAX_RHS, lines);
 }
 
 // The run of mpk_run_noalloc: the device's scratch workspace and the
@@ -1070,7 +1076,7 @@ bool run_converted(mpk_plan_t plan, const double *x, int p, int nrhs, const doub
 // capture on `stream` can take without an event query).
 mpk_status_t prepare_segment(mpk_plan_t plan, int ps, int nrhs, int wg_default, hipStream_t stream,
                              bool fresh) {
-    if (never_scheduled(plan)) {
+    if (never_scheduled(plan, nrhs)) {
         plan->shapes.insert({ps, slice_nnz(kTaskKP, nrhs)});
         return MPK_OK;
     }
@@ -1121,7 +1127,7 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
     const size_t stride = (size_t)plan->n * nrhs;
     const DevMatrix m = plan->matrix();
     const int seg = plan->tune.seg_powers > 0 ? plan->tune.seg_powers : kMaxSegPowers;
-    const bool unscheduled = never_scheduled(plan);
+    const bool unscheduled = never_scheduled(plan, nrhs);
     const int key = slice_nnz(kTaskKP, nrhs);
     if (na) {  // the caller's status word reports this run only: 0 until a wait fails
         for (int base = 0; base < p; base += seg)
@@ -1145,16 +1151,18 @@ mpk_status_t run_lb(mpk_plan_t plan, const double *x, int p, int nrhs, const dou
     const int64_t elements = (int64_t)plan->n * nrhs;
     const bool per_power =
         library_order(plan->tune) && powers_in_turn(plan, m, nrhs, lines_can);
-    if (library_order(plan->tune) && !poly && !na && !capturing &&
-        worth_converting(plan, nrhs, lines_can)) {
-        // what a capture or a no-allocation run of the same shape may ask for next
-        for (int base = 0; base < p; base += seg)
+    if (library_order(plan->tune) && !na && !capturing) {
+        // which form a run takes depends on Y's alignment, on capture and on poly:
+        // it leaves for a later capture or no-allocation run of its shape what
+        // either form asks for
+        const bool convert = !poly && worth_converting(plan, nrhs, lines_can);
+        for (int base = 0; base < p && (per_power || convert); base += seg)
             if ((st = prepare_segment(plan, std::min(seg, p - base), nrhs, wg_default, stream,
                                       false)))
                 return st;
         SliceSet *sl = nullptr;
         if ((st = spmv_slices(plan, nrhs, &sl))) return st;
-        if (run_converted(plan, x, p, nrhs, alpha, beta, gamma, Y, stream, st))
+        if (convert && run_converted(plan, x, p, nrhs, alpha, beta, gamma, Y, stream, st))
             return st ? st : note_stream(plan, stream);
     }
     for (int base = 0; base < p; base += seg) {

@@ -464,3 +464,60 @@ def test_default_run_of_a_five_point_plane_in_plan_order_is_no_slower_than_a_per
     default, persistent = times_of_default_and_persistent_runs(P, x, 8)
     assert default < 1.08 * persistent
     P.close()
+
+
+def shifted(shape, by):
+    """A vector array `by` doubles past a 128-byte boundary."""
+    n = int(np.prod(shape))
+    return torch.full((n + 16,), np.nan, dtype=torch.float64, device="cuda")[by:by + n].view(shape)
+
+
+@pytest.mark.parametrize("first", ["aligned", "unaligned", "sums"])
+@pytest.mark.parametrize("R", [1, 2, 4])
+def test_one_run_prepares_every_form_of_its_shape(first, R):
+    """A plan whose default runs take the persistent kernel or one launch per
+    power by the alignment of their output and by whether they sum: one run of
+    any kind, then no-allocation and captured runs of the others, from a fresh
+    plan each."""
+    A, p = w.anderson_3d(96), 4                    # 884,736 rows, a multiple of 16
+    x = w.uniform_vectors(A.n, R, 3)
+    xd = torch.from_numpy(x).cuda()
+    al, be, ga, wa, wb = mpk.cheb_time_coefficients(p, 0.5)
+    ref = mpk.Plan(A).run_baseline(xd, p)
+    ya, yu = shifted((p, A.n, R), 0), shifted((p, A.n, R), 1)
+    assert ya.data_ptr() % 128 == 0 and yu.data_ptr() % 128 == 8
+    sums = [torch.empty((2, A.n, R), dtype=torch.float64, device="cuda") for _ in range(4)]
+    P = mpk.Plan(A, reorder="bfs", order="plan")
+    xp = P.permute(xd, to_plan=True)
+    refp = P.permute(ref, to_plan=True)
+    P.run_baseline_poly(xp, wa, wb, al, be, ga, acc=sums[0], work=sums[1])
+    P.close()
+    calls = {"aligned": lambda P, **k: P.run(xp, p, ya, **k),
+             "unaligned": lambda P, **k: P.run(xp, p, yu, **k),
+             "sums": lambda P, **k: P.run_poly(xp, wa, wb, al, be, ga, acc=sums[2], work=sums[3], **k)}
+    outs = {"aligned": (ya, refp), "unaligned": (yu, refp), "sums": (sums[2], sums[0])}
+    for kind, (out, want) in outs.items():
+        if kind == first:
+            continue
+        P = mpk.Plan(A, reorder="bfs", order="plan")
+        if kind == "sums":                         # checks the pattern; another p
+            P.run_poly(xp, wa[:3], wb[:3], al[:2], be[:2], ga[:2], acc=sums[2], work=sums[3])
+        calls[first](P)
+        P.sync()
+        if kind != "sums":
+            out.fill_(np.nan)
+            P.run_noalloc(xp, p, out)
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(want.shape), want), (first, kind)
+        s = torch.cuda.Stream()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            calls[kind](P, stream=s)
+        for _ in range(2):
+            out.fill_(np.nan)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(want.shape), want), (first, kind)
+        del g
+        P.close()
