@@ -414,10 +414,13 @@ mpk_status_t mpk_run_baseline_poly(mpk_plan_t plan, const double *x, int p, int 
  * right-hand sides fetch from the plan's caches on first use: the
  * schedule of every segment (Sec. "RACE Applied to the Matrix Power
  * Kernel": the (level group, power) tasks of the Lp diagram), its row
- * slices for nrhs, an idle dependency workspace, and the p x SpMV slices
- * for nrhs.  No kernel runs.  Later calls of mpk_run, mpk_run_recur,
+ * slices for nrhs, an idle dependency workspace, three vectors of n*nrhs
+ * doubles where runs convert between row numberings (plan order, lattices: one
+ * set per run under way, at most four a plan; without the memory for them, runs
+ * do not convert), and the p x SpMV slices for nrhs.  No kernel runs.  Later calls of mpk_run, mpk_run_recur,
  * mpk_run_poly and the baseline forms with the same p and nrhs then do no
- * host planning and allocate nothing on the plan's side, so that their
+ * host planning and allocate nothing on the plan's side (beside an unfinished
+ * run on another stream: a workspace or vectors of their own), so that their
  * first call does not pay for it, and so that the caller may capture them
  * into its own HIP graph (stream capture) without a run beforehand; a
  * captured level-blocked run keeps its workspace until the plan is destroyed.

@@ -141,7 +141,7 @@ struct Workspace {
     }
 };
 
-// Vectors in the caller's numbering, for one run_converted at a time.
+// Three vectors in the caller's numbering, for one run_converted at a time.
 struct VecSpace {
     DevBuf buf;
     hipEvent_t ev = nullptr;   // after the last run that used it
@@ -205,6 +205,7 @@ struct mpk_plan_s {
     std::vector<std::unique_ptr<SchedEntry>> retired;
     std::vector<std::unique_ptr<Workspace>> pool;
     std::vector<std::unique_ptr<VecSpace>> vectors;   // of runs that convert
+    bool vectors_short = false;                       // memory for more was not there
     std::map<long long, int> wg_cache;
     std::set<std::pair<int, int>> shapes;         // (powers, slice size) run or prepared unscheduled
     std::map<hipStream_t, hipEvent_t> stream_ev;  // last run issued per stream
@@ -1014,40 +1015,52 @@ bool worth_converting(mpk_plan_t plan, int nrhs, bool lines_can) {
            plan->n > (int64_t)13 << 18;
 }
 
-// A run of a plan in its own order whose diagonal slices are in the caller's
-// numbering: x is converted once, the powers run one launch each on a ring of
-// two vectors in the caller's numbering, and each result is gathered into Y.
-// Returns false, nothing launched, where the vectors cannot be had: kVecSpaces
-// runs are under way, or memory is short (plan->mu held; not under capture).
-bool run_converted(mpk_plan_t plan, const double *x, int p, int nrhs, const double *alpha,
-                   const double *beta, const double *gamma, double *Y, hipStream_t stream,
-                   mpk_status_t &st) {
-    const size_t vec = (size_t)plan->n * nrhs, bytes = 3 * vec * sizeof(double);
+// Vectors that no unfinished run uses, for a converted run of nrhs right-hand
+// sides on `stream`: of the plan's own if there are, else one more (or, with
+// kVecSpaces there, an idle one made larger).  Null where every one is in use or
+// memory was short, once (plan->mu held; not under capture).
+VecSpace *get_vectors(mpk_plan_t plan, int nrhs, hipStream_t stream) {
+    const size_t bytes = 3 * (size_t)plan->n * nrhs * sizeof(double);
     auto idle = [&](const VecSpace &w) {
         return !w.recorded || hipEventQuery(w.ev) == hipSuccess;
     };
-    VecSpace *vs = nullptr;
     for (auto &w : plan->vectors)
-        if (!vs && w->buf.bytes >= bytes && (w->last_stream == stream || idle(*w))) vs = w.get();
-    if (!vs) {   // an idle one made larger, or one more
+        if (w->buf.bytes >= bytes && (w->last_stream == stream || idle(*w))) return w.get();
+    if (plan->vectors_short) return nullptr;
+    VecSpace *vs = nullptr;
+    if (plan->vectors.size() < kVecSpaces) {
+        auto w = std::make_unique<VecSpace>();
+        if (hipEventCreateWithFlags(&w->ev, hipEventDisableTiming) != hipSuccess) {
+            w->ev = nullptr;
+            return nullptr;
+        }
+        vs = w.get();
+        plan->vectors.push_back(std::move(w));
+    } else {
         for (auto &w : plan->vectors)
             if (!vs && idle(*w)) vs = w.get();
-        if (!vs) {
-            if (plan->vectors.size() >= kVecSpaces) return false;
-            auto w = std::make_unique<VecSpace>();
-            if (hipEventCreateWithFlags(&w->ev, hipEventDisableTiming) != hipSuccess) {
-                w->ev = nullptr;
-                return false;
-            }
-            vs = w.get();
-            plan->vectors.push_back(std::move(w));
-        }
-        vs->recorded = false;
-        if (vs->buf.alloc(bytes)) {
-            (void)hipGetLastError();
-            return false;
-        }
+        if (!vs) return nullptr;
     }
+    vs->recorded = false;
+    if (vs->buf.alloc(bytes)) {
+        (void)hipGetLastError();
+        plan->vectors_short = true;
+        return nullptr;
+    }
+    return vs;
+}
+
+// A run of a plan in its own order whose diagonal slices are in the caller's
+// numbering: x is converted once, the powers run one launch each on a ring of
+// two vectors in the caller's numbering, and each result is gathered into Y.
+// Returns false, nothing launched, where get_vectors has none (plan->mu held;
+// not under capture).
+bool run_converted(mpk_plan_t plan, const double *x, int p, int nrhs, const double *alpha,
+                   const double *beta, const double *gamma, double *Y, hipStream_t stream,
+                   mpk_status_t &st) {
+    const size_t vec = (size_t)plan->n * nrhs;
+    VecSpace *vs = get_vectors(plan, nrhs, stream);
+    if (!vs) return false;
     double *xc = vs->buf.as<double>(), *ring = xc + vec;
     const DevMatrix m = plan->matrix(true);
     const bool recur = alpha != nullptr;
@@ -1968,6 +1981,9 @@ mpk_status_t mpk_plan_prepare(mpk_plan_t plan, int p, int nrhs) {
         if ((st = prepare_segment(plan, std::min(seg, p - base), nrhs, wg_default, nullptr, false)))
             return st;
     }
+    // (without its own vectors a run takes them in the plan's order)
+    if (library_order(plan->tune) && worth_converting(plan, nrhs, false))
+        (void)get_vectors(plan, nrhs, nullptr);
     SliceSet *sl = nullptr;
     return spmv_slices(plan, nrhs, &sl);
 }

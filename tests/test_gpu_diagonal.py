@@ -521,3 +521,68 @@ def test_one_run_prepares_every_form_of_its_shape(first, R):
             assert torch.equal(out.view(want.shape), want), (first, kind)
         del g
         P.close()
+
+
+@pytest.mark.parametrize("counts", [(1,), (1, 9), (16, 1)])
+def test_prepared_runs_that_convert_allocate_nothing(counts):
+    """A plan-order lattice whose runs use vectors in the caller's numbering:
+    they are there once prepare was called with the counts that run."""
+    A, p = w.stencil_3d27(101), 3
+    mpk.use_torch_allocator(True)
+    try:
+        P = mpk.Plan(A, order="plan")
+        for R in counts:
+            P.prepare(p, R)
+        allocs = mpk.allocator_stats["allocs"]
+        for R in counts:
+            x = torch.from_numpy(w.uniform_vectors(A.n, R, R)).cuda()
+            Y = P.run(x, p)
+            P.sync()
+            assert mpk.allocator_stats["allocs"] == allocs, R
+            P2 = P.run_baseline(x, p)
+            P.sync()
+            assert torch.equal(Y, P2)
+        P.close()
+    finally:
+        mpk.use_torch_allocator(False)
+
+
+def test_conversion_without_memory_for_its_vectors():
+    """Where the vectors cannot be had, a run takes its own order, and asks for
+    them once."""
+    import ctypes
+    A, p = w.stencil_3d27(84), 3
+    x = torch.from_numpy(w.uniform_vectors(A.n, 1, 1)).cuda()
+    lib, limit, asked = mpk.lib(), [None], [0]
+    pool = {}
+
+    def alloc(nbytes, _):
+        if limit[0] is not None and nbytes > limit[0]:
+            asked[0] += 1
+            return 0
+        t = torch.empty(max(nbytes, 1), dtype=torch.uint8, device="cuda")
+        pool[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def free(p, _):
+        torch.cuda.synchronize()
+        pool.pop(p, None)
+    fa = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)(alloc)
+    ff = ctypes.CFUNCTYPE(None, ctypes.c_void_p, ctypes.c_void_p)(free)
+    assert lib.mpk_set_allocator(ctypes.cast(fa, ctypes.c_void_p), ctypes.cast(ff, ctypes.c_void_p), None) == 0
+    try:
+        P = mpk.Plan(A, order="plan")
+        limit[0] = A.n * 8
+        P.prepare(p, 1)
+        outs = [P.run(x, p) for _ in range(3)]
+        P.sync()
+        assert asked[0] == 1
+        limit[0] = None
+        Q = mpk.Plan(A, order="plan")
+        ref = Q.run(x, p)
+        Q.sync()
+        assert all(torch.equal(Y, ref) for Y in outs)
+        Q.close()
+        P.close()
+    finally:
+        lib.mpk_set_allocator(None, None, None)
