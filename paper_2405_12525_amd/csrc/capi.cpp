@@ -455,6 +455,11 @@ mpk_status_t build_sell(mpk_plan_t plan) {
     return MPK_OK;
 }
 
+mpk_status_t layout_fail(hipError_t e, const char *what) {
+    const mpk_status_t st = hip_fail(e, what);
+    return e == hipErrorOutOfMemory ? MPK_ENOMEM : st;
+}
+
 // The diagonal slices of the plan's matrix, where at least half of its slices
 // have one.  Slices with equal lists share one: a box stencil has a few dozen
 // lists however many rows it has.
@@ -481,7 +486,7 @@ mpk_status_t build_dia(mpk_plan_t plan) {
     std::vector<DiaCount> cnt;
     int rc = gpu_dia_count(plan->n, drow, cmap, soff, rlen, scol, plan->d_sval.ptr, plan->value_bits,
                            plan->d_sdel.ptr ? 16 : 32, reinterpret_cast<DiaCount *>(c0 + row_b), cnt);
-    if (rc) return hip_fail((hipError_t)rc, "diagonal slices");
+    if (rc) return layout_fail((hipError_t)rc, "diagonal slices");
     size_t taken = 0;
     for (const DiaCount &c : cnt) taken += c.count >= 0;
     // (the sliced layout cannot stand in for a slice in another numbering)
@@ -541,7 +546,7 @@ mpk_status_t build_dia(mpk_plan_t plan) {
         int differ = 0;
         rc = gpu_dia_fill(plan->n, drow, cmap, soff, rlen, scol, plan->d_sval.ptr, plan->value_bits, sl,
                           emit, groups, dsl, demit, dgroup, dmask, dvals, &differ);
-        if (rc) return hip_fail((hipError_t)rc, "diagonal slices");
+        if (rc) return layout_fail((hipError_t)rc, "diagonal slices");
         if (!differ) {
             plan->dsl = dsl;
             plan->dgroup = dgroup;
@@ -636,7 +641,7 @@ mpk_status_t build_win(mpk_plan_t plan) {
     std::vector<int32_t> width;
     int rc = gpu_win_rows(rows.as<int32_t>(), nch, plan->d_rowptr.as<int32_t>(),
                           reinterpret_cast<uint32_t *>(rows.as<char>() + end_b), width);
-    if (rc) return hip_fail((hipError_t)rc, "windowed rows");
+    if (rc) return layout_fail((hipError_t)rc, "windowed rows");
     std::vector<int32_t> off(n_sl + 1);
     int64_t slots = 0;   // of 64 entries
     for (size_t s = 0; s < n_sl; ++s) {
@@ -684,9 +689,37 @@ mpk_status_t build_win(mpk_plan_t plan) {
     int64_t far = 0;
     rc = gpu_win_fill(slots, plan->d_rowptr.as<int32_t>(), plan->d_col.as<int32_t>(), plan->d_val.ptr,
                       plan->value_bits, inv.as<int32_t>(), plan->win, place, val, &far);
-    if (rc) return hip_fail((hipError_t)rc, "windowed rows");
+    if (rc) return layout_fail((hipError_t)rc, "windowed rows");
     if (far > nnz / 32) plan->d_win.release();
     return MPK_OK;
+}
+
+// The layouts that a plan can do without: where memory is short for one, on the
+// device or the host, the plan runs on the layouts that it has.
+mpk_status_t build_optional(mpk_plan_t plan, mpk_status_t (*build)(mpk_plan_t),
+                            void (*drop)(mpk_plan_t)) {
+    mpk_status_t st;
+    try {
+        st = build(plan);
+    } catch (const std::bad_alloc &) {
+        st = MPK_ENOMEM;
+    }
+    if (st != MPK_ENOMEM) return st;
+    (void)hipGetLastError();
+    drop(plan);
+    return MPK_OK;
+}
+mpk_status_t build_layouts(mpk_plan_t plan) {
+    mpk_status_t st = build_sell(plan);
+    if (!st)
+        st = build_optional(plan, build_dia, [](mpk_plan_t p) {
+            p->d_dcount.release();
+            p->d_dia.release();
+            p->dsl = nullptr;
+            p->drow = nullptr;
+        });
+    if (!st) st = build_optional(plan, build_win, [](mpk_plan_t p) { p->d_win.release(); });
+    return st;
 }
 
 // Device-side state every device plan holds from the start (allocated
@@ -1632,20 +1665,16 @@ mpk_status_t mpk_plan(const mpk_csr_t *A, const mpk_plan_opts_t *opts, mpk_plan_
         } else if (!gpu_levels && !pc.identity) {
             plan->col.swap(pc.col);
         }
+        const int64_t step = fingerprint_step(A->nnz);
+        std::vector<int32_t> sample;
+        for (int64_t e2 = 0; e2 < A->nnz; e2 += step) sample.push_back(A->col[e2]);
+        plan->fingerprint = fingerprint(A->n, A->nnz, o, A->rowptr, sample);
+        if (!host_only && (st = build_layouts(plan.get()))) return st;
     } catch (const std::bad_alloc &) {
         return fail(MPK_ENOMEM, "host allocation failed");
     } catch (const std::exception &ex) {
         return fail(MPK_EINVAL, ex.what());
     }
-    {
-        const int64_t step = fingerprint_step(A->nnz);
-        std::vector<int32_t> sample;
-        for (int64_t e2 = 0; e2 < A->nnz; e2 += step) sample.push_back(A->col[e2]);
-        plan->fingerprint = fingerprint(A->n, A->nnz, o, A->rowptr, sample);
-    }
-    if (!host_only && (st = build_sell(plan.get()))) return st;
-    if (!host_only && (st = build_dia(plan.get()))) return st;
-    if (!host_only && (st = build_win(plan.get()))) return st;
     plan->plan_ms = now_ms() - t0;
     *out = plan.release();
     return MPK_OK;
@@ -1780,9 +1809,7 @@ mpk_status_t mpk_plan_device(const mpk_csr_t *A, const mpk_plan_opts_t *opts, mp
             rph = rp0.data();
         }
         plan->fingerprint = fingerprint(n, nnz, o, rph, sample);
-        mpk_status_t st2 = build_sell(plan.get());
-        if (!st2) st2 = build_dia(plan.get());
-        if (!st2) st2 = build_win(plan.get());
+        mpk_status_t st2 = build_layouts(plan.get());
         if (st2) return st2;
     } catch (const std::bad_alloc &) {
         return fail(MPK_ENOMEM, "host allocation failed");

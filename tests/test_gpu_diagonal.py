@@ -5,6 +5,10 @@ the sliced layout because a row is unsorted or repeats a column).  One launch
 per power and the persistent kernels give the oracle's bits for every count of
 right-hand sides, for row counts around the slice height, in both row
 orders, with infinities and NaN next to rows that do not read them."""
+import contextlib
+import ctypes
+import types
+
 import numpy as np
 import pytest
 
@@ -547,18 +551,15 @@ def test_prepared_runs_that_convert_allocate_nothing(counts):
         mpk.use_torch_allocator(False)
 
 
-def test_conversion_without_memory_for_its_vectors():
-    """Where the vectors cannot be had, a run takes its own order, and asks for
-    them once."""
-    import ctypes
-    A, p = w.stencil_3d27(84), 3
-    x = torch.from_numpy(w.uniform_vectors(A.n, 1, 1)).cuda()
-    lib, limit, asked = mpk.lib(), [None], [0]
-    pool = {}
+@contextlib.contextmanager
+def allocations(refuse):
+    """Every allocation of the library through torch, numbered from 0; refuse(i,
+    bytes): it gets none.  Yields the list of sizes asked for."""
+    lib, pool, sizes = mpk.lib(), {}, []
 
     def alloc(nbytes, _):
-        if limit[0] is not None and nbytes > limit[0]:
-            asked[0] += 1
+        sizes.append(nbytes)
+        if refuse(len(sizes) - 1, nbytes):
             return 0
         t = torch.empty(max(nbytes, 1), dtype=torch.uint8, device="cuda")
         pool[t.data_ptr()] = t
@@ -569,14 +570,28 @@ def test_conversion_without_memory_for_its_vectors():
         pool.pop(p, None)
     fa = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)(alloc)
     ff = ctypes.CFUNCTYPE(None, ctypes.c_void_p, ctypes.c_void_p)(free)
-    assert lib.mpk_set_allocator(ctypes.cast(fa, ctypes.c_void_p), ctypes.cast(ff, ctypes.c_void_p), None) == 0
+    assert lib.mpk_set_allocator(ctypes.cast(fa, ctypes.c_void_p),
+                                 ctypes.cast(ff, ctypes.c_void_p), None) == 0
     try:
+        yield sizes
+    finally:
+        lib.mpk_set_allocator(None, None, None)
+
+
+def test_conversion_without_memory_for_its_vectors():
+    """Where the vectors cannot be had, a run takes its own order, and asks for
+    them once."""
+    A, p = w.stencil_3d27(84), 3
+    x = torch.from_numpy(w.uniform_vectors(A.n, 1, 1)).cuda()
+    limit = [None]
+    with allocations(lambda i, b: limit[0] is not None and b > limit[0]) as sizes:
         P = mpk.Plan(A, order="plan")
         limit[0] = A.n * 8
         P.prepare(p, 1)
+        before = sum(b > limit[0] for b in sizes)
         outs = [P.run(x, p) for _ in range(3)]
         P.sync()
-        assert asked[0] == 1
+        assert sum(b > limit[0] for b in sizes) == before
         limit[0] = None
         Q = mpk.Plan(A, order="plan")
         ref = Q.run(x, p)
@@ -584,5 +599,37 @@ def test_conversion_without_memory_for_its_vectors():
         assert all(torch.equal(Y, ref) for Y in outs)
         Q.close()
         P.close()
-    finally:
-        lib.mpk_set_allocator(None, None, None)
+
+
+@pytest.mark.parametrize("matrix,reorder,optional", [("diagonals", "none", 2), ("diagonals", "bfs", 2),
+                                                     ("windows", "none", 2), ("windows", "bfs", 3)])
+@pytest.mark.parametrize("device", [False, True])
+def test_plans_do_without_layouts_that_memory_is_short_for(matrix, reorder, optional, device):
+    """Each allocation of a plan refused in turn: those of the diagonal slices or
+    the windowed rows leave a plan that runs, every other one fails it."""
+    A = (banded(6000, OFFS, 4, vary=OFFS) if matrix == "diagonals"
+         else near_band((1 << 20) + 333, 5, False))
+    x = torch.from_numpy(w.uniform_vectors(A.n, 1, 1)).cuda()
+    M = types.SimpleNamespace(n=A.n, rowptr=torch.from_numpy(A.rowptr).cuda(),
+                              col=torch.from_numpy(A.col).cuda(),
+                              val=torch.from_numpy(A.val).cuda()) if device else A
+    with allocations(lambda i, b: i == nth[0]) as sizes:
+        nth = [-1]
+        P = mpk.Plan(M, reorder=reorder)
+        count, ref = len(sizes), P.run_baseline(x, 2)
+        P.sync()
+        P.close()
+        done = 0
+        for k in range(count):
+            nth[0] = len(sizes) + k
+            try:
+                P = mpk.Plan(M, reorder=reorder)
+            except mpk.MPKError as e:
+                assert "ENOMEM" in str(e)
+                continue
+            nth[0] = -1
+            done += 1
+            assert torch.equal(P.run_baseline(x, 2), ref) and torch.equal(P.run(x, 2), ref)
+            P.sync()
+            P.close()
+    assert done == optional
