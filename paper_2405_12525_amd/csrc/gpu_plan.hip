@@ -776,7 +776,8 @@ __global__ void dia_count_kernel(int64_t n, const int32_t *drow, const int32_t *
                                     h = (h ^ (m & 0xffffffffull)) * kHashPrime;
                                     h = (h ^ (m >> 32)) * kHashPrime;
                                 }
-                                h = (h ^ (t.same ? t.lead_bits * 2 + 1 : 0)) * kHashPrime;
+                                h = (h ^ (t.same ? 1 : 0)) * kHashPrime;
+                                h = (h ^ (t.same ? t.lead_bits : 0)) * kHashPrime;
                                 c.hash = h ^ (h >> 29);
                                 if (!t.same) ++c.vblocks;
                                 c.lo = min(c.lo, t.off);

@@ -633,3 +633,61 @@ def test_plans_do_without_layouts_that_memory_is_short_for(matrix, reorder, opti
             P.sync()
             P.close()
     assert done == optional
+
+
+def two_lists(a, b, n=12800):
+    """Offsets 0 and 5, their values a[0], a[1] and b[0], b[1] in alternating
+    slices of 128 rows."""
+    rp, cols, vals = [0], [], []
+    for i in range(n):
+        v = (a, b)[i // 128 % 2]
+        cols += [c for c in (i, i + 5) if c < n]
+        vals += v[:len(cols) - rp[-1]]
+        rp.append(len(cols))
+    return w.CSR(n, np.array(rp, np.int32), np.array(cols, np.int32), np.array(vals, np.float64))
+
+
+def plan_sizes(A):
+    with allocations(lambda i, b: False) as sizes:
+        P = mpk.Plan(A, reorder="none")
+        P.close()
+    return list(sizes)
+
+
+@pytest.mark.parametrize("a,b", [((1.0, 2.0), (-1.0, 2.0)), ((0.0, 2.0), (-0.0, 2.0)),
+                                 ((1.0, -2.0), (-1.0, 2.0))])
+def test_lists_that_differ_in_a_sign_are_shared(a, b):
+    """Two lists that differ in a value's sign: each is stored once, as two
+    that differ in a value are."""
+    assert plan_sizes(two_lists(a, b)) == plan_sizes(two_lists((1.0, 2.0), (3.0, 2.0)))
+    check(two_lists(a, b), 1)
+    check(two_lists(a, b), 2)
+
+
+def list_hash(values):
+    """State of the hash of a list of offsets 0 and 5 that every row has, before
+    its last value is mixed in."""
+    h, mask = 1469598103934665603, (1 << 64) - 1
+    for off, v in zip((0, 5), list(values) + [None]):
+        for word in (off, 0xffffffff, 0xffffffff, 0xffffffff, 0xffffffff, 1):
+            h = (h ^ word) * 1099511628211 & mask
+        if v is None:
+            return h
+        h = (h ^ int(np.float64(v).view(np.uint64))) * 1099511628211 & mask
+        h ^= h >> 29
+
+
+@pytest.mark.parametrize("R", [1, 2, 3])
+def test_different_lists_of_equal_hash(R):
+    """Two lists of the same hash: found out, and every slice gets its own."""
+    a, g = (1.0, 2.0), np.random.default_rng(1)
+    while True:
+        b0 = float(g.uniform(-2, 2))
+        bits = int(np.float64(a[1]).view(np.uint64)) ^ list_hash(a[:1]) ^ list_hash([b0])
+        b1 = float(np.uint64(bits).view(np.float64))
+        if 0.01 < abs(b1) < 100:
+            break
+    A = two_lists(a, (b0, b1))
+    assert len(plan_sizes(A)) == len(plan_sizes(two_lists(a, (b0, 3.0)))) + 1   # built twice
+    check(A, R)
+    check(A, R, reorder="bfs")
