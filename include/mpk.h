@@ -513,9 +513,9 @@ mpk_status_t mpk_run_status(mpk_plan_t plan, void *hip_stream, int32_t *status);
  * times again and are compared on the mean of all their timed runs.  A plan whose tuning has
  * dynamic_tickets = 1 when the call starts keeps the shared counter in every
  * candidate.  Results are cached per (matrix fingerprint, value precision,
- * p, nrhs, recur, that dynamic_tickets): a later call with the same key
- * applies the cached tuning (the plan's spin_limit_us kept) without timing
- * unless force != 0.
+ * the layouts that the values allow, p, nrhs, recur, that dynamic_tickets): a
+ * later call with the same key applies the cached tuning (the plan's
+ * spin_limit_us kept) without timing unless force != 0.
  * recur: 0 = time mpk_run, 1 = mpk_run_recur, 2 = the weighted sums of
  * mpk_run_poly (p >= 4; their kernels differ from the plain run's).
  * x: n*nrhs doubles, Y: p*n*nrhs doubles (device scratch; overwritten).

@@ -2124,10 +2124,15 @@ mpk_status_t mpk_plan_autotune(mpk_plan_t plan, const double *x, int p, int nrhs
     // a plan set to the shared counter (for runs beside other kernels) keeps
     // it in every candidate
     const int keep_dyn = base.dynamic_tickets;
-    using Key = std::tuple<uint64_t, int, int, int, int, int>;
+    // the layouts depend on the values, which the fingerprint leaves out (of the
+    // diagonals' own values, the share of the entries in quarters)
+    const int64_t own = plan->dsl ? plan->dval_bytes * 4 / (plan->nnz * (plan->value_bits / 8)) : 0;
+    const int64_t layouts = ((plan->dsl ? 1 + plan->dgroups : 0) * 2 + (plan->d_win.ptr ? 1 : 0)) * 64 +
+                            std::min<int64_t>(own, 63);
+    using Key = std::tuple<uint64_t, int, int, int, int, int, int64_t>;
     static std::mutex cache_mu;
     static std::map<Key, std::pair<mpk_tune_t, double>> cache;
-    const Key key{plan->fingerprint, plan->value_bits, p, nrhs, recur, keep_dyn};
+    const Key key{plan->fingerprint, plan->value_bits, p, nrhs, recur, keep_dyn, layouts};
     if (!force) {
         std::pair<mpk_tune_t, double> hit;
         bool found = false;

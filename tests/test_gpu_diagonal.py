@@ -691,3 +691,19 @@ def test_different_lists_of_equal_hash(R):
     assert len(plan_sizes(A)) == len(plan_sizes(two_lists(a, (b0, 3.0)))) + 1   # built twice
     check(A, R)
     check(A, R, reorder="bfs")
+
+
+def test_autotuned_choices_of_constant_and_general_values_are_kept_apart():
+    """One pattern, one value per diagonal and then a value per entry: the second
+    is timed on its own (a choice taken over brings its time along), and a
+    general matrix of other values takes that choice over."""
+    A, B, C = (w.stencil_3d27(23) for _ in range(3))
+    B.val = np.random.default_rng(1).standard_normal(A.nnz)
+    C.val = np.random.default_rng(2).standard_normal(A.nnz)
+    x = torch.from_numpy(w.uniform_vectors(A.n, 1, 1)).cuda()
+    times = []
+    for M in (A, B, C):
+        P = mpk.Plan(M)
+        times.append(P.autotune(x, 5, reps=1)["ms"])
+        P.close()
+    assert times[0] != times[1] and times[1] == times[2]
