@@ -100,6 +100,14 @@ struct DevBuf {
     template <typename T> T *as() const { return static_cast<T *>(ptr); }
 };
 
+// Zeros, there when the call returns: hipMemset only enqueues them on the null
+// stream, which a run's own stream does not wait for, and a workspace cleared in
+// the middle of its run loses completion flags and tickets.
+hipError_t clear_now(void *dst, size_t bytes) {
+    const std::vector<char> zeros(bytes, 0);
+    return hipMemcpy(dst, zeros.data(), bytes, hipMemcpyHostToDevice);
+}
+
 // Slice table of one right-hand-side count (the staging buffer holds a fixed
 // number of products, so the nonzeros per slice depend on R).
 struct SliceSet {
@@ -374,8 +382,8 @@ mpk_status_t get_workspace(mpk_plan_t plan, int32_t n_chunks, hipStream_t stream
     const size_t words = (size_t)w->cap + kMaxQueues + 2;
     mpk_status_t st = w->buf.alloc(words * sizeof(int32_t));
     if (st) return st;
-    hipError_t e = hipMemset(w->buf.ptr, 0, words * sizeof(int32_t));
-    if (e != hipSuccess) return hip_fail(e, "hipMemset");
+    hipError_t e = clear_now(w->buf.ptr, words * sizeof(int32_t));
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy (workspace)");
     e = hipEventCreateWithFlags(&w->ev, hipEventDisableTiming);
     if (e != hipSuccess) return hip_fail(e, "hipEventCreate");
     *out = w.get();
@@ -738,8 +746,8 @@ mpk_status_t init_device_state(mpk_plan_t plan) {
     }
     mpk_status_t st = plan->status_words.alloc(kStatusSlots * sizeof(int32_t));
     if (st) return st;
-    hipError_t e = hipMemset(plan->status_words.ptr, 0, kStatusSlots * sizeof(int32_t));
-    return e == hipSuccess ? MPK_OK : hip_fail(e, "hipMemset");
+    hipError_t e = clear_now(plan->status_words.ptr, kStatusSlots * sizeof(int32_t));
+    return e == hipSuccess ? MPK_OK : hip_fail(e, "hipMemcpy (status words)");
 }
 
 // Workgroups of the level-blocked kernel the device holds at once (cached in

@@ -197,3 +197,12 @@ def test_results_write_through_and_publish_after_completion(asm, name):
         assert not any(l.startswith("buffer_wbl2") for l in body), sym
         assert any(l.startswith("buffer_inv sc1") for l in body), sym
         _publish_ok(lines)
+
+
+def test_host_code_has_cleared_memory_when_it_returns():
+    """Workspaces and failure words are cleared by copies that have ended when the
+    call returns: hipMemset only enqueues its fill, on the null stream, which runs
+    on other streams do not wait for (a workspace cleared in the middle of its run
+    loses completion flags, and the tasks that wait for them time out)."""
+    with open(os.path.join(ROOT, "paper_2405_12525_amd", "csrc", "capi.cpp")) as f:
+        assert re.findall(r"hipMemset\w*\(", f.read()) == []
