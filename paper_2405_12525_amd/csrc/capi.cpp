@@ -923,7 +923,7 @@ mpk_status_t launch_powers(mpk_plan_t plan, const SliceSet *sl, const double *x,
     const bool recur = alpha != nullptr;
     const size_t stride = (size_t)plan->n * nrhs;
     const DevMatrix m = plan->matrix();
-    if (dia_small(m)) {
+    if (dia_small(m, nrhs)) {
         for (int base = 0; base < p; base += kMaxSegPowers) {
             SegArgs a;
             Coefs cf;

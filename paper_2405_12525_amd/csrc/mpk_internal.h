@@ -310,14 +310,19 @@ inline bool few_elements(const DevMatrix &m, int R) {
 // less than a launch.  us for p = 16, launches (from the third on few_elements)
 // against this: 5-point 32^2 48 and 24, 64^2 53 and 45; Anderson 12^3 52 and 41;
 // 27-point 12^3 76 and 68; but Anderson 16^3 52 and 66, 5-point 90^2 55 and 79.
-// Rows with most values of their own read them through one compute unit: general
-// 27-point 12^3 76 and 85, with 16 right-hand sides 85 and 97.
+// Rows with values of their own read them through one compute unit in every
+// workgroup, which costs lists of more than two groups from 1024 rows (general
+// 27-point 8^3 73 and 49, 10^3 75 and 79, 12^3 76 and 85, with 16 right-hand sides
+// 85 and 97), shorter ones from 2048 with more than two right-hand sides (general
+// 5-point 45^2 with 1 and 16 52 and 31, 55 and 44; 64^2 with 1, 4 and 16 53 and
+// 48, 54 and 65, 55 and 78).
 constexpr int kSmallRows = 4096;
-inline bool dia_small(const DevMatrix &m) {
-    return m.dsl && (m.n <= kSmallRows / 2
-                         ? m.dgroups <= 8 && (m.n <= kSmallRows / 4 ||
-                                              m.dval_bytes <= (int64_t)m.n * 32)
-                         : m.n <= kSmallRows && m.dgroups <= 2);
+inline bool dia_small(const DevMatrix &m, int R) {
+    if (!m.dsl || m.n > kSmallRows) return false;
+    if (m.n <= kSmallRows / 4) return m.dgroups <= 8;
+    if (m.n <= kSmallRows / 2)
+        return m.dgroups <= 2 || (m.dgroups <= 8 && m.dval_bytes <= (int64_t)m.n * 32);
+    return m.dgroups <= 2 && (R <= 2 || m.dval_bytes <= (int64_t)m.n * 16);
 }
 
 constexpr int kMaxSegPowers = 64;   // powers per kernel launch

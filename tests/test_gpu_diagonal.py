@@ -707,3 +707,19 @@ def test_autotuned_choices_of_constant_and_general_values_are_kept_apart():
         times.append(P.autotune(x, 5, reps=1)["ms"])
         P.close()
     assert times[0] != times[1] and times[1] == times[2]
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 2048, 2049, 4096, 4097])
+@pytest.mark.parametrize("R", [1, 2, 3, 16])
+def test_small_matrices_around_the_limits_of_one_launch(n, R):
+    """One value per diagonal, a value per row on one of them, and on all; lists
+    of two groups and of three."""
+    for offs in (OFFS, OFFS + [41, 60]):
+        for vary in ((), (0,), tuple(offs)):
+            A = banded(n, offs, n, vary=vary)
+            x = w.uniform_vectors(n, R, 8)
+            P = mpk.Plan(A, reorder="none")
+            ref = oracle.powers(A, x, 4)
+            xd = torch.from_numpy(x).cuda()
+            assert np.array_equal(P.run(xd, 4).cpu().numpy().reshape(ref.shape), ref), (offs, vary)
+            P.close()
