@@ -413,13 +413,10 @@ __device__ __forceinline__ void load_2(double (&v)[2], const float *p) {
     v[1] = static_cast<double>(t.y);
 }
 // NT: past the caches (a vector too large to be read from them again).
-template <bool WT, bool NT>
+template <bool NT>
 __device__ __forceinline__ void store_2(double *p, const double (&v)[2]) {
     typedef double v2n __attribute__((ext_vector_type(2)));
-    if constexpr (WT) {
-        store_out<true>(p, v[0]);
-        store_out<true>(p + 1, v[1]);
-    } else if constexpr (NT) {
+    if constexpr (NT) {
         typedef v2n v2u __attribute__((aligned(8)));
         __builtin_nontemporal_store(v2n{v[0], v[1]}, reinterpret_cast<v2u *>(p));
     } else
@@ -428,7 +425,7 @@ __device__ __forceinline__ void store_2(double *p, const double (&v)[2]) {
 
 // accumulate and finish for two consecutive elements; y2: y_{k-2} there, where
 // needs_prev says so (loaded ahead of the sum).
-template <bool WT, bool NT>
+template <bool NT>
 __device__ __forceinline__ void accumulate_2(double *acc, int f, double w2, double w1, double w0,
                                              const double (&y2)[2], const double (&y1)[2],
                                              const double (&v)[2], size_t idx) {
@@ -455,13 +452,13 @@ __device__ __forceinline__ void accumulate_2(double *acc, int f, double w2, doub
             }
         }
     }
-    store_2<WT, NT>(acc + idx, r);
+    store_2<NT>(acc + idx, r);
 }
 template <bool ACC>
 __device__ __forceinline__ bool needs_prev(const PowerIO &io) {
     return (io.recur && io.prev && io.gamma != 0.0) || (ACC && ((io.fa | io.fb) & kAccT2));
 }
-template <bool WT, bool ACC, bool NT>
+template <bool ACC, bool NT>
 __device__ __forceinline__ void finish_2(const PowerIO &io, const double (&s)[2],
                                          const double (&y2)[2], size_t idx) {
     const bool b = io.recur && io.beta != 0.0;
@@ -482,10 +479,10 @@ __device__ __forceinline__ void finish_2(const PowerIO &io, const double (&s)[2]
             }
         }
     }
-    store_2<WT, NT>(io.out + idx, v);
+    store_2<NT>(io.out + idx, v);
     if constexpr (ACC) {
-        accumulate_2<WT, NT>(io.acc_a, io.fa, io.wa2, io.wa1, io.wa0, y2, y1, v, idx);
-        accumulate_2<WT, NT>(io.acc_b, io.fb, io.wb2, io.wb1, io.wb0, y2, y1, v, idx);
+        accumulate_2<NT>(io.acc_a, io.fa, io.wa2, io.wa1, io.wa0, y2, y1, v, idx);
+        accumulate_2<NT>(io.acc_b, io.fb, io.wb2, io.wb1, io.wb0, y2, y1, v, idx);
     }
 }
 
@@ -706,7 +703,7 @@ __device__ __forceinline__ void outer_sums(const DevMatrix &m, const double *in,
 
 // Pass q of slice s by one wave.  STREAM: the power's data is larger than the
 // memory-side cache: results are stored past it too.
-template <typename V, int MODE, bool WT, bool ACC, bool STREAM>
+template <typename V, int MODE, bool ACC, bool STREAM>
 __device__ __forceinline__ void dia_pass(const DevMatrix &m, const PowerIO &io, int32_t R,
                                          int32_t inv, int32_t s, int32_t q, int32_t keep) {
     const v8i ds = ld_const(reinterpret_cast<const v8i *>(m.dsl + s));
@@ -718,13 +715,13 @@ __device__ __forceinline__ void dia_pass(const DevMatrix &m, const PowerIO &io, 
         double y2[2] = {0.0, 0.0};
         if (needs_prev<ACC>(io)) load_2(y2, io.prev + idx);
         inner_sums<V, MODE, STREAM>(m, io.in, R, ds, s, l, whole, keep, sum);
-        finish_2<WT, ACC, STREAM>(io, sum, y2, idx);
+        finish_2<ACC, STREAM>(io, sum, y2, idx);
         return;
     }
     outer_sums<V, MODE>(m, io.in, R, ds, s, l, sum);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-        if (l.live[i]) finish<WT, ACC>(io, sum[i], idx + i);
+        if (l.live[i]) finish<false, ACC>(io, sum[i], idx + i);
 }
 
 // Products staged per thread and buffer: the slice path for R < 4 (R = 0 is
@@ -1091,8 +1088,8 @@ __global__ __launch_bounds__(kBlock, MODE == kOneRhs ? 8 : 1) void spmv_dia_kern
                       __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x / kWave));
     if (u >= units) return;
     const int32_t s = MODE == kOneRhs ? u : per(u);
-    dia_pass<V, MODE, false, ACC, STREAM>(m, io, MODE == kOneRhs ? 1 : R, inv, s,
-                                          MODE == kOneRhs ? 0 : u - s * per.d, keep);
+    dia_pass<V, MODE, ACC, STREAM>(m, io, MODE == kOneRhs ? 1 : R, inv, s,
+                                   MODE == kOneRhs ? 0 : u - s * per.d, keep);
 }
 
 // All powers of a segment in one launch: right-hand sides do not depend on each
