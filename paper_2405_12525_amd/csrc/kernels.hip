@@ -327,7 +327,6 @@ struct SpmvSellU {
 };
 constexpr int64_t kMallBytes = (int64_t)256 << 20;   // memory-side cache
 constexpr int64_t kSpmvSellGrid = 4096;   // baseline workgroups per power (sliced layout)
-constexpr int64_t kSpmvRowsGrid = 1 << 22;   // 2^30 threads: a launch holds fewer than 2^32
 // DEL: the columns come from the 16-bit offsets (col = row + offset, wrapped
 // into [0, n)).  NT: the matrix is loaded non-temporally: by the one-launch-
 // per-power baseline with one right-hand side, which reads each line once per
@@ -1639,25 +1638,27 @@ __global__ void xcc_probe_kernel(int32_t *out) {
 }
 
 // Rows of nvec vectors from one numbering to the other: thread (li, r) of a
-// block moves column r of one row in every vector, four vectors in flight.
+// block moves column r of one row in every vector, four vectors in flight, then
+// of a row a grid further on.
 template <bool SCATTER>
 __global__ __launch_bounds__(kBlock) void permute_kernel(const int32_t *src, int64_t n,
                                                          const double *in, double *out, int nvec,
                                                          int R) {
     const int rows = kBlock / R, li = (int)threadIdx.x / R, r = (int)threadIdx.x - li * R;
-    const int64_t i = (int64_t)blockIdx.x * rows + li;
-    if (li >= rows || i >= n) return;
-    const int64_t here = i * R + r, there = (int64_t)src[i] * R + r;
-    const int64_t from = SCATTER ? here : there, to = SCATTER ? there : here, vec = n * R;
-    int v = 0;
-    for (; v + 4 <= nvec; v += 4) {
-        double t[4];
+    if (li >= rows) return;
+    for (int64_t i = (int64_t)blockIdx.x * rows + li; i < n; i += (int64_t)gridDim.x * rows) {
+        const int64_t here = i * R + r, there = (int64_t)src[i] * R + r;
+        const int64_t from = SCATTER ? here : there, to = SCATTER ? there : here, vec = n * R;
+        int v = 0;
+        for (; v + 4 <= nvec; v += 4) {
+            double t[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) t[u] = in[(v + u) * vec + from];
+            for (int u = 0; u < 4; ++u) t[u] = in[(v + u) * vec + from];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) out[(v + u) * vec + to] = t[u];
+            for (int u = 0; u < 4; ++u) out[(v + u) * vec + to] = t[u];
+        }
+        for (; v < nvec; ++v) out[v * vec + to] = in[v * vec + from];
     }
-    for (; v < nvec; ++v) out[v * vec + to] = in[v * vec + from];
 }
 
 // Complex states from the two weighted sums, on column pairs (column 2j the
@@ -2004,8 +2005,7 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, const 
     int64_t grid;
     int32_t per = 0;
     if (R >= 4) {
-        const int32_t step = kBlock / R;
-        grid = std::min<int64_t>(((int64_t)m.n + step - 1) / step, kSpmvRowsGrid);
+        grid = row_grid(m.n, kBlock / R);
         if (r_index(R) == 5) {
             hipLaunchKernelGGL(spmv_rows_fn(m.value_bits, acc != nullptr), dim3((unsigned)grid),
                                dim3(kBlock), 0, (hipStream_t)stream, m, io, R);
@@ -2155,7 +2155,7 @@ int launch_permute(const int32_t *src, int64_t n, bool scatter, const double *in
                    int nvec, int R, void *stream) {
     if (R < 1 || R > 16 || nvec < 0) return (int)hipErrorInvalidValue;
     if (n == 0 || nvec == 0) return 0;
-    const int64_t rows = kBlock / R, grid = (n + rows - 1) / rows;
+    const int64_t grid = row_grid(n, kBlock / R);
     hipLaunchKernelGGL(scatter ? permute_kernel<true> : permute_kernel<false>,
                        dim3((unsigned)grid), dim3(kBlock), 0, (hipStream_t)stream, src, n, in, out,
                        nvec, R);

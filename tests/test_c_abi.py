@@ -40,3 +40,13 @@ def test_host_only_plan_from_c(tmp_path):
     assert rows["bad_tune"] == [str(_capi.MPK_EINVAL)]
     assert rows["run_host_only"] != [str(_capi.MPK_OK)]
     assert rows["version"][0].startswith("mpk-mi355x")
+
+
+@pytest.mark.skipif(not shutil.which("g++"), reason="needs g++")
+def test_launches_of_rows_hold_fewer_threads_than_a_launch_can(tmp_path):
+    exe = tmp_path / "launch_limits"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", f"-I{ROOT}/include",
+                    f"-I{ROOT}/paper_2405_12525_amd/csrc",
+                    os.path.join(ROOT, "tests", "c", "launch_limits.cpp"), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
