@@ -1638,27 +1638,25 @@ __global__ void xcc_probe_kernel(int32_t *out) {
 }
 
 // Rows of nvec vectors from one numbering to the other: thread (li, r) of a
-// block moves column r of one row in every vector, four vectors in flight, then
-// of a row a grid further on.
+// block moves column r of one row in every vector, four vectors in flight.
 template <bool SCATTER>
 __global__ __launch_bounds__(kBlock) void permute_kernel(const int32_t *src, int64_t n,
                                                          const double *in, double *out, int nvec,
                                                          int R) {
     const int rows = kBlock / R, li = (int)threadIdx.x / R, r = (int)threadIdx.x - li * R;
-    if (li >= rows) return;
-    for (int64_t i = (int64_t)blockIdx.x * rows + li; i < n; i += (int64_t)gridDim.x * rows) {
-        const int64_t here = i * R + r, there = (int64_t)src[i] * R + r;
-        const int64_t from = SCATTER ? here : there, to = SCATTER ? there : here, vec = n * R;
-        int v = 0;
-        for (; v + 4 <= nvec; v += 4) {
-            double t[4];
+    const int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * rows + li;
+    if (li >= rows || i >= n) return;
+    const int64_t here = i * R + r, there = (int64_t)src[i] * R + r;
+    const int64_t from = SCATTER ? here : there, to = SCATTER ? there : here, vec = n * R;
+    int v = 0;
+    for (; v + 4 <= nvec; v += 4) {
+        double t[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) t[u] = in[(v + u) * vec + from];
+        for (int u = 0; u < 4; ++u) t[u] = in[(v + u) * vec + from];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) out[(v + u) * vec + to] = t[u];
-        }
-        for (; v < nvec; ++v) out[v * vec + to] = in[v * vec + from];
+        for (int u = 0; u < 4; ++u) out[(v + u) * vec + to] = t[u];
     }
+    for (; v < nvec; ++v) out[v * vec + to] = in[v * vec + from];
 }
 
 // Complex states from the two weighted sums, on column pairs (column 2j the
@@ -2155,10 +2153,10 @@ int launch_permute(const int32_t *src, int64_t n, bool scatter, const double *in
                    int nvec, int R, void *stream) {
     if (R < 1 || R > 16 || nvec < 0) return (int)hipErrorInvalidValue;
     if (n == 0 || nvec == 0) return 0;
-    const int64_t grid = row_grid(n, kBlock / R);
+    const int64_t rows = kBlock / R, x = row_grid(n, rows), y = (n + x * rows - 1) / (x * rows);
     hipLaunchKernelGGL(scatter ? permute_kernel<true> : permute_kernel<false>,
-                       dim3((unsigned)grid), dim3(kBlock), 0, (hipStream_t)stream, src, n, in, out,
-                       nvec, R);
+                       dim3((unsigned)x, (unsigned)y), dim3(kBlock), 0, (hipStream_t)stream, src, n,
+                       in, out, nvec, R);
     return (int)hipGetLastError();
 }
 

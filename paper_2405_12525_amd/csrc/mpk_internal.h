@@ -471,8 +471,9 @@ int launch_lb(const DevMatrix &m, const DevSchedule &s, const DevWorkspace &ws,
 int launch_step(const DevMatrix &m, DevSlices sl, const int32_t *chunk_sptr,
                 const int32_t *chunk_row, const int32_t *tasks, int32_t n_tasks,
                 const SegArgs &a, const Coefs *cf, const AccCoefs *acc, void *stream);
-// Workgroups of 256 threads for n rows, `rows` at a time, that walk on by the
-// grid: a launch holds fewer than 2^32 threads, here at most 2^30.
+// Workgroups of 256 threads for n rows, `rows` at a time: a grid holds fewer than
+// 2^32 threads in a direction, here at most 2^30, and goes on in another, or the
+// workgroups walk on by it.
 inline int64_t row_grid(int64_t n, int64_t rows) {
     const int64_t blocks = (n + rows - 1) / rows, most = (int64_t)1 << 22;
     return blocks < most ? blocks : most;
