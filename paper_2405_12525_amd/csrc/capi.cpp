@@ -991,19 +991,20 @@ bool library_order(const mpk_tune_t &t) {
 //   sizes.  Several right-hand sides: below 2^19 elements (p = 8, us: 27-point
 //   52^3 with 3 in plan order 264 against 143, 56^3, beyond, equal; 16 entries a row
 //   within +-2000, 250 k rows with 2 192 against 163).  One: with 32-bit columns
-//   and on lattices of at most two lists, too (random columns, 350 k and 450 k
-//   rows 396 and 470 against 360 and 423; 5-point 700^2 in plan order 94 against
-//   79).  With other lists and 16-bit offsets below 2^18 rows (27-point 60^3 and
-//   64^3 162 and 147 against 151 and 159; 8 entries within +-2000, 200 k and 300 k
-//   rows 0.95 and 1.32 of the persistent kernel's time), without any lists below
-//   3 M entries (16 within +-2000, 170 k and 200 k rows 0.91 and 1.15), of at most
-//   32 a row, whose two-slot batches are the time (33, 40 and 100, 30 k rows:
-//   1.04, 1.13 and 1.58), unless few_elements has its own.
+//   and on lattices of at most eight entries a row, too (random columns, 350 k and
+//   450 k rows 396 and 470 against 360 and 423; in plan order 5-point 700^2 94
+//   against 79, Anderson 64^3 77 against 62).  On other lattices and with 16-bit
+//   offsets below 2^18 rows (27-point 60^3 and 64^3 162 and 147 against 151 and 159;
+//   8 entries within +-2000, 200 k and 300 k rows 0.95 and 1.32 of the persistent
+//   kernel's time), without any lists below 3 M entries (16 within +-2000, 170 k
+//   and 200 k rows 0.91 and 1.15), of at most 32 a row, whose two-slot batches are
+//   the time (33, 40 and 100, 30 k rows: 1.04, 1.13 and 1.58), unless few_elements
+//   has its own.
 bool powers_in_turn(mpk_plan_t plan, const DevMatrix &m, int nrhs, bool lines_can) {
     if (m.dsl) return true;
     if (!m.scol) return plan->longest_row <= kSpmvKP * 256;
     if (!lines_can || few_elements(m, nrhs)) return true;
-    if (nrhs > 1 || !m.sdel || (plan->dsl && plan->dgroups <= 2))
+    if (nrhs > 1 || !m.sdel || (plan->dsl && plan->nnz <= 8 * plan->n))
         return plan->n * nrhs < (int64_t)1 << 19;
     return plan->n < (int64_t)1 << 18 && plan->nnz <= 32 * plan->n &&
            (plan->dsl || plan->nnz < (int64_t)3 << 20);
@@ -1052,7 +1053,7 @@ bool worth_converting(mpk_plan_t plan, int nrhs, bool lines_can) {
     if (!plan->dia_converts() || !dia_addressable(plan->matrix(true), nrhs) ||
         plan->n * nrhs < (int64_t)1 << (nrhs == 1 ? 19 : 23))
         return false;
-    return nrhs > 1 || !lines_can || plan->nnz > 6 * plan->n || plan->n < (int64_t)1 << 20 ||
+    return nrhs > 1 || !lines_can || plan->nnz > 6 * plan->n || plan->n <= (int64_t)1 << 20 ||
            plan->n > (int64_t)13 << 18;
 }
 
