@@ -587,8 +587,11 @@ mpk_status_t build_dia(mpk_plan_t plan) {
 mpk_status_t build_win(mpk_plan_t plan) {
     const int64_t n = plan->n, nnz = plan->nnz;
     if (plan->d_scol.ptr ? plan->dsl || n < kWinMinRows : n == 0) return MPK_OK;
+    int32_t longest = 0;
+#pragma omp parallel for schedule(static) reduction(max : longest) if (n > 65536)
     for (int64_t r = 0; r < n; ++r)
-        plan->longest_row = std::max(plan->longest_row, plan->rowptr[r + 1] - plan->rowptr[r]);
+        longest = std::max(longest, plan->rowptr[r + 1] - plan->rowptr[r]);
+    plan->longest_row = longest;
     // (win_rows_kernel's row word holds lengths below 2^22)
     static_assert((INT32_MAX >> kWinRowShift) < 1 << 22, "length field");
     if (n < kWinMinRows || nnz < 4 * n || plan->longest_row > nnz >> kWinRowShift) return MPK_OK;
