@@ -959,9 +959,10 @@ __global__ __launch_bounds__(kWave) void spmv_few_kernel(DevMatrix m, PowerIO io
 // input row is gathered from memory about twice a power (a ring's first fill
 // included) instead of once per entry, and the entries gather from LDS.  Random
 // band, 2^22 rows, 67 M entries: 274 us per power against 400 from CSR rows
-// staged in LDS, whose gathers take a cache line each; 670 MB of entries at
-// 2.4 TB/s, bound by the chain of loads, sum and barriers of a chunk (13 us with
-// one workgroup per compute unit, which the ring allows).
+// staged in LDS, whose gathers take a cache line each.  670 MB of entries, but 1.68
+// GB leave the L2, 6.1 TB/s: in the caller's numbering a ring's rows lie apart, and
+// each of the two loads of a row takes a 128-byte line (in plan order 1.3 M rows
+// take 49 us per power, here 98).
 template <typename V, bool ACC>
 __global__ __launch_bounds__(kWinRows) void spmv_win_kernel(DevMatrix m, PowerIO io, WinMatrix w,
                                                             int32_t keep) {
@@ -1071,12 +1072,12 @@ FastDiv fast_div(int32_t d) {
 // passes per slice); workgroup b runs on XCD b mod 8, and the blocks are dealt
 // in runs: XCD x takes run x, then run x + 8, ...
 //
-// Bound by: 27-point 128^3, one right-hand side: 18.6 us per power against
-// 125 from the sliced layout; the texture units (27 loads of 1 KB per 128 rows,
-// 453 MB at 24 TB/s) and launches are the time, HBM traffic is 35 MB.  With
-// general coefficients 71 against 125 us: 446 MB of values and 34 MB of
-// vectors, 6.7 TB/s.  Anderson 160^3 with 8 right-hand sides, recurrence: 185
-// against 364 us, 800 MB of vectors, 4.3 TB/s (a 4 GB copy: 4.8 TB/s).
+// Bound by: 27-point 128^3, one right-hand side: 18.5 us per power against
+// 125 from the sliced layout; the vector caches (27 loads of 1 KB per 128 rows are
+// 453 MB, and 615 MB of 64-byte accesses as they lie: 33 TB/s) and launches are
+// the time, 37 MB leave the L2.  With general coefficients 71 against 125 us: 486
+// MB leave it, 446 of them values, 6.8 TB/s.  Anderson 160^3 with 8 right-hand
+// sides, recurrence: 189 against 364 us, 818 MB, 4.3 TB/s (a 4 GB copy: 4.8 TB/s).
 template <typename V, int MODE, bool ACC, bool STREAM>
 __global__ __launch_bounds__(kBlock, MODE == kOneRhs ? 8 : 1) void spmv_dia_kernel(
         DevMatrix m, PowerIO io, int32_t R, int32_t inv, int32_t units, FastDiv per, FastDiv run,
@@ -1979,9 +1980,10 @@ int launch_spmv_power(const DevMatrix &m, DevSlices sl, int32_t n_slices, const 
         // (256 MiB).  Where it does not fit, results go past the cache (160^3
         // with 8 right-hand sides 190 -> 180 us; 27-point 64^3 with 16, which
         // fits, 31.5 -> 38), and of every 16 slices' values only as many are
-        // cached as fit beside the vectors: those stay from one power to the
-        // next while the others stream (27-point 128^3, 446 MB of values: none
-        // cached 82 us, half 71, all 88).
+        // cached as fit beside 32 MB, the vectors of this size with one
+        // right-hand side: those stay from one power to the next while the
+        // others stream (27-point 128^3, 446 MB of values: none cached 82 us,
+        // half 71, all 88).
         const int64_t vecs = (int64_t)m.n * R * 8 * (recur && inm1 ? 3 : 2);
         const bool past = vecs + m.dval_bytes > kMallBytes - ((int64_t)16 << 20);
         const int32_t keep = (int32_t)std::min<int64_t>(
