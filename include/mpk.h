@@ -358,8 +358,9 @@ mpk_status_t mpk_run_recur(mpk_plan_t plan, const double *x, int p, int nrhs,
                            double *Y, void *hip_stream);
 
 /*
- * Baseline: p back-to-back CSR SpMVs, one kernel launch per power (Alg. 1
- * without halo exchange), on the plan's matrix.  Every kernel of this
+ * Baseline: p back-to-back CSR SpMVs, one kernel launch per power (small
+ * matrices: one for all powers; Alg. 1 without halo exchange), on the plan's
+ * matrix.  Every kernel of this
  * library forms each entry of y_k as the plain CSR sum: products rounded one
  * by one, added left to right in stored order from 0.0 (no fused
  * multiply-add), so baseline and level-blocked results are bit-identical.
