@@ -203,6 +203,7 @@ struct mpk_plan_s {
     const int32_t *drow = nullptr;           // caller's row -> plan row (permuted plans)
     int32_t dgroups = 0, dreach = 0;
     int64_t dval_bytes = 0;
+    int32_t drest = 0;                       // slices without a list
     int32_t longest_row = 0;                 // entries (without the sliced layout)
     int64_t sell_entries = 0;
     std::map<int, std::unique_ptr<SliceSet>> spmv_slices;  // p x SpMV, by slice size
@@ -233,7 +234,7 @@ struct mpk_plan_s {
                          callers ? nullptr : d_scol.as<int32_t>(), d_sdel.as<int16_t>(),
                          d_sval.ptr,
                          dia ? dsl : nullptr, dgroup, dmask, dvals, drow, dgroups,
-                         dreach, dval_bytes};
+                         dreach, dval_bytes, drest};
     }
     ~mpk_plan_s() {
         if (!host_only) {
@@ -561,6 +562,7 @@ mpk_status_t build_dia(mpk_plan_t plan) {
             plan->dmask = dmask;
             plan->dvals = dvals;
             plan->drow = drow;
+            plan->drest = (int32_t)(n_sl - taken);
             plan->dval_bytes = blocks * kDiaRows * (plan->value_bits / 8);
             std::vector<int32_t> reach;
             for (const DiaCount &c : cnt) {
@@ -981,7 +983,12 @@ bool library_order(const mpk_tune_t &t) {
 // slower
 // * wherever the plan has diagonal slices (5-point 64^2, p = 4: 33 against 18 us;
 //   27-point 128^3, p = 8: 1067 against 156 us; Anderson 160^3 with 8 right-hand
-//   sides, p = 16: 7568 against 3023 us);
+//   sides, p = 16: 7568 against 3023 us), unless more than a quarter of them
+//   have no list, most values are their own and one right-hand side is large (16
+//   entries a row, 20, 30 and 45% of the slices irregular, p = 8: 500 k rows 189,
+//   192 and 206 against 173, 201 and 225 us, 2 M rows 606, 633 and 672 against 613,
+//   718 and 894; with one value for all, 2 M rows, 30 and 45%, 632 and 672 against
+//   444 and 608);
 // * on CSR rows: random bands of 8192, 60 k, 200 k and 800 k rows, p = 8, one
 //   right-hand side 66, 110, 231 and 681 against 42, 61, 182 and 544 us, four 130,
 //   169, 332 and 1465 against 42, 94, 249 and 895, sixteen (to 400 k) 339, 441, 850
@@ -1004,7 +1011,10 @@ bool library_order(const mpk_tune_t &t) {
 //   the time (33, 40 and 100, 30 k rows: 1.04, 1.13 and 1.58), unless few_elements
 //   has its own.
 bool powers_in_turn(mpk_plan_t plan, const DevMatrix &m, int nrhs, bool lines_can) {
-    if (m.dsl) return true;
+    if (m.dsl)
+        return nrhs > 1 || !lines_can || plan->n < (int64_t)3 << 17 ||
+               (int64_t)plan->drest * 4 * kDiaRows <= plan->n ||
+               2 * plan->dval_bytes <= plan->nnz * (plan->value_bits / 8);
     if (!m.scol) return plan->longest_row <= kSpmvKP * 256;
     if (!lines_can || few_elements(m, nrhs)) return true;
     if (nrhs > 1 || !m.sdel || (plan->dsl && plan->nnz <= 8 * plan->n))

@@ -662,7 +662,45 @@ __device__ __forceinline__ void inner_sums(const DevMatrix &m, const double *in,
     else
         dia_sum<V, MODE, kDiaPerRow, false>(m, in, ds[0], ds[1], vals, l, rbytes, whole, sum);
 }
-// The same in any other slice; sets l.live.
+// The same from the sliced layout's rows.  Two right-hand sides of a row share its
+// slots: a wave that read them once for each held up matrices with many such
+// slices (16 entries a row, nearly every other 256 rows irregular, 250 k rows, us
+// per power with 2 and 4 right-hand sides, before and now: 25 and 16; 30 and 19).  Two
+// rows go one after the other: both at once do not fit 64 registers.
+template <typename V, int MODE>
+__device__ __forceinline__ void row_sums(const DevMatrix &m, const double *in, int32_t R,
+                                         int32_t s, const DiaLane &l, double (&sum)[2]) {
+    constexpr int N = MODE == kEven ? 2 : 1;   // elements of a row
+    const V *sval = static_cast<const V *>(m.sval);
+#pragma unroll
+    for (int i = 0; i < 2; i += N) {
+        if (!l.live[i]) continue;
+        const int32_t row = s * kDiaRows + l.row[i], pr = m.drow ? m.drow[row] : row;
+        const int32_t rr = (int32_t)(l.at / 8u + i - (uint32_t)row * (uint32_t)R);
+        const int32_t L = m.rlen[pr];
+        const int64_t b = m.soff[pr / kSellRows] + pr % kSellRows;
+        double t[N] = {};
+        for (int32_t j = 0; j < L; j += 4) {
+            double a[4], x[4][N];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t c = b + (int64_t)min(j + u, L - 1) * kSellRows;
+                a[u] = static_cast<double>(sval[c]);
+                const double *at = in + (size_t)m.scol[c] * R + rr;
+                if constexpr (N == 2) load_2(x[u], at);
+                else x[u][0] = *at;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int k = 0; k < N; ++k)
+                    if (j + u < L) t[k] = t[k] + a[u] * x[u][k];
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) sum[i + k] = t[k];
+    }
+}
+// The same in any slice but an inner one; sets l.live.
 template <typename V, int MODE>
 __device__ __forceinline__ void outer_sums(const DevMatrix &m, const double *in, int32_t R,
                                            const v8i &ds, int32_t s, DiaLane &l,
@@ -673,30 +711,8 @@ __device__ __forceinline__ void outer_sums(const DevMatrix &m, const double *in,
         const V *vals = static_cast<const V *>(m.dvals) + (size_t)ds[2] * kDiaRows;
         dia_sum<V, MODE, kDiaMixed, false, true, false>(m, in, ds[0], ds[1], vals, l,
                                                         R * (int32_t)sizeof(double), sum);
-    } else {   // rows as the sliced layout holds them
-        const V *sval = static_cast<const V *>(m.sval);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            if (!l.live[i]) continue;
-            const int32_t row = s * kDiaRows + l.row[i], pr = m.drow ? m.drow[row] : row;
-            const int32_t rr = (int32_t)(l.at / 8u + i - (uint32_t)row * (uint32_t)R);
-            const int32_t L = m.rlen[pr];
-            const int64_t b = m.soff[pr / kSellRows] + pr % kSellRows;
-            double t = 0.0;
-            for (int32_t j = 0; j < L; j += 4) {
-                double a[4], x[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int64_t c = b + (int64_t)min(j + u, L - 1) * kSellRows;
-                    a[u] = static_cast<double>(sval[c]);
-                    x[u] = in[(size_t)m.scol[c] * R + rr];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (j + u < L) t = t + a[u] * x[u];
-            }
-            sum[i] = t;
-        }
+    } else {
+        row_sums<V, MODE>(m, in, R, s, l, sum);
     }
 }
 

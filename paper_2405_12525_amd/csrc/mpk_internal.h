@@ -273,6 +273,7 @@ struct DevMatrix {
     int32_t dgroups;          // groups of the longest list
     int32_t dreach;           // the farthest diagonal of a typical slice, in rows
     int64_t dval_bytes;       // of the per-row values
+    int32_t drest;            // slices that are read in the sliced layout
 };
 
 // Whether a run of R right-hand sides reads the diagonal slices: their gathers
@@ -281,14 +282,24 @@ struct DevMatrix {
 // the time, where the sliced layout has twice the waves: 27-point 24^3 with 4
 // right-hand sides 7.9 against 6.8 us per power, 48^3 10.2 against 17.3 us;
 // lists of two groups are short enough (5-point 100^2 with 4: 3.6 against 4.0).
-// One right-hand side gains at every size, by its 16-byte loads.
+// One right-hand side gains at every size, by its 16-byte loads.  Of an odd
+// number, a wave reads its rows one after the other in slices without a list, and
+// a sixth of such slices makes the sliced layout faster up to 2^21 elements (16
+// entries a row, 20, 30 and 45% of the slices irregular, 3 right-hand sides, us per
+// power, sliced and diagonals: 250 k rows 21.6 and 21.8, 22.9 and 26.3, 24.1 and
+// 31.7; 500 k rows 36.7 and 36.8, 38.6 and 44.5, 41.6 and 51.3; but 2 M rows 183 and
+// 158, 194 and 187, 212 and 235), a sixteenth below 2^18 (60 k rows, 10%: 7.5 and
+// 8.3).
 constexpr int64_t kDiaElements = 3 * 256 * 128;
 inline bool dia_addressable(const DevMatrix &m, int R) {
     return m.dsl && (int64_t)m.n * R * (int64_t)sizeof(double) < ((int64_t)1 << 32);
 }
 inline bool dia_fits(const DevMatrix &m, int R) {
-    return dia_addressable(m, R) &&
-           (R == 1 || m.dgroups <= 2 || (int64_t)m.n * R >= kDiaElements);
+    const int64_t elements = (int64_t)m.n * R, rest = (int64_t)m.drest * kDiaRows;
+    if (R > 1 && R % 2 && ((elements < (int64_t)1 << 21 && 6 * rest > m.n) ||
+                           (elements < (int64_t)1 << 18 && 16 * rest > m.n)))
+        return false;
+    return dia_addressable(m, R) && (R == 1 || m.dgroups <= 2 || elements >= kDiaElements);
 }
 
 // Whether a power is too small to fill the device, and takes as long as one
