@@ -996,7 +996,10 @@ bool library_order(const mpk_tune_t &t) {
 //   row, which one thread adds, and no other power's work goes on beside it: with
 //   a row of 6000 or 12000 entries among every 40000, 1.1 M rows, 1 to 4
 //   right-hand sides, the persistent kernel is up to 25% faster (natural order,
-//   four: 3% slower);
+//   four: 3% slower).  So is it for two and three, whose slices end with their
+//   longest rows too, where rows are very uneven (22 entries on average, 520 at
+//   most, p = 6, 300 k rows, 1 to 4 right-hand sides: 260, 602, 675, 1491 against
+//   281, 657, 869, 1379 us);
 // * in the sliced layout, where its runs need the invalidation and at small
 //   sizes.  Several right-hand sides: below 2^19 elements (p = 8, us: 27-point
 //   52^3 with 3 in plan order 264 against 143, 56^3, beyond, equal; 16 entries a row
@@ -1015,7 +1018,10 @@ bool powers_in_turn(mpk_plan_t plan, const DevMatrix &m, int nrhs, bool lines_ca
         return nrhs > 1 || !lines_can || plan->n < (int64_t)3 << 17 ||
                (int64_t)plan->drest * 4 * kDiaRows <= plan->n ||
                2 * plan->dval_bytes <= plan->nnz * (plan->value_bits / 8);
-    if (!m.scol) return plan->longest_row <= kSpmvKP * 256;
+    if (!m.scol)
+        return plan->longest_row <= kSpmvKP * 256 &&
+               (nrhs == 1 || nrhs > 3 || plan->nnz < (int64_t)3 << 20 ||
+                plan->longest_row * plan->n <= 8 * plan->nnz);
     if (!lines_can || few_elements(m, nrhs)) return true;
     if (nrhs > 1 || !m.sdel || (plan->dsl && plan->nnz <= 8 * plan->n))
         return plan->n * nrhs < (int64_t)1 << 19;
