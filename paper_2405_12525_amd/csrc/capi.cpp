@@ -203,7 +203,7 @@ struct mpk_plan_s {
     const int32_t *drow = nullptr;           // caller's row -> plan row (permuted plans)
     int32_t dgroups = 0, dreach = 0;
     int64_t dval_bytes = 0;
-    int32_t drest = 0;                       // slices without a list
+    int16_t drest = 0;                       // of 4096 slices, those without a list
     int32_t longest_row = 0;                 // entries (without the sliced layout)
     int64_t sell_entries = 0;
     std::map<int, std::unique_ptr<SliceSet>> spmv_slices;  // p x SpMV, by slice size
@@ -229,12 +229,13 @@ struct mpk_plan_s {
     DevMatrix matrix(bool callers = false) const {
         const bool dia = callers || !dia_converts();
         return DevMatrix{d_rowptr.as<int32_t>(), d_col.as<int32_t>(), d_val.ptr,
-                         d_outrow.as<int32_t>(), (int32_t)n, value_bits,
+                         d_outrow.as<int32_t>(), (int32_t)n,
+                         (int16_t)value_bits, drest,
                          d_soff.as<const int64_t>(), d_rlen.as<int32_t>(),
                          callers ? nullptr : d_scol.as<int32_t>(), d_sdel.as<int16_t>(),
                          d_sval.ptr,
                          dia ? dsl : nullptr, dgroup, dmask, dvals, drow, dgroups,
-                         dreach, dval_bytes, drest};
+                         dreach, dval_bytes};
     }
     ~mpk_plan_s() {
         if (!host_only) {
@@ -562,7 +563,7 @@ mpk_status_t build_dia(mpk_plan_t plan) {
             plan->dmask = dmask;
             plan->dvals = dvals;
             plan->drow = drow;
-            plan->drest = (int32_t)(n_sl - taken);
+            plan->drest = (int16_t)((n_sl - taken) * 4096 / n_sl);
             plan->dval_bytes = blocks * kDiaRows * (plan->value_bits / 8);
             std::vector<int32_t> reach;
             for (const DiaCount &c : cnt) {
@@ -1016,7 +1017,7 @@ bool library_order(const mpk_tune_t &t) {
 bool powers_in_turn(mpk_plan_t plan, const DevMatrix &m, int nrhs, bool lines_can) {
     if (m.dsl)
         return nrhs > 1 || !lines_can || plan->n < (int64_t)3 << 17 ||
-               (int64_t)plan->drest * 4 * kDiaRows <= plan->n ||
+               plan->drest * 4 <= 4096 ||
                2 * plan->dval_bytes <= plan->nnz * (plan->value_bits / 8);
     if (!m.scol)
         return plan->longest_row <= kSpmvKP * 256 &&

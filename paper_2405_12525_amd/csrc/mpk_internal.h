@@ -254,7 +254,8 @@ struct DevMatrix {
     const void *val;          // double or float
     const int32_t *out_row;   // nullptr: output row = plan row
     int32_t n;
-    int32_t value_bits;
+    int16_t value_bits;
+    int16_t drest;            // of 4096 slices, those read in the sliced layout
     // the sliced layout (null when the plan has none: too much padding; or, with
     // dsl there, when its rows and columns are numbered otherwise than the vectors)
     const int64_t *soff;      // n_slices + 1 slot offsets
@@ -273,7 +274,6 @@ struct DevMatrix {
     int32_t dgroups;          // groups of the longest list
     int32_t dreach;           // the farthest diagonal of a typical slice, in rows
     int64_t dval_bytes;       // of the per-row values
-    int32_t drest;            // slices that are read in the sliced layout
 };
 
 // Whether a run of R right-hand sides reads the diagonal slices: their gathers
@@ -295,9 +295,9 @@ inline bool dia_addressable(const DevMatrix &m, int R) {
     return m.dsl && (int64_t)m.n * R * (int64_t)sizeof(double) < ((int64_t)1 << 32);
 }
 inline bool dia_fits(const DevMatrix &m, int R) {
-    const int64_t elements = (int64_t)m.n * R, rest = (int64_t)m.drest * kDiaRows;
-    if (R > 1 && R % 2 && ((elements < (int64_t)1 << 21 && 6 * rest > m.n) ||
-                           (elements < (int64_t)1 << 18 && 16 * rest > m.n)))
+    const int64_t elements = (int64_t)m.n * R;
+    if (R > 1 && R % 2 && ((elements < (int64_t)1 << 21 && 6 * m.drest > 4096) ||
+                           (elements < (int64_t)1 << 18 && 16 * m.drest > 4096)))
         return false;
     return dia_addressable(m, R) && (R == 1 || m.dgroups <= 2 || elements >= kDiaElements);
 }
