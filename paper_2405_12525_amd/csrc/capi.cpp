@@ -1078,10 +1078,11 @@ bool worth_converting(mpk_plan_t plan, int nrhs, bool lines_can) {
 }
 
 // Vectors that no unfinished run uses, for a converted run of nrhs right-hand
-// sides on `stream`: of the plan's own if there are, else one more (or, with
-// kVecSpaces there, an idle one made larger).  Null where every one is in use or
-// memory was short, once (plan->mu held; not under capture).
-VecSpace *get_vectors(mpk_plan_t plan, int nrhs, hipStream_t stream) {
+// sides on `stream`: of the plan's own if there are, else one more or an idle one
+// made larger, which waits for the device (so only with kVecSpaces there, or
+// `ahead` of runs).  Null where every one is in use or memory was short, once
+// (plan->mu held; not under capture).
+VecSpace *get_vectors(mpk_plan_t plan, int nrhs, hipStream_t stream, bool ahead = false) {
     const size_t bytes = 3 * (size_t)plan->n * nrhs * sizeof(double);
     auto idle = [&](const VecSpace &w) {
         return !w.recorded || hipEventQuery(w.ev) == hipSuccess;
@@ -1090,7 +1091,11 @@ VecSpace *get_vectors(mpk_plan_t plan, int nrhs, hipStream_t stream) {
         if (w->buf.bytes >= bytes && (w->last_stream == stream || idle(*w))) return w.get();
     if (plan->vectors_short) return nullptr;
     VecSpace *vs = nullptr;
-    if (plan->vectors.size() < kVecSpaces) {
+    if (ahead || plan->vectors.size() >= kVecSpaces)
+        for (auto &w : plan->vectors)
+            if (!vs && idle(*w)) vs = w.get();
+    if (!vs) {
+        if (plan->vectors.size() >= kVecSpaces) return nullptr;
         auto w = std::make_unique<VecSpace>();
         if (hipEventCreateWithFlags(&w->ev, hipEventDisableTiming) != hipSuccess) {
             w->ev = nullptr;
@@ -1098,13 +1103,11 @@ VecSpace *get_vectors(mpk_plan_t plan, int nrhs, hipStream_t stream) {
         }
         vs = w.get();
         plan->vectors.push_back(std::move(w));
-    } else {
-        for (auto &w : plan->vectors)
-            if (!vs && idle(*w)) vs = w.get();
-        if (!vs) return nullptr;
     }
     vs->recorded = false;
+    const size_t held = vs->buf.bytes;
     if (vs->buf.alloc(bytes)) {
+        if (held) (void)vs->buf.alloc(held);   // as it was, for fewer right-hand sides
         (void)hipGetLastError();
         plan->vectors_short = true;
         return nullptr;
@@ -2039,7 +2042,7 @@ mpk_status_t mpk_plan_prepare(mpk_plan_t plan, int p, int nrhs) {
     }
     // (without its own vectors a run takes them in the plan's order)
     if (library_order(plan->tune) && worth_converting(plan, nrhs, false))
-        (void)get_vectors(plan, nrhs, nullptr);
+        (void)get_vectors(plan, nrhs, nullptr, true);
     SliceSet *sl = nullptr;
     return spmv_slices(plan, nrhs, &sl);
 }

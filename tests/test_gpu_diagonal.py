@@ -789,3 +789,24 @@ def test_default_run_of_very_uneven_rows_is_no_slower_than_a_persistent_one():
     default, persistent = times_of_default_and_persistent_runs(P, x, 6)
     assert default < 1.12 * persistent
     P.close()
+
+
+def test_vectors_for_more_right_hand_sides_that_memory_is_short_for():
+    """One set for each count is made larger for the next by prepare; where that
+    fails, the smaller one stays and is used."""
+    A = w.stencil_3d27(101)
+    limit = [None]
+    with allocations(lambda i, b: limit[0] is not None and b > limit[0]) as sizes:
+        P = mpk.Plan(A, order="plan")
+        P.prepare([3], [1, 9])
+        limit[0] = 9 * 24 * A.n
+        P.prepare([3], [16])
+        before = len(sizes)
+        for R in (1, 9, 16):
+            x = torch.from_numpy(w.uniform_vectors(A.n, R, 2)).cuda()
+            Y = P.run(x, 3)
+            P.sync()
+            assert torch.equal(Y, P.run_baseline(x, 3)), R
+            P.sync()
+        assert len(sizes) == before
+        P.close()
